@@ -97,6 +97,8 @@ struct Derived {
     std::vector<uint8_t> flags;
     std::vector<int32_t> producer, out, in_off, in, ch_off, ch, adj_off, adj, rel_off, rel, req, consts;
     std::vector<dtr::TRecX> rec;
+    std::vector<dtr::SweepRec> sw;   // walk heuristics' sweep tables (make_sweep)
+    std::vector<uint16_t> sx;
     int64_t const_mem = 0;
     int64_t peak = 0;        // memory with no eviction: frees at release points (dispatch order)
 };
@@ -243,6 +245,38 @@ int validate_and_derive(const dtr_trace &tr, int32_t index, Derived &d)
     return DTR_OK;
 }
 
+// The sweep tables of a trace (layout.h): node o is operation o's output.
+void make_sweep(Derived &d)
+{
+    d.sw.resize((size_t)(d.F + dtr::WAVE - 1) / dtr::WAVE * dtr::WAVE);     // whole chunks, padded with zeros
+    std::memset(d.sw.data(), 0, d.sw.size() * sizeof(dtr::SweepRec));
+    std::vector<uint16_t> xp, xc;
+    for (int32_t o = 0; o < d.F; o++) {
+        dtr::SweepRec &r = d.sw[o];
+        const int32_t t = d.out[o];
+        r.c0 = (int32_t)d.c0[t];
+        xp.clear();
+        xc.clear();
+        auto edge = [&](int32_t v, uint64_t &row, std::vector<uint16_t> &ext) {
+            const int32_t p = d.producer[v];
+            if (p < 0) return;                      // a constant is never evicted
+            if (p / dtr::WAVE == o / dtr::WAVE) row |= uint64_t(1) << (p % dtr::WAVE);
+            else ext.push_back((uint16_t)p);
+        };
+        for (int32_t k = d.in_off[o]; k < d.in_off[o + 1]; k++) edge(d.in[k], r.rowp, xp);
+        for (int32_t k = d.ch_off[t]; k < d.ch_off[t + 1]; k++) edge(d.ch[k], r.rowc, xc);
+        r.nxp = (uint16_t)xp.size();
+        r.nxc = (uint16_t)xc.size();
+        for (size_t j = 0; j < dtr::SWEEP_HEAD; j++) {
+            r.xp[j] = j < xp.size() ? xp[j] : 0;
+            r.xc[j] = j < xc.size() ? xc[j] : 0;
+        }
+        r.xoff = (int32_t)d.sx.size();
+        d.sx.insert(d.sx.end(), xp.begin(), xp.end());
+        d.sx.insert(d.sx.end(), xc.begin(), xc.end());
+    }
+}
+
 // workspace: [header | trace tables | trace descriptors | specs | order | results | slots]
 struct Plan {
     std::vector<Derived> traces;
@@ -253,6 +287,7 @@ struct Plan {
     dtr::SlotLayout L{};
     int32_t n_slots = 0;
     bool static_only = false;        // runs only through dtr_sim_run_static: no slots in the workspace
+    int32_t sweep_chunks = 0;        // of the longest swept trace (0: none)
     std::vector<int32_t> order;
     int32_t class_count[dtr::N_GROUPS] = {0, 0, 0, 0, 0, 0};
 };
@@ -265,7 +300,7 @@ size_t trace_bytes(const Derived &d)
     return bytes_of(d.size) + bytes_of(d.c0) + bytes_of(d.flags) + bytes_of(d.producer) + bytes_of(d.out) +
            bytes_of(d.cost) + bytes_of(d.in_off) + bytes_of(d.in) + bytes_of(d.ch_off) + bytes_of(d.ch) +
            bytes_of(d.adj_off) + bytes_of(d.adj) + bytes_of(d.rel_off) + bytes_of(d.rel) + bytes_of(d.req) +
-           bytes_of(d.consts) + bytes_of(d.rec) + 8 * ALIGN;
+           bytes_of(d.consts) + bytes_of(d.rec) + bytes_of(d.sw) + bytes_of(d.sx) + 8 * ALIGN;
 }
 
 int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sims, int32_t n_sims,
@@ -285,6 +320,8 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
         if (rc) return rc;
     }
     bool need_uf = false, need_walk = false, need_banish = false;
+    // a small lane queue asks for the lane walks and the whole-wavefront ones
+    const bool sweep = !(opt && (opt->flags & DTR_OPT_WALK_QUEUE_SMALL));
     int32_t n_max = 1;
     for (int32_t i = 0; i < n_sims; i++) {
         const dtr_sim_spec &s = sims[i];
@@ -295,6 +332,12 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
         need_uf |= heuristic_class(s.heuristic) == 0;
         need_walk |= heuristic_class(s.heuristic) == 1;
         n_max = std::max(n_max, p.traces[s.trace].n);
+        Derived &d = p.traces[s.trace];
+        if (heuristic_class(s.heuristic) == 1 && sweep && d.F > 0 && d.F <= dtr::SWEEP_OPS &&
+            2 * (int64_t)d.n + 128 <= dtr::SWEEP_MAX_POOL) {
+            if (d.sw.empty()) make_sweep(d);
+            p.sweep_chunks = std::max(p.sweep_chunks, (d.F + dtr::WAVE - 1) / dtr::WAVE);
+        }
     }
     // slot layout
     dtr::SlotLayout &L = p.L;
@@ -314,7 +357,7 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     // walk heuristics: wavefronts per workgroup (more for large traces, whose
     // pools are long), a visited bitmap and a member queue per lane
     int32_t ww = opt ? (opt->flags >> DTR_OPT_WALK_WAVES_SHIFT) & 15 : 0;
-    if (ww == 0) ww = n_max >= 8192 ? dtr::MAX_WALK_WAVES : n_max >= 1024 ? 4 : 1;
+    if (ww == 0) ww = n_max >= 8192 ? dtr::MAX_WALK_WAVES : n_max >= 1024 ? 4 : p.sweep_chunks > 0 ? 2 : 1;
     L.walk_waves = need_walk ? ww : 1;
     const size_t lanes = (size_t)L.walk_waves * dtr::WAVE;
     L.vis_words = (int64_t)((n + 127) / 128 * 4);
@@ -522,6 +565,8 @@ int dtr_sim_create(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec
         D.req = put(d.req);
         D.consts = put(d.consts);
         D.rec = put(d.rec);
+        D.sw = d.sw.empty() ? nullptr : put(d.sw);
+        D.sx = d.sw.empty() ? nullptr : put(d.sx);
     }
     std::memcpy(H + p.desc_off, descs.data(), sizeof(dtr::TraceDev) * n_traces);
     for (int32_t i = 0; i < n_sims; i++) {
@@ -605,6 +650,7 @@ int launch_traces(dtr_sim *h, void *stream, uint8_t *slots, uint32_t *queue, int
         a[c].L = p.L;
         a[c].n_sims = p.class_count[c];
         a[c].n_slots = (int32_t)std::max<int64_t>(1, share[c]);
+        a[c].sweep_chunks = p.sweep_chunks;
         a[c].prof = nullptr;
 #ifdef DTR_PROFILE
         a[c].prof = (int64_t *)(h->ws + p.prof_off);

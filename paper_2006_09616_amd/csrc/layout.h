@@ -44,6 +44,25 @@ struct TRecX {
 };
 static_assert(sizeof(TRecX) == 64, "tensor record element layout");
 
+// Sweep tables (walk heuristics, traces of up to SWEEP_OPS operations): node
+// o is the tensor produced by operation o, so that edges go from smaller to
+// larger numbers; 64 consecutive nodes are a chunk.  rowp/rowc: the node's
+// parents and children inside its own chunk, a bit each; xp/xc: the first of
+// those in other chunks (nxp, nxc of them in all: the rest are read from `sx`
+// at xoff, parents first, constants left out).
+constexpr int SWEEP_HEAD = 4;
+struct __attribute__((aligned(16))) SweepRec {
+    uint64_t rowp, rowc;
+    int32_t c0, xoff;
+    uint16_t nxp, nxc;
+    uint32_t pad;
+    uint16_t xp[SWEEP_HEAD], xc[SWEEP_HEAD];
+};
+static_assert(sizeof(SweepRec) == 48, "sweep record layout");
+constexpr int SWEEP_OPS = 2048;              // at most 64 chunks: the pending chunks are one 64-bit mask
+constexpr int SWEEP_POS_SHIFT = 13;          // a listed candidate: pool position << 13 | node
+constexpr int64_t SWEEP_MAX_POOL = int64_t(1) << (32 - SWEEP_POS_SHIFT);
+
 struct TraceDev {
     int32_t n;               // tensors
     int32_t F;               // ops
@@ -66,6 +85,8 @@ struct TraceDev {
     const int32_t *req;      // [n_req]
     const int32_t *consts;   // [n_const]
     const TRecX *rec;        // [n]
+    const SweepRec *sw;      // [F], null when the trace's walks go lane by lane
+    const uint16_t *sx;
 };
 
 struct SpecDev {
@@ -177,6 +198,11 @@ constexpr int PROGRESS_OFFSET = 32;
 constexpr int COUNTER_WORDS = PROGRESS_OFFSET / 4 + 2;
 constexpr int PROGRESS_STEP = 4096;
 
+constexpr int64_t sweep_lds_bytes(int64_t chunks, int64_t waves)
+{
+    return chunks * (8 + 4 * WAVE + waves * 8 * WAVE);
+}
+
 struct KernelArgs {
     const TraceDev *traces;
     const SpecDev *specs;
@@ -188,6 +214,10 @@ struct KernelArgs {
     SlotLayout L;
     int32_t n_sims;
     int32_t n_slots;
+    // walk heuristics: chunks of the largest trace that is swept (0: none); the
+    // workgroup's dynamic LDS holds the evicted masks, the candidate list and
+    // each wavefront's reach masks for that many
+    int32_t sweep_chunks;
     int64_t *prof;           // DTR_PROFILE builds: PROF_FIELDS counters per sim
 };
 

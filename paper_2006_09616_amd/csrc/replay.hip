@@ -41,6 +41,7 @@
 
 #include "../../include/dtr_sim.h"
 #include "layout.h"
+#include "sweep.h"
 
 namespace dtr {
 
@@ -240,6 +241,8 @@ struct Sim {
     int32_t nw;                   // wavefronts in the workgroup (walk heuristics)
     int32_t trace_idx;
     LAS struct WalkCtl *ctl;      // their control block in LDS
+    LAS uint8_t *sweep_lds;       // the sweeps' arrays in LDS, for traces of
+    int32_t sweep_chunks;         // up to this many chunks
     unsigned long long *progress; // the launch's progress counter (walk heuristics)
     int64_t evict_no;
     int64_t total, base, remat_cost, executed, remats, evictions, eager, scores;
@@ -416,9 +419,10 @@ struct WaveBest {
 };
 struct WalkCtl {
     int32_t cmd, sim, end, both, use_m, use_s, sample, trace;
-    uint32_t ctr, ovf, ctr2, pad;
+    uint32_t ctr, ovf, ctr2, ncand;
     int64_t T, evict_no;
     uint64_t min_size, tau, seed;
+    uint64_t side[MAX_WALK_WAVES / 2][WAVE];   // a sweep's descendant sums, by the wavefront pair's group
     WaveBest res[MAX_WALK_WAVES];
 };
 enum { CMD_WALK = 1, CMD_DONE = 2 };
@@ -1341,6 +1345,233 @@ __device__ void walk_listed(const TraceDev &t, const Slot &S, GAS uint64_t *tst,
     }
 }
 
+// ------------------------------------------------------------- sweeps --
+
+// What a wavefront needs for the sweeps of a scan: the trace's sweep tables,
+// the masks of evicted nodes (a 64-bit word per chunk), this wavefront's
+// reach masks (all zero between sweeps) and the scan's candidate list.
+struct Sweep {
+    const SweepRec *rec;
+    const uint16_t *sx;
+    LAS uint64_t *ev;
+    LAS uint32_t *list;
+    LAS uint64_t *M;
+};
+
+__device__ __forceinline__ Sweep sweep_at(LAS uint8_t *lds, int32_t chunks, int32_t wave, const TraceDev &t)
+{
+    Sweep W;
+    W.rec = t.sw;
+    W.sx = t.sx;
+    W.ev = (LAS uint64_t *)lds;
+    W.list = (LAS uint32_t *)(lds + 8 * chunks);
+    W.M = (LAS uint64_t *)(lds + (8 + 4 * WAVE) * chunks) + (size_t)wave * (size_t)(WAVE * chunks);
+    return W;
+}
+
+// A chunk's records as one lane sees them while the chunk is swept.
+struct SweepNode {
+    u32x4 rows, info;
+    uint64_t hp, hc;
+};
+
+__device__ __forceinline__ SweepNode sweep_node(const Sweep &W, int32_t node)
+{
+    const GAS u32x4 *R = (const GAS u32x4 *)(W.rec + node);
+    const u32x4 h = R[2];
+    SweepNode r;
+    r.rows = R[0];
+    r.info = R[1];
+    r.hp = (uint64_t)h.x | ((uint64_t)h.y << 32);
+    r.hc = (uint64_t)h.z | ((uint64_t)h.w << 32);
+    return r;
+}
+
+// The evicted ancestors (up) or descendants of up to 64 candidates at once,
+// one candidate (node o, when `has`) per lane.  M holds for each node the set
+// of candidates whose walk has reached it, a bit per lane.  Edges go one way
+// along the node numbers, so chunks are taken in that order (ancestors from
+// the last chunk down, with the lanes reversed, so that in both directions a
+// lane's sources have smaller lane numbers).  After a chunk every set joins
+// those of its evicted neighbours in later chunks (an LDS OR each); chunks
+// that nothing has reached are skipped.
+//
+// Bound by the issue of the chunk step's instructions: about eleven vector
+// ones per node for all 64 candidates together, where lane-by-lane walks took
+// a chain of three dependent device-memory reads (over 2000 cycles) per member
+// of the longest set.  A scan of the ResNet trace's heaviest h_DTR replay
+// (about 60 candidates, e* of up to some 60 members) went from 128,000 cycles
+// to 31,000, one of a 600-layer chain from 157,000 to 37,000.  Returns this lane's candidate's (count << 50 | summed c0):
+// costs sum below 2^50.
+__device__ uint64_t sweep_side(const Sweep &W, bool up, int32_t lane, bool has, int32_t o)
+{
+    constexpr uint64_t ONE = uint64_t(1);
+    const int32_t at = up ? WAVE - 1 - lane : lane;      // this lane's node within a chunk
+    uint64_t sum = 0, pend = 0;
+    int32_t cnt = 0;
+    if (has) W.M[o] = ONE << lane;
+    lds_order();
+    join_masks(pend, has ? ONE << (o >> 6) : 0);
+    auto next = [&]() { return up ? 63 - __builtin_clzll(pend) : __builtin_ctzll(pend); };
+    if (!pend) return 0;
+    int32_t c = next();
+    SweepNode R = sweep_node(W, c * WAVE + at);
+    for (;;) {
+        pend &= ~(ONE << c);
+        const int32_t node = c * WAVE + at;
+        const uint64_t Mv = W.M[node];
+        W.M[node] = 0;
+        uint64_t ev = (uint64_t)uni64((int64_t)W.ev[c]);
+        if (up) ev = __builtin_bitreverse64(ev);
+        // the records of the chunk that probably comes next
+        const int32_t guess = pend ? next() : up ? max(c - 1, 0) : c;
+        const SweepNode G = sweep_node(W, guess * WAVE + at);
+        const bool mine = lane_in(ev);
+        uint32_t s0 = up ? __builtin_bitreverse32(R.rows.w) : R.rows.x;
+        uint32_t s1 = up ? __builtin_bitreverse32(R.rows.z) : R.rows.y;
+        s0 = mine ? s0 : 0;
+        s1 = mine ? s1 : 0;
+        const uint32_t c0 = mine ? R.info.x : 0;
+        uint32_t m0 = (uint32_t)Mv, m1 = (uint32_t)(Mv >> 32);
+        sweep_chunk(m0, m1, s0, s1, c0, sum, cnt);
+        // neighbours in other chunks
+        const int32_t nx = (m0 | m1) ? (up ? (int32_t)(R.info.z & 0xFFFF) : (int32_t)(R.info.z >> 16)) : 0;
+        if (__ballot(nx > 0)) {
+            const uint64_t Mi = (uint64_t)m0 | ((uint64_t)m1 << 32);
+            const uint64_t hd = up ? R.hp : R.hc;
+            const LAS uint32_t *EW = (const LAS uint32_t *)W.ev;
+            uint64_t to = 0;             // chunks this lane has reached
+            uint32_t p[SWEEP_HEAD], w[SWEEP_HEAD];
+#pragma unroll
+            for (int j = 0; j < SWEEP_HEAD; j++) {
+                p[j] = (uint32_t)(hd >> (16 * j)) & 0xFFFF;
+                w[j] = EW[p[j] >> 5];
+            }
+#pragma unroll
+            for (int j = 0; j < SWEEP_HEAD; j++)
+                if (j < nx && ((w[j] >> (p[j] & 31)) & 1)) {
+                    __hip_atomic_fetch_or(W.M + p[j], Mi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    to |= ONE << (p[j] >> 6);
+                }
+            for (int32_t j = SWEEP_HEAD; __ballot(j < nx); j++) {
+                if (j >= nx) continue;
+                const uint32_t pj = gld(W.sx + R.info.y + (up ? 0 : (int32_t)(R.info.z & 0xFFFF)) + j);
+                if ((EW[pj >> 5] >> (pj & 31)) & 1) {
+                    __hip_atomic_fetch_or(W.M + pj, Mi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    to |= ONE << (pj >> 6);
+                }
+            }
+            join_masks(pend, to);
+        }
+        lds_order();
+        if (!pend) break;
+        c = next();
+        R = G;
+        if (c != guess) R = sweep_node(W, c * WAVE + at);
+    }
+    // every candidate has counted itself (at no cost) once
+    return sum + ((uint64_t)(uint32_t)(cnt - (has ? 1 : 0)) << 50);
+}
+
+// List the scan's candidates in node order (pool position << SWEEP_POS_SHIFT
+// | node) and the evicted nodes of every chunk; returns the number listed.
+__device__ __forceinline__ int32_t sweep_list(const Sim &s, const Sweep &W)
+{
+    constexpr int B = 4;             // chunks whose reads are issued together
+    const int32_t F = s.t.F;
+    int32_t n = 0;
+    for (int32_t c0 = 0; c0 * WAVE < F; c0 += B) {
+        int32_t t[B];
+        uint64_t w[B];
+#pragma unroll
+        for (int j = 0; j < B; j++) {
+            const int32_t o = (c0 + j) * WAVE + s.lane;
+            t[j] = gld(s.t.out + min(o, F - 1));
+        }
+#pragma unroll
+        for (int j = 0; j < B; j++) w[j] = s.S.tst[t[j]];
+#pragma unroll
+        for (int j = 0; j < B; j++) {
+            const int32_t o = (c0 + j) * WAVE + s.lane;
+            if ((c0 + j) * WAVE >= F) break;
+            const uint64_t ev = __ballot(o < F && ts_sw(w[j]) >= 0);
+            const bool in = o < F && ts_in_pool(w[j]);
+            const uint64_t m = __ballot(in);
+            if (s.lane == 0) W.ev[c0 + j] = ev;
+            if (in) W.list[n + lane_rank(m)] = ts_pos(w[j]) << SWEEP_POS_SHIFT | (uint32_t)o;
+            n += __popcll(m);
+        }
+    }
+    return n;
+}
+
+// Sweep and score the listed candidates, 64 to a group; wavefront `wave` of
+// `nw` takes every nw-th group.  With at most nw / 2 groups and both sides to
+// walk, a pair of wavefronts shares each group, a side each (the second hands
+// its sums over through the control block).  The workgroup barrier inside is
+// passed by every wavefront when nw > 1.
+template <int HC>
+__device__ void sweep_groups(const Slot &S, const Sweep &W, const WalkParams &P, int32_t n, int32_t lane, int32_t wave,
+                             int32_t nw, LAS WalkCtl *C, Best &best, int64_t &nbr, int64_t &adj, int64_t &nscored)
+{
+    const int32_t groups = (n + WAVE - 1) / WAVE;
+    const bool split = P.both && 2 * groups <= nw;
+    int32_t id = 0, deg = 0, slot = 0;
+    int64_t last = 0, size = 0, c0 = 0;
+    bool has = false;
+    uint64_t acc = 0;
+    auto load = [&](int32_t g) {
+        const int32_t k = g * WAVE + lane;
+        has = k < n;
+        const uint32_t e = W.list[has ? k : 0];
+        slot = (int32_t)(e >> SWEEP_POS_SHIFT);
+        i32x4 q0, q1;
+        if (slot < POOL_LDS) {
+            const LAS i32x4 *PS = (const LAS i32x4 *)S.lpool_l + PQL * slot;
+            q0 = PS[0]; q1 = PS[1];
+        } else {
+            const GAS i32x4 *PS = (const GAS i32x4 *)S.gpool + PQ * (size_t)slot;
+            q0 = PS[0]; q1 = PS[1];
+        }
+        id = q0.x;
+        deg = q0.y >> 8;
+        last = (int64_t)(((uint64_t)(uint32_t)q0.w << 32) | (uint32_t)q0.z);
+        size = (int64_t)(((uint64_t)(uint32_t)q1.y << 32) | (uint32_t)q1.x);
+        c0 = (int64_t)q1.z;
+        if (approx(HC)) {
+            has = has && (uint64_t)size >= P.min_size;
+            if (P.sample) has = has && sample_draw_at(P.seed, P.evict_no, id) < P.tau;
+        }
+        return (int32_t)(e & ((1u << SWEEP_POS_SHIFT) - 1));
+    };
+    auto score = [&]() {
+        const uint64_t N = (uint64_t)c0 + (acc & ((uint64_t(1) << 50) - 1));
+        const uint64_t DA = P.use_m ? (uint64_t)size : 1;
+        const uint64_t DB = P.use_s ? (uint64_t)(P.T - last) : 1;
+        take(best, has, score_est(N, DA, DB), N, DA, DB, id, slot);
+        if (has) {
+            nbr += (int64_t)(acc >> 50);
+            adj += deg;
+            nscored++;
+        }
+    };
+    // (one call of the sweep in the code: it is long)
+    const int32_t g0 = split ? wave >> 1 : wave;
+    for (int32_t g = g0; g < groups; g += nw) {
+        const int32_t o = load(g);
+        acc = 0;
+        const int32_t side0 = split ? wave & 1 : 0, side1 = split ? side0 + 1 : P.both ? 2 : 1;
+        for (int32_t side = side0; side < side1; side++) acc += sweep_side(W, side == 0, lane, has, o);
+        if (!split) score();
+        else if (wave & 1) C->side[g][lane] = acc;
+    }
+    if (nw > 1) __syncthreads();
+    if (split && g0 < groups && !(wave & 1)) {
+        acc += C->side[g0][lane];
+        score();
+    }
+}
+
 // the wavefront's best (exact lexicographic minimum of score and id over its
 // lanes), uniform
 __device__ WaveBest wave_best(const Best &best)
@@ -1401,6 +1632,13 @@ __device__ void walk_scan(Sim &s, const Filter &F, Best &best, int64_t &scored)
     P.seed = s.seed;
     LAS WalkCtl *C = s.ctl;
     const bool multi = s.nw > 1;
+    const bool swept = s.t.sw != nullptr;
+    Sweep W;
+    int32_t ncand = 0;
+    if (swept) {
+        W = sweep_at(s.sweep_lds, s.sweep_chunks, 0, s.t);
+        ncand = sweep_list(s, W);
+    }
     if (s.lane == 0) {
         C->ovf = 0;
         C->ctr = 0;
@@ -1420,6 +1658,7 @@ __device__ void walk_scan(Sim &s, const Filter &F, Best &best, int64_t &scored)
             C->min_size = P.min_size;
             C->tau = P.tau;
             C->seed = P.seed;
+            C->ncand = (uint32_t)ncand;
         }
         __syncthreads();
     } else {
@@ -1431,18 +1670,21 @@ __device__ void walk_scan(Sim &s, const Filter &F, Best &best, int64_t &scored)
     // the helpers, of the whole-wavefront walks, and their number
     const int64_t w1 = (int64_t)__builtin_readcyclecounter();
 #endif
-    walk_lanes<HC>(s.t, s.S, s.S.tst, P, s.lane, s.lane, multi ? (LAS uint32_t *)&C->ctr : nullptr,
-                   (LAS uint32_t *)&C->ovf, best, nbr, adj, nscored);
+    if (swept) {
+        sweep_groups<HC>(s.S, W, P, ncand, s.lane, 0, s.nw, C, best, nbr, adj, nscored);
+    } else {
+        walk_lanes<HC>(s.t, s.S, s.S.tst, P, s.lane, s.lane, multi ? (LAS uint32_t *)&C->ctr : nullptr,
+                       (LAS uint32_t *)&C->ovf, best, nbr, adj, nscored);
+        if (multi) __syncthreads();
+        else wave_sync();
+    }
 #ifdef DTR_PROFILE
     const int64_t w2 = (int64_t)__builtin_readcyclecounter();
+    const int64_t w3 = w2;
 #endif
-    if (multi) __syncthreads();
-    else wave_sync();
-#ifdef DTR_PROFILE
-    const int64_t w3 = (int64_t)__builtin_readcyclecounter();
-#endif
-    walk_listed<HC>(s.t, s.S, s.S.tst, P, s.lane, 0, uni((int32_t)C->ovf), multi ? (LAS uint32_t *)&C->ctr2 : nullptr,
-                    best, nbr, adj, nscored);
+    if (!swept)
+        walk_listed<HC>(s.t, s.S, s.S.tst, P, s.lane, 0, uni((int32_t)C->ovf),
+                        multi ? (LAS uint32_t *)&C->ctr2 : nullptr, best, nbr, adj, nscored);
 #ifdef DTR_PROFILE
     const int64_t w4 = (int64_t)__builtin_readcyclecounter();
     s.prof_rounds += w2 - w1;
@@ -1475,7 +1717,8 @@ __device__ void walk_scan(Sim &s, const Filter &F, Best &best, int64_t &scored)
 // wavefront's walk scans (the three workgroup barriers of each) until it is
 // released at the end of the simulation.
 template <int HC>
-__device__ void help_walks(const KernelArgs &a, const Slot &S, int32_t lane, int32_t wave, LAS WalkCtl *C)
+__device__ void help_walks(const KernelArgs &a, const Slot &S, int32_t lane, int32_t wave, LAS WalkCtl *C,
+                           LAS uint8_t *sweep_lds)
 {
     for (;;) {
         __syncthreads();
@@ -1500,11 +1743,16 @@ __device__ void help_walks(const KernelArgs &a, const Slot &S, int32_t lane, int
         best.slot = -1;
         best.have = 0;
         int64_t nbr = 0, adj = 0, nscored = 0;
-        walk_lanes<HC>(t, S, S.tst, P, lane, wave * WAVE + lane, (LAS uint32_t *)&C->ctr, (LAS uint32_t *)&C->ovf,
-                       best, nbr, adj, nscored);
-        __syncthreads();
-        walk_listed<HC>(t, S, S.tst, P, lane, wave, uni((int32_t)C->ovf), (LAS uint32_t *)&C->ctr2, best, nbr, adj,
-                        nscored);
+        if (t.sw) {
+            sweep_groups<HC>(S, sweep_at(sweep_lds, a.sweep_chunks, wave, t), P, uni((int32_t)C->ncand), lane, wave,
+                             (int32_t)a.L.walk_waves, C, best, nbr, adj, nscored);
+        } else {
+            walk_lanes<HC>(t, S, S.tst, P, lane, wave * WAVE + lane, (LAS uint32_t *)&C->ctr, (LAS uint32_t *)&C->ovf,
+                           best, nbr, adj, nscored);
+            __syncthreads();
+            walk_listed<HC>(t, S, S.tst, P, lane, wave, uni((int32_t)C->ovf), (LAS uint32_t *)&C->ctr2, best, nbr, adj,
+                            nscored);
+        }
         WaveBest r = wave_best(best);
         r.nbr = wave_sum(nbr);
         r.adj = wave_sum(adj);
@@ -2146,7 +2394,7 @@ __device__ __forceinline__ bool release(Sim &s, int32_t o)
 
 template <int HC>
 __device__ __forceinline__ void run_sim(const KernelArgs &a, int32_t sim, const Slot &S, int32_t lane, LAS WalkCtl *ctl,
-                                       int32_t nw)
+                                       int32_t nw, LAS uint8_t *sweep_lds)
 {
     Sim s;
     const SpecDev sp = a.specs[sim];
@@ -2156,6 +2404,8 @@ __device__ __forceinline__ void run_sim(const KernelArgs &a, int32_t sim, const 
     s.progress = a.progress;
     s.nw = nw;
     s.ctl = ctl;
+    s.sweep_lds = sweep_lds;
+    s.sweep_chunks = a.sweep_chunks;
     s.h = sp.heuristic;
     s.policy = sp.policy;
     s.search = sp.search;
@@ -2302,7 +2552,7 @@ __device__ __forceinline__ void eq_waves(const KernelArgs &a, UfNode *lds_nodes,
         if (lane == 0) k = atomicAdd(a.queue, 1u);
         k = (uint32_t)uni((int32_t)k);
         if (k >= (uint32_t)a.n_sims) break;
-        run_sim<HC>(a, a.order[k], S, lane, nullptr, 1);
+        run_sim<HC>(a, a.order[k], S, lane, nullptr, 1, nullptr);
     }
 }
 
@@ -2317,6 +2567,7 @@ __global__ void __launch_bounds__(cls(HC) == HC_WALK ? MAX_WALK_WAVES * WAVE : l
     __attribute__((amdgpu_waves_per_eu(2))) replay_kernel(KernelArgs a)
 {
     constexpr int LW = lds_waves(HC);
+    extern __shared__ __align__(16) uint8_t lds_dyn[];       // the sweeps' arrays (walk heuristics)
     // union-find nodes (h_DTR^eq: one array per wavefront), or the walk
     // control block (walk heuristics)
     __shared__ UfNode lds_nodes[cls(HC) == HC_EQ ? UF_LDS * LW : CTL_NODES];
@@ -2341,6 +2592,10 @@ __global__ void __launch_bounds__(cls(HC) == HC_WALK ? MAX_WALK_WAVES * WAVE : l
         for (size_t i = lane; i < (size_t)WAVE * (size_t)S.vis_bytes / 16; i += WAVE) V[i] = u32x4{0u, 0u, 0u, 0u};
         GAS uint32_t *B = S.bigvis + (size_t)wave * (size_t)S.vis_words;
         for (int32_t i = lane; i < S.vis_words; i += WAVE) B[i] = 0u;
+        // and so do this wavefront's reach masks
+        LAS uint64_t *M = (LAS uint64_t *)((LAS uint8_t *)lds_dyn + (8 + 4 * WAVE) * a.sweep_chunks) +
+                          wave * WAVE * a.sweep_chunks;
+        for (int32_t i = lane; i < WAVE * a.sweep_chunks; i += WAVE) M[i] = 0;
         wave_sync();
     }
     for (;;) {
@@ -2355,10 +2610,10 @@ __global__ void __launch_bounds__(cls(HC) == HC_WALK ? MAX_WALK_WAVES * WAVE : l
         }
         if (k >= (uint32_t)a.n_sims) break;
         if constexpr (cls(HC) == HC_WALK) {
-            if (wave == 0) run_sim<HC>(a, a.order[k], S, lane, ctl, nw);
-            else help_walks<HC>(a, S, lane, wave, ctl);
+            if (wave == 0) run_sim<HC>(a, a.order[k], S, lane, ctl, nw, (LAS uint8_t *)lds_dyn);
+            else help_walks<HC>(a, S, lane, wave, ctl, (LAS uint8_t *)lds_dyn);
         } else {
-            run_sim<HC>(a, a.order[k], S, lane, ctl, 1);
+            run_sim<HC>(a, a.order[k], S, lane, ctl, 1, nullptr);
         }
     }
 }
@@ -2417,14 +2672,22 @@ extern "C" hipError_t dtr_launch_group(const dtr::KernelArgs *a, int32_t group, 
     using namespace dtr;
     if (a->n_sims <= 0) return hipSuccess;
     const dim3 grid(a->n_slots), blk(WAVE), wblk(WAVE * (uint32_t)a->L.walk_waves);
+    const uint32_t wlds = (uint32_t)sweep_lds_bytes(a->sweep_chunks, a->L.walk_waves);
     // the exact h_DTR^eq kernel: EQ_WAVES slots per workgroup
     const dim3 egrid((a->n_slots + EQ_WAVES - 1) / EQ_WAVES), eblk(WAVE * EQ_WAVES);
+    // (the kernels' static LDS, about 14 KB, comes on top)
+    if (wlds > 48 * 1024 && (group == 1 || group == 4)) {
+        const void *f = group == 1 ? (const void *)replay_kernel<HC_WALK>
+                                   : (const void *)replay_kernel<HC_WALK | HC_APPROX>;
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)wlds);
+        if (e != hipSuccess) return e;
+    }
     switch (group) {
     case 0: hipLaunchKernelGGL(replay_kernel<HC_EQ>, egrid, eblk, 0, stream, *a); break;
-    case 1: hipLaunchKernelGGL(replay_kernel<HC_WALK>, grid, wblk, 0, stream, *a); break;
+    case 1: hipLaunchKernelGGL(replay_kernel<HC_WALK>, grid, wblk, wlds, stream, *a); break;
     case 2: hipLaunchKernelGGL(replay_kernel<HC_SIMPLE>, grid, blk, 0, stream, *a); break;
     case 3: hipLaunchKernelGGL(replay_kernel<HC_EQ | HC_APPROX>, grid, blk, 0, stream, *a); break;
-    case 4: hipLaunchKernelGGL(replay_kernel<HC_WALK | HC_APPROX>, grid, wblk, 0, stream, *a); break;
+    case 4: hipLaunchKernelGGL(replay_kernel<HC_WALK | HC_APPROX>, grid, wblk, wlds, stream, *a); break;
     case 5: hipLaunchKernelGGL(replay_kernel<HC_SIMPLE | HC_APPROX>, grid, blk, 0, stream, *a); break;
     default: return hipErrorInvalidValue;
     }

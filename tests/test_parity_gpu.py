@@ -481,6 +481,36 @@ def test_walk_workgroup_shapes(gpu, oracle_lib, waves, small):
     compare(gpu.run(traces, specs, flags=flags), ref, specs, f"walk {waves} waves small={small}")
 
 
+_SWEEP_REF = []
+
+
+@pytest.mark.parametrize("waves", [0, 1, 3, 8])
+def test_sweep_chunk_edges(gpu, oracle_lib, waves):
+    """The walk heuristics on programs around the sweeps' limits: whole and
+    ragged chunks of 64 operations, the longest swept program (2048) and one
+    more (walked lane by lane), operators with more neighbours outside their
+    chunk than a record holds, more than 64 candidates, fewer and more groups
+    of them than wavefront pairs; ids in and out of execution order."""
+    traces, rows = [], []
+    for s, F in enumerate((1, 2, 63, 64, 65, 127, 128, 129, 700, 2047, 2048, 2049)):
+        tr = W.random_program(5200 + s, n_ops=F, n_const=s % 3, max_in=2 + 5 * (s % 2), max_size=1 + 7 * (s % 3),
+                              max_cost=9, window=None if s % 2 else 40, permute_ids=s % 4 != 1)
+        assert tr.n_ops == F
+        traces.append(tr)
+        peak = W.natural_peak(tr)
+        for h in WALK_H if F < 2000 else (W.H_DTR, W.H_MSPS):
+            for frac in (0.45, 0.8) if F < 2000 else (0.65,):
+                for pol in (W.POLICY_EAGER, W.POLICY_IGNORE) if F < 1000 else (W.POLICY_EAGER,):
+                    rows.append((s, h, max(1, int(peak * frac)), s, pol, s % 4 if F < 700 else 0))
+    specs = specs_of(rows)
+    print(f"sweep edges, {waves} waves: {len(specs)} sims", flush=True)
+    if not _SWEEP_REF:
+        _SWEEP_REF.append(oracle_lib.run(traces, specs))
+    ref = _SWEEP_REF[0]
+    assert int(ref["n_scores"].max()) > 64 and int(ref["n_nbr_visits"].max()) > 0
+    compare(gpu.run(traces, specs, flags=gpu.opt_walk_waves(waves)), ref, specs, f"sweep edges waves={waves}")
+
+
 _EQ_BATCH = {}
 
 
