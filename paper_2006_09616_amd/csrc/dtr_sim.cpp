@@ -287,6 +287,7 @@ struct Plan {
     dtr::SlotLayout L{};
     int32_t n_slots = 0;
     bool static_only = false;        // runs only through dtr_sim_run_static: no slots in the workspace
+    int32_t small_n[dtr::N_GROUPS] = {0, 0, 0, 0, 0, 0};   // per group: state words kept in LDS (0: in the slot)
     int32_t sweep_chunks = 0;        // of the longest swept trace (0: none)
     std::vector<int32_t> order;
     int32_t class_count[dtr::N_GROUPS] = {0, 0, 0, 0, 0, 0};
@@ -436,6 +437,21 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     });
     for (int c = 0; c < dtr::N_GROUPS; c++) p.class_count[c] = 0;
     for (int32_t i = 0; i < n_sims; i++) p.class_count[cls(i)]++;
+    // groups whose traces are all small keep their state words in LDS; under
+    // h_DTR^eq only if the group is resident at once that way (a workgroup per
+    // compute unit, or more)
+    int32_t group_n[dtr::N_GROUPS] = {0, 0, 0, 0, 0, 0};
+    for (int32_t i = 0; i < n_sims; i++)
+        group_n[cls(i)] = std::max(group_n[cls(i)], p.traces[sims[i].trace].n);
+    for (int c = 0; c < dtr::N_GROUPS; c++) {
+        if (group_n[c] > dtr::SMALL_TENSORS || (c % 3 == 1 && !sweep)) continue;
+        const int32_t sn = std::max(2, (group_n[c] + 1) / 2 * 2);
+        if (c == 0) {
+            const int64_t wg = dtr::EQ_WAVES * (dtr::small_lds_bytes(sn) + dtr::eq_wave_lds_bytes());
+            if (p.class_count[c] > cus * dtr::EQ_WAVES * ((160 << 10) / wg)) continue;
+        }
+        p.small_n[c] = sn;
+    }
 
     size_t w = align_up(64);   // header: work counter
     p.trace_off.resize(n_traces);
@@ -651,6 +667,7 @@ int launch_traces(dtr_sim *h, void *stream, uint8_t *slots, uint32_t *queue, int
         a[c].n_sims = p.class_count[c];
         a[c].n_slots = (int32_t)std::max<int64_t>(1, share[c]);
         a[c].sweep_chunks = p.sweep_chunks;
+        a[c].small_n = p.small_n[c];
         a[c].prof = nullptr;
 #ifdef DTR_PROFILE
         a[c].prof = (int64_t *)(h->ws + p.prof_off);

@@ -188,6 +188,9 @@ struct __attribute__((aligned(16))) UfNode {
     int32_t size;
 };
 
+// static LDS of an h_DTR^eq wavefront: nodes and (padded) pool slots
+constexpr int64_t eq_wave_lds_bytes() { return UF_LDS * (int64_t)sizeof(UfNode) + POOL_LDS * 80; }
+
 // simulation groups, one kernel specialisation each: heuristic class
 // (union-find neighbourhood, neighbourhood walk, none), plus 3 with the
 // search approximations on
@@ -202,6 +205,12 @@ constexpr int64_t sweep_lds_bytes(int64_t chunks, int64_t waves)
 {
     return chunks * (8 + 4 * WAVE + waves * 8 * WAVE);
 }
+
+// Traces of up to this many tensors keep their state words and the first
+// SMALL_STACK frames of the rematerialization stack in LDS.
+constexpr int SMALL_TENSORS = 2048;
+constexpr int SMALL_STACK = 16;
+constexpr int64_t small_lds_bytes(int64_t n) { return n > 0 ? (8 * n + 15) / 16 * 16 + SMALL_STACK * (int64_t)sizeof(StackFrame) : 0; }
 
 struct KernelArgs {
     const TraceDev *traces;
@@ -218,6 +227,7 @@ struct KernelArgs {
     // workgroup's dynamic LDS holds the evicted masks, the candidate list and
     // each wavefront's reach masks for that many
     int32_t sweep_chunks;
+    int32_t small_n;         // the small-trace kernels: state words of a simulation in LDS
     int64_t *prof;           // DTR_PROFILE builds: PROF_FIELDS counters per sim
 };
 

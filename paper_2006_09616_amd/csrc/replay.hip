@@ -38,6 +38,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "../../include/dtr_sim.h"
 #include "layout.h"
@@ -75,9 +76,12 @@ constexpr int LB = 8;            // neighbour reads issued together when buildin
 static_assert(LB == NB_HEAD, "a cache build may take its first chunk from the record element");
 // kernel specialisations by heuristic class (register budgets differ widely),
 // each with exact search or with the search approximations (HC | HC_APPROX)
-enum { HC_EQ = 0, HC_WALK = 1, HC_SIMPLE = 2, HC_APPROX = 4 };
+// and, for traces of up to SMALL_TENSORS tensors, with the state words and the
+// top of the rematerialization stack in LDS (| HC_SMALL)
+enum { HC_EQ = 0, HC_WALK = 1, HC_SIMPLE = 2, HC_APPROX = 4, HC_SMALL = 8 };
 __host__ __device__ constexpr int cls(int hc) { return hc & 3; }
 __host__ __device__ constexpr bool approx(int hc) { return (hc & HC_APPROX) != 0; }
+__host__ __device__ constexpr bool small(int hc) { return (hc & HC_SMALL) != 0; }
 // candidates per lane per scan round (their reads are issued together); the
 // h_DTR^eq round is instruction-issue bound, so a second candidate per lane
 // only doubles the round
@@ -171,8 +175,14 @@ struct __attribute__((aligned(16))) PoolSlotL {
 };
 // Evictable pool: slots below POOL_LDS in this wavefront's LDS array, the
 // rest in the slot's global array (same indices).
+// the state words' home: LDS (small traces) or the slot in device memory
+template <int HC>
+using Tst = typename std::conditional<small(HC), LAS uint64_t *, GAS uint64_t *>::type;
+
+template <int HC>
 struct Slot {
-    GAS uint64_t *tst;
+    Tst<HC> tst;
+    LAS i32x4 *stack_l;           // the first SMALL_STACK frames (small traces)
     GAS int32_t *lockx;           // lock counts >= LOCKS_SAT
     PoolSlotL *lpool;             // flat view of the LDS head
     LAS PoolSlotL *lpool_l;
@@ -194,11 +204,14 @@ struct Slot {
     }
 };
 
-__device__ __forceinline__ Slot slot_at(const KernelArgs &a, int32_t k)
+template <int HC>
+__device__ __forceinline__ Slot<HC> slot_at(const KernelArgs &a, int32_t k, LAS uint8_t *lds_small)
 {
     uint8_t *b = a.slots + (size_t)k * (size_t)a.L.bytes;
-    Slot S;
-    S.tst = (GAS uint64_t *)(b + a.L.tst);
+    Slot<HC> S;
+    if constexpr (small(HC)) S.tst = (LAS uint64_t *)lds_small;
+    else S.tst = (GAS uint64_t *)(b + a.L.tst);
+    S.stack_l = (LAS i32x4 *)(lds_small + 8 * (size_t)a.small_n);
     S.lockx = (GAS int32_t *)(b + a.L.lockx);
     S.lpool = nullptr;
     S.lpool_l = nullptr;
@@ -224,9 +237,10 @@ __device__ __forceinline__ Slot slot_at(const KernelArgs &a, int32_t k)
 }
 
 // Wave-uniform simulation state.
+template <int HC>
 struct Sim {
     TraceDev t;
-    Slot S;
+    Slot<HC> S;
     int32_t h;
     int32_t cmode, use_s, use_m;  // the heuristic as (cost measure, staleness used, size used)
     int32_t policy;               // what a release does
@@ -264,14 +278,16 @@ struct Sim {
 #endif
 enum { PH_EVICT = 0, PH_EXECUTE, PH_UNLOCK, PH_LOCK, PH_RELEASE, PH_RESUME, PH_OUTPUT, PH_DESCEND };
 
-__device__ __forceinline__ void set_status(Sim &s, int32_t st)
+template <int HC>
+__device__ __forceinline__ void set_status(Sim<HC> &s, int32_t st)
 {
     if (s.status == ST_OK) s.status = st;
 }
 
 // uniform read of a tensor's static record (two 16-byte scalar loads)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ TRec rec_u(const Sim &s, int32_t x)
+template <int HC>
+__device__ __forceinline__ TRec rec_u(const Sim<HC> &s, int32_t x)
 {
     const __attribute__((address_space(4))) u32x4 *p =
         (const __attribute__((address_space(4))) u32x4 *)&s.t.rec[x].r;
@@ -303,7 +319,8 @@ __device__ __forceinline__ TRec rec_v_t(const TraceDev &t, int32_t x)
     return r;
 }
 
-__device__ __forceinline__ TRec rec_v(const Sim &s, int32_t x) { return rec_v_t(s.t, x); }
+template <int HC>
+__device__ __forceinline__ TRec rec_v(const Sim<HC> &s, int32_t x) { return rec_v_t(s.t, x); }
 
 // ------------------------------------------------------ neighbour cache --
 
@@ -316,7 +333,8 @@ struct NbCache {
     i32x4 q[KQ];
 };
 
-__device__ __forceinline__ NbCache list_build(const Sim &s, int32_t b, int32_t e, int32_t &deg,
+template <int HC>
+__device__ __forceinline__ NbCache list_build(const Sim<HC> &s, int32_t b, int32_t e, int32_t &deg,
                                               const i32x4 *head = nullptr)
 {
     int32_t c[K];
@@ -366,7 +384,8 @@ __device__ __forceinline__ void cache_store(PoolSlot &ps, const NbCache &c)
     for (int k = 0; k < KQ; k++) ((i32x4 *)ps.nb)[k] = c.q[k];
 }
 
-__device__ __forceinline__ void list_add(const Sim &s, int32_t i, int32_t nd)
+template <int HC>
+__device__ __forceinline__ void list_add(const Sim<HC> &s, int32_t i, int32_t nd)
 {
     PoolSlot &ps = s.S.pool(i);
     const int32_t pd = ps.deg;
@@ -377,7 +396,8 @@ __device__ __forceinline__ void list_add(const Sim &s, int32_t i, int32_t nd)
 }
 
 // returns false if nd was not cached (cannot happen while the caches are consistent)
-__device__ __forceinline__ bool list_remove(const Sim &s, int32_t i, int32_t nd)
+template <int HC>
+__device__ __forceinline__ bool list_remove(const Sim<HC> &s, int32_t i, int32_t nd)
 {
     PoolSlot &ps = s.S.pool(i);
     int32_t v[K];
@@ -438,7 +458,7 @@ __device__ __forceinline__ void wave_sync()
 
 // wavefronts per workgroup that hold simulations of their own (each with its
 // own LDS pool and node arrays): the exact h_DTR^eq kernel's four, else one
-__host__ __device__ constexpr int lds_waves(int hc) { return hc == HC_EQ ? EQ_WAVES : 1; }
+__host__ __device__ constexpr int lds_waves(int hc) { return cls(hc) == HC_EQ && !approx(hc) ? EQ_WAVES : 1; }
 
 // the simulating wavefront's synchronization: wavefront-local where its
 // workgroup holds other wavefronts (walk heuristics, h_DTR^eq), a workgroup
@@ -455,7 +475,7 @@ __device__ __forceinline__ void slot_sync()
 
 // Squeeze tombstones out of the pool (order preserved; positions updated).
 template <int HC>
-__device__ __forceinline__ void pool_compact(Sim &s)
+__device__ __forceinline__ void pool_compact(Sim<HC> &s)
 {
     const int32_t lane = s.lane;
     int32_t kept = 0;
@@ -494,7 +514,7 @@ __device__ __forceinline__ void pool_compact(Sim &s)
 // access `last`; returns its slot (or -1).  The caller stores x's new state.
 // `known`: x's record when the caller holds it already (uniform x).
 template <int HC>
-__device__ __forceinline__ int32_t pool_append(Sim &s, bool want, int32_t x, int64_t last, const TRec *known = nullptr)
+__device__ __forceinline__ int32_t pool_append(Sim<HC> &s, bool want, int32_t x, int64_t last, const TRec *known = nullptr)
 {
     const uint64_t m = __ballot(want);
     if (!m) return -1;
@@ -588,8 +608,8 @@ __device__ __forceinline__ int32_t find_ro(const NodeStore &nodes, int32_t x, in
 }
 
 // uniform find with path compression (used where one set is touched)
-template <class NS>
-__device__ __forceinline__ int32_t find_compress(Sim &s, const NS &N, int32_t x)
+template <int HC, class NS>
+__device__ __forceinline__ int32_t find_compress(Sim<HC> &s, const NS &N, int32_t x)
 {
     int32_t root = x;
     for (int32_t k = 0;; k++) {
@@ -610,7 +630,8 @@ __device__ __forceinline__ int32_t find_compress(Sim &s, const NS &N, int32_t x)
 // evicted tensor (sets left with phantom members only are unreachable).
 // Membership and running costs are unchanged, so every later score is too;
 // the neighbour caches are rebuilt with the new node ids.
-__device__ __forceinline__ void uf_compact(Sim &s)
+template <int HC>
+__device__ __forceinline__ void uf_compact(Sim<HC> &s)
 {
     const int32_t lane = s.lane, n = s.t.n;
     const NodeStore &N = s.S.nodes;
@@ -677,8 +698,8 @@ __device__ __forceinline__ void uf_compact(Sim &s)
 // v's fresh node nd (cost c0(v)) joins the sets of all v's evicted neighbours
 // (found in parallel, merged under the largest; ties: the earliest), and every
 // neighbour waiting in the pool caches nd.
-template <class NS>
-__device__ __forceinline__ bool evict_merge(Sim &s, const NS &N, int32_t nd, const TRec &rv, int32_t head)
+template <int HC, class NS>
+__device__ __forceinline__ bool evict_merge(Sim<HC> &s, const NS &N, int32_t nd, const TRec &rv, int32_t head)
 {
     int32_t R = nd;               // current root of v's set
     int64_t Rcost = rv.c0;
@@ -755,7 +776,7 @@ __device__ __forceinline__ bool evict_merge(Sim &s, const NS &N, int32_t nd, con
 // neighbours (found in parallel, merged under the largest), and every
 // neighbour waiting in the pool caches the new node.
 template <int HC>
-__device__ __forceinline__ bool evict(Sim &s, int32_t v, int32_t slot, bool eager)
+__device__ __forceinline__ bool evict(Sim<HC> &s, int32_t v, int32_t slot, bool eager)
 {
     // size, c0 and neighbour range come from v's pool slot (LDS for the pool
     // head), not from the static record; the first neighbours from the
@@ -806,8 +827,8 @@ __device__ __forceinline__ bool evict(Sim &s, int32_t v, int32_t slot, bool eage
 // state reads are issued together; the finds then advance in lockstep, with
 // the first hop compressed (every lane writes the same root).  Returns the
 // number of evicted neighbours in the chunk; `bad` is set on a broken forest.
-template <class NS>
-__device__ __forceinline__ int32_t chunk_roots(const Sim &s, const NS &N, int32_t k0, int32_t e, int32_t (&r)[LB],
+template <int HC, class NS>
+__device__ __forceinline__ int32_t chunk_roots(const Sim<HC> &s, const NS &N, int32_t k0, int32_t e, int32_t (&r)[LB],
                                                bool &bad)
 {
     int32_t w[LB], q[LB];
@@ -849,8 +870,8 @@ __device__ __forceinline__ int32_t chunk_roots(const Sim &s, const NS &N, int32_
 // summed running costs of the distinct sets of its evicted neighbours.  A
 // set counts at its first neighbour; chunks after the first compare against
 // the roots of the chunks before them.
-template <class NS>
-__device__ __forceinline__ int64_t eq_cost_full(const Sim &s, const NS &N, int32_t b, int32_t e, int64_t &ev_count,
+template <int HC, class NS>
+__device__ __forceinline__ int64_t eq_cost_full(const Sim<HC> &s, const NS &N, int32_t b, int32_t e, int64_t &ev_count,
                                                 bool &bad)
 {
     int64_t sum = 0, cnt = 0;
@@ -947,7 +968,8 @@ struct Filter {
     uint64_t min_size, tau;
 };
 
-__device__ __forceinline__ uint64_t sample_draw(const Sim &s, int32_t x)
+template <int HC>
+__device__ __forceinline__ uint64_t sample_draw(const Sim<HC> &s, int32_t x)
 {
     const uint64_t key = ((uint64_t)s.evict_no << 32) + (uint64_t)(uint32_t)x;
     return mix64((s.seed ^ 0xD6E8FEB86659FD93ull) + 0x9E3779B97F4A7C15ull * key);
@@ -956,7 +978,7 @@ __device__ __forceinline__ uint64_t sample_draw(const Sim &s, int32_t x)
 // filter of the first search pass; `sample` stays off when it would keep
 // every candidate (ceil(sqrt(n0)) >= n0)
 template <int HC>
-__device__ __forceinline__ Filter make_filter(Sim &s)
+__device__ __forceinline__ Filter make_filter(Sim<HC> &s)
 {
     Filter F;
     const uint32_t n0 = (uint32_t)s.pool_live;
@@ -1058,7 +1080,7 @@ __device__ __forceinline__ uint64_t sample_draw_at(uint64_t seed, int64_t evict_
 // abandoned (cleared) and its slot listed: those are walked afterwards by
 // whole wavefronts.
 template <int HC>
-__device__ void walk_lanes(const TraceDev &t, const Slot &S, GAS uint64_t *tst, const WalkParams &P,
+__device__ void walk_lanes(const TraceDev &t, const Slot<HC> &S, Tst<HC> tst, const WalkParams &P,
                            int32_t lane, int32_t lid, LAS uint32_t *ctr, LAS uint32_t *novf, Best &best,
                            int64_t &nbr, int64_t &adj, int64_t &nscored)
 {
@@ -1224,7 +1246,8 @@ __device__ void walk_lanes(const TraceDev &t, const Slot &S, GAS uint64_t *tst, 
 // neighbours), claims evicted neighbours with an atomic OR on the bitmap, and
 // claimed ones are appended in lane order.  Returns the summed c0 of the
 // members (uniform); *count gets their number.
-__device__ int64_t walk_wave(const TraceDev &t, GAS uint64_t *tst, GAS uint32_t *bv, GAS int32_t *bq, int32_t x,
+template <int HC>
+__device__ int64_t walk_wave(const TraceDev &t, Tst<HC> tst, GAS uint32_t *bv, GAS int32_t *bq, int32_t x,
                              bool both, int32_t lane, int64_t *count)
 {
     constexpr int WB = 8;
@@ -1307,7 +1330,7 @@ __device__ int64_t walk_wave(const TraceDev &t, GAS uint64_t *tst, GAS uint32_t 
 // shared counter ctr2 (this wavefront alone when ctr2 is null) and keep the
 // best in `best` (lane 0 takes each result).
 template <int HC>
-__device__ void walk_listed(const TraceDev &t, const Slot &S, GAS uint64_t *tst, const WalkParams &P, int32_t lane,
+__device__ void walk_listed(const TraceDev &t, const Slot<HC> &S, Tst<HC> tst, const WalkParams &P, int32_t lane,
                             int32_t wave, int32_t n_ovf, LAS uint32_t *ctr2, Best &best, int64_t &nbr,
                             int64_t &adj, int64_t &nscored)
 {
@@ -1331,7 +1354,7 @@ __device__ void walk_listed(const TraceDev &t, const Slot &S, GAS uint64_t *tst,
         const int64_t size = uni64((int64_t)(((uint64_t)(uint32_t)q1.y << 32) | (uint32_t)q1.x));
         const int64_t c0x = (int64_t)uni(q1.z);
         int64_t cnt = 0;
-        const int64_t sum = walk_wave(t, tst, bv, bq, x, P.both, lane, &cnt);
+        const int64_t sum = walk_wave<HC>(t, tst, bv, bq, x, P.both, lane, &cnt);
         const uint64_t N = (uint64_t)(c0x + sum);
         const uint64_t DA = P.use_m ? (uint64_t)size : 1;
         const uint64_t DB = P.use_s ? (uint64_t)(P.T - last) : 1;
@@ -1475,7 +1498,8 @@ __device__ uint64_t sweep_side(const Sweep &W, bool up, int32_t lane, bool has, 
 
 // List the scan's candidates in node order (pool position << SWEEP_POS_SHIFT
 // | node) and the evicted nodes of every chunk; returns the number listed.
-__device__ __forceinline__ int32_t sweep_list(const Sim &s, const Sweep &W)
+template <int HC>
+__device__ __forceinline__ int32_t sweep_list(const Sim<HC> &s, const Sweep &W)
 {
     constexpr int B = 4;             // chunks whose reads are issued together
     const int32_t F = s.t.F;
@@ -1511,7 +1535,7 @@ __device__ __forceinline__ int32_t sweep_list(const Sim &s, const Sweep &W)
 // its sums over through the control block).  The workgroup barrier inside is
 // passed by every wavefront when nw > 1.
 template <int HC>
-__device__ void sweep_groups(const Slot &S, const Sweep &W, const WalkParams &P, int32_t n, int32_t lane, int32_t wave,
+__device__ void sweep_groups(const Slot<HC> &S, const Sweep &W, const WalkParams &P, int32_t n, int32_t lane, int32_t wave,
                              int32_t nw, LAS WalkCtl *C, Best &best, int64_t &nbr, int64_t &adj, int64_t &nscored)
 {
     const int32_t groups = (n + WAVE - 1) / WAVE;
@@ -1617,7 +1641,7 @@ __device__ __forceinline__ int64_t wave_sum(int64_t v)
 // helpers' bests enter this wavefront's lanes 1.. and their counters are
 // added.
 template <int HC>
-__device__ void walk_scan(Sim &s, const Filter &F, Best &best, int64_t &scored)
+__device__ void walk_scan(Sim<HC> &s, const Filter &F, Best &best, int64_t &scored)
 {
     WalkParams P;
     P.end = s.pool_end;
@@ -1632,7 +1656,7 @@ __device__ void walk_scan(Sim &s, const Filter &F, Best &best, int64_t &scored)
     P.seed = s.seed;
     LAS WalkCtl *C = s.ctl;
     const bool multi = s.nw > 1;
-    const bool swept = s.t.sw != nullptr;
+    const bool swept = small(HC) || s.t.sw != nullptr;
     Sweep W;
     int32_t ncand = 0;
     if (swept) {
@@ -1672,7 +1696,7 @@ __device__ void walk_scan(Sim &s, const Filter &F, Best &best, int64_t &scored)
 #endif
     if (swept) {
         sweep_groups<HC>(s.S, W, P, ncand, s.lane, 0, s.nw, C, best, nbr, adj, nscored);
-    } else {
+    } else if constexpr (!small(HC)) {
         walk_lanes<HC>(s.t, s.S, s.S.tst, P, s.lane, s.lane, multi ? (LAS uint32_t *)&C->ctr : nullptr,
                        (LAS uint32_t *)&C->ovf, best, nbr, adj, nscored);
         if (multi) __syncthreads();
@@ -1682,7 +1706,7 @@ __device__ void walk_scan(Sim &s, const Filter &F, Best &best, int64_t &scored)
     const int64_t w2 = (int64_t)__builtin_readcyclecounter();
     const int64_t w3 = w2;
 #endif
-    if (!swept)
+    if constexpr (!small(HC)) if (!swept)
         walk_listed<HC>(s.t, s.S, s.S.tst, P, s.lane, 0, uni((int32_t)C->ovf),
                         multi ? (LAS uint32_t *)&C->ctr2 : nullptr, best, nbr, adj, nscored);
 #ifdef DTR_PROFILE
@@ -1717,7 +1741,7 @@ __device__ void walk_scan(Sim &s, const Filter &F, Best &best, int64_t &scored)
 // wavefront's walk scans (the three workgroup barriers of each) until it is
 // released at the end of the simulation.
 template <int HC>
-__device__ void help_walks(const KernelArgs &a, const Slot &S, int32_t lane, int32_t wave, LAS WalkCtl *C,
+__device__ void help_walks(const KernelArgs &a, const Slot<HC> &S, int32_t lane, int32_t wave, LAS WalkCtl *C,
                            LAS uint8_t *sweep_lds)
 {
     for (;;) {
@@ -1743,10 +1767,10 @@ __device__ void help_walks(const KernelArgs &a, const Slot &S, int32_t lane, int
         best.slot = -1;
         best.have = 0;
         int64_t nbr = 0, adj = 0, nscored = 0;
-        if (t.sw) {
+        if (small(HC) || t.sw) {
             sweep_groups<HC>(S, sweep_at(sweep_lds, a.sweep_chunks, wave, t), P, uni((int32_t)C->ncand), lane, wave,
                              (int32_t)a.L.walk_waves, C, best, nbr, adj, nscored);
-        } else {
+        } else if constexpr (!small(HC)) {
             walk_lanes<HC>(t, S, S.tst, P, lane, wave * WAVE + lane, (LAS uint32_t *)&C->ctr, (LAS uint32_t *)&C->ovf,
                            best, nbr, adj, nscored);
             __syncthreads();
@@ -1767,7 +1791,7 @@ __device__ void help_walks(const KernelArgs &a, const Slot &S, int32_t lane, int
 // global memory are read one round ahead, so that their latency overlaps the
 // scoring of the round before (scans start in LDS).
 template <int HC>
-__device__ __forceinline__ void scan_rounds(Sim &s, const Filter &F, Best &best, int64_t &scored, bool &bad)
+__device__ __forceinline__ void scan_rounds(Sim<HC> &s, const Filter &F, Best &best, int64_t &scored, bool &bad)
 {
     const int32_t end = s.pool_end;
     const int32_t lane = s.lane;
@@ -1949,7 +1973,7 @@ __device__ __forceinline__ void scan_rounds(Sim &s, const Filter &F, Best &best,
 }
 
 template <int HC>
-__device__ __forceinline__ int32_t scan(Sim &s, int32_t &victim_slot, const Filter &F, int64_t &scored)
+__device__ __forceinline__ int32_t scan(Sim<HC> &s, int32_t &victim_slot, const Filter &F, int64_t &scored)
 {
     bool bad = false;
     Best best;
@@ -1993,7 +2017,7 @@ __device__ __forceinline__ int32_t scan(Sim &s, int32_t &victim_slot, const Filt
 // ----------------------------------------------------- operator calls --
 
 template <int HC>
-__device__ __forceinline__ bool allocate(Sim &s, int64_t sz)
+__device__ __forceinline__ bool allocate(Sim<HC> &s, int64_t sz)
 {
     while (s.mem + sz > s.budget) {
         if (s.pool_live == 0) { set_status(s, ST_OOM); return false; }
@@ -2042,7 +2066,8 @@ struct Frame {
 // leave the pool.  Fills f for single-chunk operations.
 // `head`: when >= -1, lanes below NB_HEAD hold the first entries of ids[b..)
 // already (an operation's inputs are the first neighbours of its output)
-__device__ __forceinline__ void lock_inputs(Sim &s, const int32_t *ids, int32_t b, int32_t e, Frame &f,
+template <int HC>
+__device__ __forceinline__ void lock_inputs(Sim<HC> &s, const int32_t *ids, int32_t b, int32_t e, Frame &f,
                                             int32_t head = -2)
 {
     for (int32_t k0 = b; k0 < e; k0 += WAVE) {
@@ -2074,7 +2099,8 @@ __device__ __forceinline__ void lock_inputs(Sim &s, const int32_t *ids, int32_t 
 
 // reload a frame's inputs after returning from nested rematerializations;
 // lanes below NB_HEAD have their input id from the stack frame already (u8)
-__device__ __forceinline__ void reload_frame(const Sim &s, int32_t b, int32_t e, Frame &f, int32_t u8)
+template <int HC>
+__device__ __forceinline__ void reload_frame(const Sim<HC> &s, int32_t b, int32_t e, Frame &f, int32_t u8)
 {
     const int32_t k = b + s.lane;
     f.u = k < e ? (s.lane < NB_HEAD ? u8 : gld(s.t.in + k)) : -1;
@@ -2084,7 +2110,7 @@ __device__ __forceinline__ void reload_frame(const Sim &s, int32_t b, int32_t e,
 // unlock inputs [b, e); tensors left unlocked and resident rejoin the pool
 // with last access `last`
 template <int HC>
-__device__ __forceinline__ void unlock_inputs(Sim &s, int32_t b, int32_t e, int64_t last, const Frame &f)
+__device__ __forceinline__ void unlock_inputs(Sim<HC> &s, int32_t b, int32_t e, int64_t last, const Frame &f)
 {
     for (int32_t k0 = b; k0 < e; k0 += WAVE) {
         const int32_t k = k0 + s.lane;
@@ -2118,7 +2144,8 @@ __device__ __forceinline__ void unlock_inputs(Sim &s, int32_t b, int32_t e, int6
 }
 
 // index (relative to b) of the first evicted input at or after `from`, or e - b
-__device__ __forceinline__ int32_t next_evicted(const Sim &s, int32_t b, int32_t e, int32_t from, const Frame &f)
+template <int HC>
+__device__ __forceinline__ int32_t next_evicted(const Sim<HC> &s, int32_t b, int32_t e, int32_t from, const Frame &f)
 {
     const bool ev0 = s.lane >= from && b + s.lane < e && ts_sw(f.w) >= 0;
     const uint64_t m0 = __ballot(ev0);
@@ -2136,7 +2163,7 @@ __device__ __forceinline__ int32_t next_evicted(const Sim &s, int32_t b, int32_t
 // run the parent operation of t (record rt); its start time is the last
 // access of its inputs and output
 template <int HC>
-__device__ __forceinline__ bool execute(Sim &s, int32_t t, const TRec &rt, bool remat, uint32_t locks)
+__device__ __forceinline__ bool execute(Sim<HC> &s, int32_t t, const TRec &rt, bool remat, uint32_t locks)
 {
     const int64_t c = rt.c0;
     s.T += c;
@@ -2183,7 +2210,8 @@ __device__ __forceinline__ bool execute(Sim &s, int32_t t, const TRec &rt, bool 
 // is reclaimed if resident (constants included), it is gone for good, and its
 // resident children are pinned (never evictable).  Counted with the eager
 // evictions.
-__device__ __forceinline__ void try_banish(Sim &s, int32_t t)
+template <int HC>
+__device__ __forceinline__ void try_banish(Sim<HC> &s, int32_t t)
 {
     const uint64_t w = (uint64_t)uni64((int64_t)s.S.tst[t]);
     const int32_t b = uni(cld(s.t.ch_off + t)), e = uni(cld(s.t.ch_off + t + 1));
@@ -2225,7 +2253,8 @@ __device__ __forceinline__ void try_banish(Sim &s, int32_t t)
 // after a rematerialization by the operation with inputs [b, e): the new
 // tensor is a child of each input, so pending inputs retry banishing (in
 // listed order)
-__device__ __forceinline__ void retry_banish(Sim &s, int32_t b, int32_t e)
+template <int HC>
+__device__ __forceinline__ void retry_banish(Sim<HC> &s, int32_t b, int32_t e)
 {
     for (int32_t k0 = b; k0 < e; k0 += WAVE) {
         const int32_t k = k0 + s.lane;
@@ -2244,14 +2273,15 @@ __device__ __forceinline__ void retry_banish(Sim &s, int32_t b, int32_t e)
     }
 }
 
+__device__ __forceinline__ GAS int32_t *words(GAS i32x4 *p) { return (GAS int32_t *)p; }
+__device__ __forceinline__ LAS int32_t *words(LAS i32x4 *p) { return (LAS int32_t *)p; }
 constexpr int FQ = (int)(sizeof(StackFrame) / 16);    // 16-byte quads per stack frame
 
 // push the current frame (tensor t, next input to check, its record); lane k
 // below NB_HEAD saves its input id u
-__device__ __forceinline__ void stack_push(const Sim &s, int32_t sp, int32_t t, int32_t next, const TRec &r, int32_t u)
+template <int HC>
+__device__ __forceinline__ void stack_push(const Sim<HC> &s, int32_t sp, int32_t t, int32_t next, const TRec &r, int32_t u)
 {
-    GAS i32x4 *F = s.S.stack + FQ * (size_t)sp;
-    if (s.lane < NB_HEAD) ((GAS int32_t *)(F + 3))[s.lane] = u;
     i32x4 a, b, c;
     a.x = t;
     a.y = next;
@@ -2264,16 +2294,28 @@ __device__ __forceinline__ void stack_push(const Sim &s, int32_t sp, int32_t t, 
     c.y = r.in_e;
     c.z = r.adj_b;
     c.w = r.adj_e;
-    F[0] = a;
-    F[1] = b;
-    F[2] = c;
+    auto put = [&](auto *F) {
+        if (s.lane < NB_HEAD) words(F + 3)[s.lane] = u;
+        F[0] = a;
+        F[1] = b;
+        F[2] = c;
+    };
+    if (small(HC) && sp < SMALL_STACK) put(s.S.stack_l + FQ * sp);
+    else put(s.S.stack + FQ * (size_t)sp);
 }
 
-__device__ __forceinline__ void stack_pop(const Sim &s, int32_t sp, int32_t &t, int32_t &next, TRec &r, int32_t &u8)
+template <int HC>
+__device__ __forceinline__ void stack_pop(const Sim<HC> &s, int32_t sp, int32_t &t, int32_t &next, TRec &r, int32_t &u8)
 {
-    const GAS i32x4 *F = s.S.stack + FQ * (size_t)sp;
-    u8 = s.lane < NB_HEAD ? ((const GAS int32_t *)(F + 3))[s.lane] : -1;
-    const i32x4 a = F[0], b = F[1], c = F[2];
+    i32x4 a, b, c;
+    auto get = [&](auto *F) {
+        u8 = s.lane < NB_HEAD ? words(F + 3)[s.lane] : -1;
+        a = F[0];
+        b = F[1];
+        c = F[2];
+    };
+    if (small(HC) && sp < SMALL_STACK) get(s.S.stack_l + FQ * sp);
+    else get(s.S.stack + FQ * (size_t)sp);
     t = uni(a.x);
     next = uni(a.y);
     r.size = uni64((int64_t)(((uint64_t)(uint32_t)b.y << 32) | (uint32_t)b.x));
@@ -2290,7 +2332,7 @@ __device__ __forceinline__ void stack_pop(const Sim &s, int32_t sp, int32_t &t, 
 // a rematerialization held by the output condition.  Returns false once the
 // simulation has stopped.
 template <int HC>
-__device__ __forceinline__ bool call(Sim &s, int32_t root, bool root_remat, uint32_t root_locks)
+__device__ __forceinline__ bool call(Sim<HC> &s, int32_t root, bool root_remat, uint32_t root_locks)
 {
     int32_t sp = 0;
     int32_t tt = root, cur = -1;
@@ -2364,7 +2406,7 @@ __device__ __forceinline__ bool call(Sim &s, int32_t root, bool root_remat, uint
 // what happens to the tensors released after op o (ascending id): eager
 // eviction, nothing, or banishing
 template <int HC>
-__device__ __forceinline__ bool release(Sim &s, int32_t o)
+__device__ __forceinline__ bool release(Sim<HC> &s, int32_t o)
 {
     const int32_t b = uni(cld(s.t.rel_off + o)), e = uni(cld(s.t.rel_off + o + 1));
     if (s.policy == POLICY_IGNORE) return true;
@@ -2393,10 +2435,10 @@ __device__ __forceinline__ bool release(Sim &s, int32_t o)
 }
 
 template <int HC>
-__device__ __forceinline__ void run_sim(const KernelArgs &a, int32_t sim, const Slot &S, int32_t lane, LAS WalkCtl *ctl,
+__device__ __forceinline__ void run_sim(const KernelArgs &a, int32_t sim, const Slot<HC> &S, int32_t lane, LAS WalkCtl *ctl,
                                        int32_t nw, LAS uint8_t *sweep_lds)
 {
-    Sim s;
+    Sim<HC> s;
     const SpecDev sp = a.specs[sim];
     s.t = a.traces[sp.trace];
     s.S = S;
@@ -2538,11 +2580,11 @@ __device__ __forceinline__ void run_sim(const KernelArgs &a, int32_t sim, const 
 // allocation serves four simulations).
 template <int HC>
 __device__ __forceinline__ void eq_waves(const KernelArgs &a, UfNode *lds_nodes, PoolSlotL *lds_pool, int32_t lane,
-                                         int32_t wave)
+                                         int32_t wave, LAS uint8_t *lds_small)
 {
     const int32_t slot = (int32_t)blockIdx.x * lds_waves(HC) + wave;
     if (slot >= a.n_slots) return;
-    Slot S = slot_at(a, slot);
+    Slot<HC> S = slot_at<HC>(a, slot, lds_small + wave * small_lds_bytes(a.small_n));
     S.nodes.lds = lds_nodes + wave * UF_LDS;
     S.nodes.lds_l = (LAS UfNode *)lds_nodes + wave * UF_LDS;
     S.lpool = lds_pool + wave * POOL_LDS;
@@ -2567,7 +2609,9 @@ __global__ void __launch_bounds__(cls(HC) == HC_WALK ? MAX_WALK_WAVES * WAVE : l
     __attribute__((amdgpu_waves_per_eu(2))) replay_kernel(KernelArgs a)
 {
     constexpr int LW = lds_waves(HC);
-    extern __shared__ __align__(16) uint8_t lds_dyn[];       // the sweeps' arrays (walk heuristics)
+    // the sweeps' arrays (walk heuristics), then each simulation's state
+    // words and stack top (small traces)
+    extern __shared__ __align__(16) uint8_t lds_dyn[];
     // union-find nodes (h_DTR^eq: one array per wavefront), or the walk
     // control block (walk heuristics)
     __shared__ UfNode lds_nodes[cls(HC) == HC_EQ ? UF_LDS * LW : CTL_NODES];
@@ -2575,23 +2619,25 @@ __global__ void __launch_bounds__(cls(HC) == HC_WALK ? MAX_WALK_WAVES * WAVE : l
     const int32_t lane = (int32_t)threadIdx.x & (WAVE - 1);
     const int32_t wave = uni((int32_t)threadIdx.x / WAVE);
     if constexpr (LW > 1) {
-        eq_waves<HC>(a, lds_nodes, lds_pool, lane, wave);
+        eq_waves<HC>(a, lds_nodes, lds_pool, lane, wave, (LAS uint8_t *)lds_dyn);
         return;
     }
     const int32_t nw = cls(HC) == HC_WALK ? (int32_t)a.L.walk_waves : 1;
-    Slot S = slot_at(a, blockIdx.x);
+    Slot<HC> S = slot_at<HC>(a, blockIdx.x, (LAS uint8_t *)lds_dyn + (cls(HC) == HC_WALK ? sweep_lds_bytes(a.sweep_chunks, nw) : 0));
     S.nodes.lds = lds_nodes;
     S.nodes.lds_l = (LAS UfNode *)lds_nodes;
     S.lpool = lds_pool;
     S.lpool_l = (LAS PoolSlotL *)lds_pool;
     LAS WalkCtl *ctl = (LAS WalkCtl *)lds_nodes;
-    if (cls(HC) == HC_WALK) {
-        // visited bitmaps start clear (every walk clears what it set)
-        // (the flags 16 bytes at a time: vis_bytes is a multiple of 16)
-        GAS u32x4 *V = (GAS u32x4 *)(S.visb + (size_t)(wave * WAVE) * (size_t)S.vis_bytes);
-        for (size_t i = lane; i < (size_t)WAVE * (size_t)S.vis_bytes / 16; i += WAVE) V[i] = u32x4{0u, 0u, 0u, 0u};
-        GAS uint32_t *B = S.bigvis + (size_t)wave * (size_t)S.vis_words;
-        for (int32_t i = lane; i < S.vis_words; i += WAVE) B[i] = 0u;
+    if constexpr (cls(HC) == HC_WALK) {
+        if constexpr (!small(HC)) {
+            // visited bitmaps start clear (every walk clears what it set)
+            // (the flags 16 bytes at a time: vis_bytes is a multiple of 16)
+            GAS u32x4 *V = (GAS u32x4 *)(S.visb + (size_t)(wave * WAVE) * (size_t)S.vis_bytes);
+            for (size_t i = lane; i < (size_t)WAVE * (size_t)S.vis_bytes / 16; i += WAVE) V[i] = u32x4{0u, 0u, 0u, 0u};
+            GAS uint32_t *B = S.bigvis + (size_t)wave * (size_t)S.vis_words;
+            for (int32_t i = lane; i < S.vis_words; i += WAVE) B[i] = 0u;
+        }
         // and so do this wavefront's reach masks
         LAS uint64_t *M = (LAS uint64_t *)((LAS uint8_t *)lds_dyn + (8 + 4 * WAVE) * a.sweep_chunks) +
                           wave * WAVE * a.sweep_chunks;
@@ -2667,29 +2713,42 @@ extern "C" hipError_t dtr_launch_reset(uint32_t *queue, hipStream_t stream)
     return hipGetLastError();
 }
 
+template <int HC>
+static hipError_t launch(const dtr::KernelArgs &a, hipStream_t stream)
+{
+    using namespace dtr;
+    const int64_t waves = cls(HC) == HC_WALK ? a.L.walk_waves : lds_waves(HC);
+    // h_DTR^eq: a slot per wavefront; the others: one per workgroup
+    const dim3 grid((uint32_t)((a.n_slots + lds_waves(HC) - 1) / lds_waves(HC))), blk((uint32_t)(WAVE * waves));
+    int64_t lds = small_lds_bytes(small(HC) ? a.small_n : 0) * lds_waves(HC);
+    if (cls(HC) == HC_WALK) lds += sweep_lds_bytes(a.sweep_chunks, waves);
+    if (lds > 0) {
+        // (a workgroup may take more than the default 64 KB, static LDS included)
+        const hipError_t e = hipFuncSetAttribute((const void *)replay_kernel<HC>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(replay_kernel<HC>, grid, blk, (uint32_t)lds, stream, a);
+    return hipGetLastError();
+}
+
 extern "C" hipError_t dtr_launch_group(const dtr::KernelArgs *a, int32_t group, hipStream_t stream)
 {
     using namespace dtr;
     if (a->n_sims <= 0) return hipSuccess;
-    const dim3 grid(a->n_slots), blk(WAVE), wblk(WAVE * (uint32_t)a->L.walk_waves);
-    const uint32_t wlds = (uint32_t)sweep_lds_bytes(a->sweep_chunks, a->L.walk_waves);
-    // the exact h_DTR^eq kernel: EQ_WAVES slots per workgroup
-    const dim3 egrid((a->n_slots + EQ_WAVES - 1) / EQ_WAVES), eblk(WAVE * EQ_WAVES);
-    // (the kernels' static LDS, about 14 KB, comes on top)
-    if (wlds > 48 * 1024 && (group == 1 || group == 4)) {
-        const void *f = group == 1 ? (const void *)replay_kernel<HC_WALK>
-                                   : (const void *)replay_kernel<HC_WALK | HC_APPROX>;
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)wlds);
-        if (e != hipSuccess) return e;
-    }
-    switch (group) {
-    case 0: hipLaunchKernelGGL(replay_kernel<HC_EQ>, egrid, eblk, 0, stream, *a); break;
-    case 1: hipLaunchKernelGGL(replay_kernel<HC_WALK>, grid, wblk, wlds, stream, *a); break;
-    case 2: hipLaunchKernelGGL(replay_kernel<HC_SIMPLE>, grid, blk, 0, stream, *a); break;
-    case 3: hipLaunchKernelGGL(replay_kernel<HC_EQ | HC_APPROX>, grid, blk, 0, stream, *a); break;
-    case 4: hipLaunchKernelGGL(replay_kernel<HC_WALK | HC_APPROX>, grid, wblk, wlds, stream, *a); break;
-    case 5: hipLaunchKernelGGL(replay_kernel<HC_SIMPLE | HC_APPROX>, grid, blk, 0, stream, *a); break;
+    switch (group + (a->small_n > 0 ? N_GROUPS : 0)) {
+    case 0: return launch<HC_EQ>(*a, stream);
+    case 1: return launch<HC_WALK>(*a, stream);
+    case 2: return launch<HC_SIMPLE>(*a, stream);
+    case 3: return launch<HC_EQ | HC_APPROX>(*a, stream);
+    case 4: return launch<HC_WALK | HC_APPROX>(*a, stream);
+    case 5: return launch<HC_SIMPLE | HC_APPROX>(*a, stream);
+    case 6: return launch<HC_EQ | HC_SMALL>(*a, stream);
+    case 7: return launch<HC_WALK | HC_SMALL>(*a, stream);
+    case 8: return launch<HC_SIMPLE | HC_SMALL>(*a, stream);
+    case 9: return launch<HC_EQ | HC_APPROX | HC_SMALL>(*a, stream);
+    case 10: return launch<HC_WALK | HC_APPROX | HC_SMALL>(*a, stream);
+    case 11: return launch<HC_SIMPLE | HC_APPROX | HC_SMALL>(*a, stream);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }

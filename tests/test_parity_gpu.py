@@ -511,6 +511,33 @@ def test_sweep_chunk_edges(gpu, oracle_lib, waves):
     compare(gpu.run(traces, specs, flags=gpu.opt_walk_waves(waves)), ref, specs, f"sweep edges waves={waves}")
 
 
+def test_small_trace_limits(gpu, oracle_lib):
+    """Traces of up to 2048 tensors keep their state words and the top 16
+    stack frames in LDS: the limit and one tensor more, deep
+    rematerialization, tiny traces, every class of heuristics, exact search
+    and the approximations, and more h_DTR^eq simulations than are resident
+    at once that way."""
+    traces, rows = [], []
+    for s, n in enumerate((1, 2, 3, 65, 2047, 2048, 2049)):
+        tr = W.random_program(5400 + s, n_ops=n - n // 20, n_const=n // 20, max_in=3, max_size=9, max_cost=9, window=30)
+        assert tr.n_tensors == n
+        traces.append(tr)
+    traces += [W.chain_trace(200), W.chain_trace(32)]
+    batches = {}
+    for i, tr in enumerate(traces):
+        peak = W.natural_peak(tr)
+        for h in (W.H_EQ, W.H_LRU, W.H_RAND, W.H_MSPS, W.h_family(W.C_EQCLASS, 0, 1)):
+            for frac in (0.5, 0.8) if tr.n_tensors > 1000 else (0.3, 0.5, 0.8):
+                for search in (0, 3):
+                    row = (i, h, max(1, int(peak * frac)), i, W.POLICY_EAGER, search)
+                    batches.setdefault((tr.n_tensors > 2048, search, W.H_EQ == h), []).append(row)
+    batches["eq"] = [(8, W.H_EQ, 9 + k % 24, k) for k in range(2100)]
+    for key, rows in batches.items():
+        specs = specs_of(rows)
+        print(f"small traces {key}: {len(specs)} sims", flush=True)
+        compare(gpu.run(traces, specs), oracle_lib.run(traces, specs), specs, f"small traces {key}")
+
+
 _EQ_BATCH = {}
 
 
