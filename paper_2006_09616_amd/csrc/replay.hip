@@ -144,6 +144,24 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z)
     return z ^ (z >> 31);
 }
 
+// x's minimum over the lanes that are not NaN (uniform): row shifts, then the
+// rows' results passed on, a few cycles a step where a shuffle goes through LDS
+__device__ __forceinline__ float wave_min(float x)
+{
+    auto step = [&](auto ctrl, auto rows) {
+        const int v = __builtin_bit_cast(int, x);
+        x = fminf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, ctrl.value, rows.value, 0xF, false)));
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>(), integral_constant<int, 0xF>());    // row_shr:1
+    step(integral_constant<int, 0x112>(), integral_constant<int, 0xF>());    // row_shr:2
+    step(integral_constant<int, 0x114>(), integral_constant<int, 0xF>());    // row_shr:4
+    step(integral_constant<int, 0x118>(), integral_constant<int, 0xF>());    // row_shr:8
+    step(integral_constant<int, 0x142>(), integral_constant<int, 0xA>());    // row_bcast:15 into rows 1 and 3
+    step(integral_constant<int, 0x143>(), integral_constant<int, 0xC>());    // row_bcast:31 into rows 2 and 3
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), WAVE - 1));
+}
+
 // a strictly better (lower score) than b; ties go to the smaller id
 __device__ __forceinline__ bool better(uint64_t na, u128 da, int32_t ia, uint64_t nb, u128 db, int32_t ib)
 {
@@ -154,17 +172,44 @@ __device__ __forceinline__ bool better(uint64_t na, u128 da, int32_t ia, uint64_
 }
 
 // Union-find node store: ids below UF_LDS in this wavefront's LDS array, the
-// rest in the slot's global array; one id space, read through flat pointers
-// (or straight from LDS while every node id is below UF_LDS).
+// rest in the slot's global array; one id space.  Each access takes an LDS or
+// a global instruction (a flat one would wait for both kinds).
 struct NodeStore {
-    UfNode *lds;
     LAS UfNode *lds_l;
-    UfNode *glob;
-    __device__ __forceinline__ UfNode &operator[](int32_t id) const
+    GAS UfNode *glob;
+    template <class F>
+    __device__ __forceinline__ void at(int32_t id, F f) const
     {
-        return id < UF_LDS ? lds[id] : glob[id - UF_LDS];
+        if (id < UF_LDS) f(lds_l + id);
+        else f(glob + (id - UF_LDS));
     }
+    __device__ __forceinline__ int32_t parent(int32_t i) const
+    {
+        int32_t v;
+        at(i, [&](auto *n) { v = n->parent; });
+        return v;
+    }
+    __device__ __forceinline__ int32_t size(int32_t i) const
+    {
+        int32_t v;
+        at(i, [&](auto *n) { v = n->size; });
+        return v;
+    }
+    __device__ __forceinline__ int64_t cost(int32_t i) const
+    {
+        int64_t v;
+        at(i, [&](auto *n) { v = n->cost; });
+        return v;
+    }
+    __device__ __forceinline__ void set_parent(int32_t i, int32_t v) const { at(i, [&](auto *n) { n->parent = v; }); }
+    __device__ __forceinline__ void set_size(int32_t i, int32_t v) const { at(i, [&](auto *n) { n->size = v; }); }
+    __device__ __forceinline__ void set_cost(int32_t i, int64_t v) const { at(i, [&](auto *n) { n->cost = v; }); }
 };
+
+// 32-bit words of a quad array (a pool slot: id, degree and count, last access
+// (2), size (2), c0, neighbour range, cached nodes)
+__device__ __forceinline__ GAS int32_t *words(GAS i32x4 *p) { return (GAS int32_t *)p; }
+__device__ __forceinline__ LAS int32_t *words(LAS i32x4 *p) { return (LAS int32_t *)p; }
 
 // LDS pool slots are padded to 80 bytes, so the 16-byte reads of 64
 // consecutive slots fall in distinct bank groups
@@ -184,7 +229,6 @@ struct Slot {
     Tst<HC> tst;
     LAS i32x4 *stack_l;           // the first SMALL_STACK frames (small traces)
     GAS int32_t *lockx;           // lock counts >= LOCKS_SAT
-    PoolSlotL *lpool;             // flat view of the LDS head
     LAS PoolSlotL *lpool_l;
     GAS PoolSlot *gpool;
     NodeStore nodes;
@@ -198,9 +242,22 @@ struct Slot {
     GAS uint8_t *pending;         // released, banishing deferred (banishing policy)
     int32_t pcap, ucap, n_max;
     int32_t vis_words, vis_bytes, wq_cap;
-    __device__ __forceinline__ PoolSlot &pool(int32_t i) const
+    // f on the quads of pool slot i, through an LDS or a global pointer: a
+    // flat access would wait for every outstanding access of both kinds
+    template <class F>
+    __device__ __forceinline__ void pool(int32_t i, F f) const
     {
-        return i < POOL_LDS ? lpool[i].s : *(PoolSlot *)(gpool + i);
+        if (i < POOL_LDS) f((LAS i32x4 *)lpool_l + PQL * i);
+        else f((GAS i32x4 *)gpool + PQ * (size_t)i);
+    }
+    __device__ __forceinline__ void pool_kill(int32_t i) const
+    {
+        pool(i, [](auto *Q) { words(Q)[0] = -1; });
+    }
+    // the slot's two header quads
+    __device__ __forceinline__ void pool_head(int32_t i, i32x4 &q0, i32x4 &q1) const
+    {
+        pool(i, [&](auto *Q) { q0 = Q[0]; q1 = Q[1]; });
     }
 };
 
@@ -213,12 +270,10 @@ __device__ __forceinline__ Slot<HC> slot_at(const KernelArgs &a, int32_t k, LAS 
     else S.tst = (GAS uint64_t *)(b + a.L.tst);
     S.stack_l = (LAS i32x4 *)(lds_small + 8 * (size_t)a.small_n);
     S.lockx = (GAS int32_t *)(b + a.L.lockx);
-    S.lpool = nullptr;
     S.lpool_l = nullptr;
     S.gpool = (GAS PoolSlot *)(b + a.L.pool);
-    S.nodes.lds = nullptr;
     S.nodes.lds_l = nullptr;
-    S.nodes.glob = (UfNode *)(b + a.L.nodes);
+    S.nodes.glob = (GAS UfNode *)(b + a.L.nodes);
     S.remap = (GAS int32_t *)(b + a.L.uf_remap);
     S.stack = (GAS i32x4 *)(b + a.L.stack);
     S.visb = (GAS uint8_t *)(b + a.L.vis);
@@ -325,45 +380,65 @@ __device__ __forceinline__ TRec rec_v(const Sim<HC> &s, int32_t x) { return rec_
 // ------------------------------------------------------ neighbour cache --
 
 // This lane's cache of evicted-neighbour nodes for a tensor with neighbour
-// range [b, e), built in registers: the first K evicted neighbours' nodes
-// (unused entries hold node 0, the null node: cost 0, its own root).  Returns
-// the cache; `deg` receives (degree << 8) | count (K + 1: overflowed).
-// Neighbour states are read LB at a time, all loads unconditional.
+// range [b, e) (empty for a lane without one), built in registers: the first K
+// evicted neighbours' nodes (unused entries hold node 0, the null node: cost
+// 0, its own root).  Returns the cache; `deg` receives (degree << 8) | count
+// (K + 1: overflowed).  A tensor with up to LB neighbours is read by its own
+// lane, all loads issued together; one with more by the whole wavefront, 64
+// neighbours at a time (a lane of its own would take two dependent reads per
+// LB neighbours).  Called by every lane.
 struct NbCache {
     i32x4 q[KQ];
 };
 
 template <int HC>
-__device__ __forceinline__ NbCache list_build(const Sim<HC> &s, int32_t b, int32_t e, int32_t &deg,
-                                              const i32x4 *head = nullptr)
+__device__ __forceinline__ NbCache list_build(const Sim<HC> &s, int32_t b, int32_t e, int32_t &deg, const i32x4 *head)
 {
     int32_t c[K];
 #pragma unroll
     for (int k = 0; k < K; k++) c[k] = 0;
     int32_t cnt = 0;
-    for (int32_t k0 = b; k0 < e; k0 += LB) {
+    const bool wide = e - b > LB;
+    {
         int32_t w[LB];
         int32_t q[LB];
-        if (head && k0 == b) {
 #pragma unroll
-            for (int j = 0; j < LB / 4; j++) {
-                w[4 * j] = head[j].x;
-                w[4 * j + 1] = head[j].y;
-                w[4 * j + 2] = head[j].z;
-                w[4 * j + 3] = head[j].w;
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < LB; j++) w[j] = gld(s.t.adj + (k0 + j < e ? k0 + j : k0));
+        for (int j = 0; j < LB / 4; j++) {
+            w[4 * j] = head[j].x;
+            w[4 * j + 1] = head[j].y;
+            w[4 * j + 2] = head[j].z;
+            w[4 * j + 3] = head[j].w;
         }
 #pragma unroll
         for (int j = 0; j < LB; j++) q[j] = ts_sw(s.S.tst[w[j]]);
 #pragma unroll
         for (int j = 0; j < LB; j++) {
-            const bool v = k0 + j < e && q[j] >= 0;
+            const bool v = b + j < e && q[j] >= 0 && !wide;
 #pragma unroll
-            for (int k = 0; k < K; k++) c[k] = v && cnt == k ? q[j] : c[k];
+            for (int k = 0; k <= j && k < K; k++) c[k] = v && cnt == k ? q[j] : c[k];
             cnt += v ? 1 : 0;
+        }
+    }
+    for (uint64_t m = ballot(wide); m; m &= m - 1) {
+        const int32_t j = __builtin_ctzll(m);
+        const int32_t jb = __builtin_amdgcn_readlane(b, j), je = __builtin_amdgcn_readlane(e, j);
+        int32_t total = 0, got = 0;           // got: lane k holds the k-th evicted neighbour's node
+        for (int32_t k0 = jb; k0 < je; k0 += WAVE) {
+            const int32_t k = k0 + s.lane;
+            const int32_t q = k < je ? ts_sw(s.S.tst[gld(s.t.adj + k)]) : -1;
+            const uint64_t ev = ballot(q >= 0);
+            // send each node to the lane of its rank (nodes past the cache, and
+            // lanes without one, to the last lane; a lane sent nothing gets 0)
+            const int32_t to = q >= 0 ? min(total + lane_rank(ev), WAVE - 1) : WAVE - 1;
+            got |= __builtin_amdgcn_ds_permute(4 * to, q);
+            total += __popcll(ev);
+        }
+        const bool me = s.lane == j;
+        cnt = me ? total : cnt;
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            const int32_t v = __builtin_amdgcn_readlane(got, k);
+            c[k] = me ? v : c[k];
         }
     }
     deg = ((e - b) << 8) | (cnt > K ? K + 1 : cnt);
@@ -378,38 +453,37 @@ __device__ __forceinline__ NbCache list_build(const Sim<HC> &s, int32_t b, int32
     return r;
 }
 
-__device__ __forceinline__ void cache_store(PoolSlot &ps, const NbCache &c)
-{
-#pragma unroll
-    for (int k = 0; k < KQ; k++) ((i32x4 *)ps.nb)[k] = c.q[k];
-}
-
 template <int HC>
 __device__ __forceinline__ void list_add(const Sim<HC> &s, int32_t i, int32_t nd)
 {
-    PoolSlot &ps = s.S.pool(i);
-    const int32_t pd = ps.deg;
-    const int32_t c = pd & 0xFF;
-    if (c > K) return;
-    if (c < K) ps.nb[c] = nd;
-    ps.deg = (pd & ~0xFF) | (c + 1);
+    s.S.pool(i, [&](auto *Q) {
+        auto *w = words(Q);
+        const int32_t pd = w[1];
+        const int32_t c = pd & 0xFF;
+        if (c > K) return;
+        if (c < K) w[8 + c] = nd;
+        w[1] = (pd & ~0xFF) | (c + 1);
+    });
 }
 
 // returns false if nd was not cached (cannot happen while the caches are consistent)
 template <int HC>
 __device__ __forceinline__ bool list_remove(const Sim<HC> &s, int32_t i, int32_t nd)
 {
-    PoolSlot &ps = s.S.pool(i);
     int32_t v[K];
+    i32x4 q0;
+    s.S.pool(i, [&](auto *Q) {
+        q0 = Q[0];
 #pragma unroll
-    for (int k = 0; k < KQ; k++) {
-        const i32x4 q = ((const i32x4 *)ps.nb)[k];
-        v[4 * k] = q.x;
-        v[4 * k + 1] = q.y;
-        v[4 * k + 2] = q.z;
-        v[4 * k + 3] = q.w;
-    }
-    const int32_t pd = ps.deg;
+        for (int k = 0; k < KQ; k++) {
+            const i32x4 q = Q[2 + k];
+            v[4 * k] = q.x;
+            v[4 * k + 1] = q.y;
+            v[4 * k + 2] = q.z;
+            v[4 * k + 3] = q.w;
+        }
+    });
+    const int32_t pd = q0.y;
     const int32_t c = pd & 0xFF;
     if (c > K) return true;
     int32_t at = -1;
@@ -421,9 +495,12 @@ __device__ __forceinline__ bool list_remove(const Sim<HC> &s, int32_t i, int32_t
 #pragma unroll
     for (int k = 0; k < K; k++)
         if (k == c - 1) lastv = v[k];
-    ps.nb[at] = lastv;
-    ps.nb[c - 1] = 0;
-    ps.deg = (pd & ~0xFF) | (c - 1);
+    s.S.pool(i, [&](auto *Q) {
+        auto *w = words(Q);
+        w[8 + at] = lastv;
+        w[8 + c - 1] = 0;
+        w[1] = (pd & ~0xFF) | (c - 1);
+    });
     return true;
 }
 
@@ -485,23 +562,26 @@ __device__ __forceinline__ void pool_compact(Sim<HC> &s)
     slot_sync<HC>();
     for (int32_t base = 0; base < s.pool_end; base += WAVE) {
         const int32_t i = base + lane;
-        const i32x4 *P = (const i32x4 *)&s.S.pool(i < s.pool_end ? i : 0);
-        const i32x4 q0 = P[0], q1 = P[1];
-        i32x4 qc[KQ];
+        i32x4 q0, q1, qc[KQ];
+        s.S.pool(i < s.pool_end ? i : 0, [&](auto *P) {
+            q0 = P[0];
+            q1 = P[1];
 #pragma unroll
-        for (int k = 0; k < KQ; k++) qc[k] = cls(HC) != HC_SIMPLE ? P[2 + k] : 0;
+            for (int k = 0; k < KQ; k++) qc[k] = cls(HC) != HC_SIMPLE ? P[2 + k] : 0;
+        });
         const int32_t x = i < s.pool_end ? q0.x : -1;
         const bool keep = x >= 0;
-        const uint64_t m = __ballot(keep);
+        const uint64_t m = ballot(keep);
         slot_sync<HC>();
         if (keep) {
             const int32_t j = kept + lane_rank(m);
-            i32x4 *Q = (i32x4 *)&s.S.pool(j);
-            Q[0] = q0;
-            Q[1] = q1;
-            if (cls(HC) != HC_SIMPLE)
+            s.S.pool(j, [&](auto *Q) {
+                Q[0] = q0;
+                Q[1] = q1;
+                if (cls(HC) != HC_SIMPLE)
 #pragma unroll
-                for (int k = 0; k < KQ; k++) Q[2 + k] = qc[k];
+                    for (int k = 0; k < KQ; k++) Q[2 + k] = qc[k];
+            });
             s.S.tst[x] = ts_make(S_RESIDENT, (uint32_t)j, 0);
         }
         kept += __popcll(m);
@@ -516,28 +596,31 @@ __device__ __forceinline__ void pool_compact(Sim<HC> &s)
 template <int HC>
 __device__ __forceinline__ int32_t pool_append(Sim<HC> &s, bool want, int32_t x, int64_t last, const TRec *known = nullptr)
 {
-    const uint64_t m = __ballot(want);
+    const uint64_t m = ballot(want);
     if (!m) return -1;
     const int32_t cnt = __popcll(m);
     if (s.pool_end + cnt > s.S.pcap) {
         pool_compact<HC>(s);
         if (s.pool_end + cnt > s.S.pcap) { set_status(s, ST_CAPACITY); return -1; }
     }
-    int32_t i = -1;
+    // the record and the first neighbours are one 64-byte element
+    TRec r = {};
+    i32x4 hd[2] = {};
     if (want) {
-        i = s.pool_end + lane_rank(m);
-        // the record and the first neighbours are one 64-byte element
         const GAS i32x4 *px = (const GAS i32x4 *)&s.t.rec[x];
-        i32x4 hd[2];
         if (cls(HC) != HC_SIMPLE) {
             hd[0] = px[2];
             hd[1] = px[3];
         }
-        const TRec r = known ? *known : rec_v(s, x);
-        // walk heuristics: the low byte holds the parent count (255: read the record)
-        int32_t deg = (r.adj_e - r.adj_b) << 8 | (cls(HC) == HC_WALK ? min(r.in_e - r.in_b, 255) : 0);
-        NbCache nb;
-        if (cls(HC) == HC_EQ) nb = list_build(s, r.adj_b, r.adj_e, deg, hd);
+        r = known ? *known : rec_v(s, x);
+    }
+    // walk heuristics: the low byte holds the parent count (255: read the record)
+    int32_t deg = (r.adj_e - r.adj_b) << 8 | (cls(HC) == HC_WALK ? min(r.in_e - r.in_b, 255) : 0);
+    NbCache nb;
+    if (cls(HC) == HC_EQ) nb = list_build(s, r.adj_b, r.adj_e, deg, hd);
+    int32_t i = -1;
+    if (want) {
+        i = s.pool_end + lane_rank(m);
         i32x4 q0, q1;
         q0.x = x;
         q0.y = deg;
@@ -547,15 +630,14 @@ __device__ __forceinline__ int32_t pool_append(Sim<HC> &s, bool want, int32_t x,
         q1.y = (int32_t)(uint32_t)((uint64_t)r.size >> 32);
         q1.z = r.c0;
         q1.w = r.adj_b;
-        i32x4 *Q = (i32x4 *)&s.S.pool(i);
-        Q[0] = q0;
-        Q[1] = q1;
-        if (cls(HC) == HC_EQ) cache_store(s.S.pool(i), nb);
-        if (cls(HC) == HC_WALK) {
-            // the first neighbours, so that a walk starts from the slot alone
-            Q[2] = hd[0];
-            Q[3] = hd[1];
-        }
+        s.S.pool(i, [&](auto *Q) {
+            Q[0] = q0;
+            Q[1] = q1;
+            // walks: the first neighbours, so that a walk starts from the slot alone
+#pragma unroll
+            for (int k = 0; k < KQ; k++)
+                if (cls(HC) != HC_SIMPLE) Q[2 + k] = cls(HC) == HC_EQ ? nb.q[k] : hd[k];
+        });
     }
     s.pool_end += cnt;
     s.pool_live += cnt;
@@ -564,8 +646,8 @@ __device__ __forceinline__ int32_t pool_append(Sim<HC> &s, bool want, int32_t x,
 
 // ---------------------------------------------------------- union-find --
 
-// Union-find node access: straight from LDS while every node id is below
-// UF_LDS, else through the hybrid store (flat pointers).
+// Union-find node access straight from LDS, while every node id is below
+// UF_LDS (else through the NodeStore).
 struct LdsNodes {
     LAS UfNode *p;
     __device__ __forceinline__ int32_t parent(int32_t i) const { return p[i].parent; }
@@ -575,32 +657,12 @@ struct LdsNodes {
     __device__ __forceinline__ void set_size(int32_t i, int32_t v) const { p[i].size = v; }
     __device__ __forceinline__ void set_cost(int32_t i, int64_t v) const { p[i].cost = v; }
 };
-struct AnyNodes {
-    NodeStore n;
-    __device__ __forceinline__ int32_t parent(int32_t i) const { return n[i].parent; }
-    __device__ __forceinline__ int32_t size(int32_t i) const { return n[i].size; }
-    __device__ __forceinline__ int64_t cost(int32_t i) const { return n[i].cost; }
-    __device__ __forceinline__ void set_parent(int32_t i, int32_t v) const { n[i].parent = v; }
-    __device__ __forceinline__ void set_size(int32_t i, int32_t v) const { n[i].size = v; }
-    __device__ __forceinline__ void set_cost(int32_t i, int64_t v) const { n[i].cost = v; }
-};
-
 
 template <class NS>
 __device__ __forceinline__ int32_t find_in(const NS &N, int32_t x, int32_t limit)
 {
     for (int32_t k = 0; k <= limit; k++) {
         const int32_t p = N.parent(x);
-        if (p == x) return x;
-        x = p;
-    }
-    return -1;   // not a forest: reported as a capacity error
-}
-
-__device__ __forceinline__ int32_t find_ro(const NodeStore &nodes, int32_t x, int32_t limit)
-{
-    for (int32_t k = 0; k <= limit; k++) {
-        const int32_t p = nodes[x].parent;
         if (p == x) return x;
         x = p;
     }
@@ -646,7 +708,7 @@ __device__ __forceinline__ void uf_compact(Sim<HC> &s)
         const uint64_t w = s.S.tst[x];
         const int32_t v = ts_sw(w);
         if (v >= 0) {
-            int32_t r = find_ro(N, v, s.uf_n);
+            int32_t r = find_in(N, v, s.uf_n);
             if (r < 0) r = v;        // cannot happen in a forest; keeps indices in range
             s.S.tst[x] = ts_make(v, (uint32_t)r, ts_locks(w));   // pos is unused while evicted
             R[r] = 0;
@@ -657,17 +719,17 @@ __device__ __forceinline__ void uf_compact(Sim<HC> &s)
     for (int32_t base = 0; base < s.uf_n; base += WAVE) {
         const int32_t i = base + lane;
         const bool keep = i > 0 && i < s.uf_n && R[i] == 0;
-        const int64_t c = keep ? N[i].cost : 0;
-        const uint64_t m = __ballot(keep);
+        const int64_t c = keep ? N.cost(i) : 0;
+        const uint64_t m = ballot(keep);
         wave_sync();
         if (keep) {
             const int32_t ni = kept + lane_rank(m);
             R[i] = ni;
-            UfNode nd;
-            nd.cost = c;
-            nd.parent = ni;
-            nd.size = 1;
-            N[ni] = nd;
+            N.at(ni, [&](auto *nd) {
+                nd->cost = c;
+                nd->parent = ni;
+                nd->size = 1;
+            });
         }
         kept += __popcll(m);
         wave_sync();
@@ -680,15 +742,26 @@ __device__ __forceinline__ void uf_compact(Sim<HC> &s)
     s.uf_n = kept;
     // stay inside LDS while the live sets fit comfortably, else double
     s.uf_limit = kept + 256 <= UF_LDS ? UF_LDS : min(UF_LDS + s.S.ucap, 2 * kept + 256);
-    for (int32_t i = lane; i < s.pool_end; i += WAVE) {
-        PoolSlot &ps = s.S.pool(i);
-        const int32_t x = ps.id;
+    for (int32_t i0 = 0; i0 < s.pool_end; i0 += WAVE) {
+        const int32_t i = i0 + lane;
+        int32_t x = -1;
+        if (i < s.pool_end) s.S.pool(i, [&](auto *Q) { x = words(Q)[0]; });
+        TRec r = {};
+        i32x4 hd[2] = {};
         if (x >= 0) {
-            const TRec r = rec_v(s, x);
-            int32_t deg;
-            cache_store(ps, list_build(s, r.adj_b, r.adj_e, deg));
-            ps.deg = deg;
+            const GAS i32x4 *px = (const GAS i32x4 *)&s.t.rec[x];
+            hd[0] = px[2];
+            hd[1] = px[3];
+            r = rec_v(s, x);
         }
+        int32_t deg;
+        const NbCache nb = list_build(s, r.adj_b, r.adj_e, deg, hd);
+        if (x >= 0)
+            s.S.pool(i, [&](auto *Q) {
+                words(Q)[1] = deg;
+#pragma unroll
+                for (int k = 0; k < KQ; k++) Q[2 + k] = nb.q[k];
+            });
     }
     wave_sync();
 }
@@ -724,7 +797,7 @@ __device__ __forceinline__ bool evict_merge(Sim<HC> &s, const NS &N, int32_t nd,
         }
         // first lane holding each distinct root contributes it
         bool first = r >= 0;
-        uint64_t m = __ballot(r >= 0);
+        uint64_t m = ballot(r >= 0);
         while (m) {
             const int32_t j = __ffsll((long long)m) - 1;
             m &= m - 1;
@@ -739,7 +812,7 @@ __device__ __forceinline__ bool evict_merge(Sim<HC> &s, const NS &N, int32_t nd,
             rs = N.size(r);
         }
         // merge every distinct root into the largest (ties: the earliest)
-        uint64_t mr = __ballot(r >= 0);
+        uint64_t mr = ballot(r >= 0);
         int32_t big = R, bigsize = Rsize;
         int64_t sumc = Rcost;
         int32_t sums = Rsize;
@@ -762,7 +835,7 @@ __device__ __forceinline__ bool evict_merge(Sim<HC> &s, const NS &N, int32_t nd,
             Rsize = sums;
         }
     }
-    if (__ballot(bad)) { set_status(s, ST_CAPACITY); return false; }
+    if (ballot(bad)) { set_status(s, ST_CAPACITY); return false; }
     if (s.lane == 0) {
         N.set_cost(R, Rcost);
         N.set_size(R, Rsize);
@@ -784,14 +857,14 @@ __device__ __forceinline__ bool evict(Sim<HC> &s, int32_t v, int32_t slot, bool 
     const int32_t head = cls(HC) == HC_EQ ? gld(s.t.rec[v].nb + (s.lane & (NB_HEAD - 1))) : 0;
     TRec rv;
     {
-        const i32x4 *P = (const i32x4 *)&s.S.pool(slot);
-        const i32x4 q0 = P[0], q1 = P[1];
+        i32x4 q0, q1;
+        s.S.pool_head(slot, q0, q1);
         rv.size = uni64((int64_t)(((uint64_t)(uint32_t)q1.y << 32) | (uint32_t)q1.x));
         rv.c0 = uni(q1.z);
         rv.adj_b = uni(q1.w);
         rv.adj_e = rv.adj_b + uni(q0.y >> 8);
     }
-    s.S.pool(slot).id = -1;
+    s.S.pool_kill(slot);
     s.pool_live--;
     s.mem -= rv.size;
     if (eager) s.eager++;
@@ -811,8 +884,7 @@ __device__ __forceinline__ bool evict(Sim<HC> &s, int32_t v, int32_t slot, bool 
         NL.p = s.S.nodes.lds_l;
         ok = evict_merge(s, NL, nd, rv, head);
     } else {
-        AnyNodes NA;
-        NA.n = s.S.nodes;
+        const NodeStore &NA = s.S.nodes;
         ok = evict_merge(s, NA, nd, rv, head);
     }
     if (!ok) return false;
@@ -822,79 +894,58 @@ __device__ __forceinline__ bool evict(Sim<HC> &s, int32_t v, int32_t slot, bool 
 
 // ---------------------------------------------------------------- scan --
 
-// Set roots of the neighbours k0 .. k0+LB-1 (below e) of a candidate: r[j] is
-// the root of neighbour k0+j if it is evicted, else -1.  All neighbour and
-// state reads are issued together; the finds then advance in lockstep, with
-// the first hop compressed (every lane writes the same root).  Returns the
-// number of evicted neighbours in the chunk; `bad` is set on a broken forest.
+// This lane's neighbour k0 + lane of [b, e): the root of its set if it is
+// evicted, else -1.  The finds advance in lockstep, with the path's start
+// compressed; `bad` is set on a broken forest.
 template <int HC, class NS>
-__device__ __forceinline__ int32_t chunk_roots(const Sim<HC> &s, const NS &N, int32_t k0, int32_t e, int32_t (&r)[LB],
-                                               bool &bad)
+__device__ __forceinline__ int32_t neighbour_root(const Sim<HC> &s, const NS &N, int32_t k0, int32_t e, bool &bad)
 {
-    int32_t w[LB], q[LB];
-#pragma unroll
-    for (int j = 0; j < LB; j++) w[j] = gld(s.t.adj + (k0 + j < e ? k0 + j : k0));
-#pragma unroll
-    for (int j = 0; j < LB; j++) q[j] = ts_sw(s.S.tst[w[j]]);
-    int32_t cnt = 0;
-#pragma unroll
-    for (int j = 0; j < LB; j++) {
-        const bool v = k0 + j < e && q[j] >= 0;
-        q[j] = v ? q[j] : 0;            // node 0: the null node, its own root
-        r[j] = q[j];
-        cnt += v ? 1 : 0;
-    }
+    const int32_t k = k0 + s.lane;
+    const int32_t q = k < e ? ts_sw(s.S.tst[gld(s.t.adj + k)]) : -1;
+    int32_t r = q >= 0 ? q : 0;         // node 0: the null node, its own root
     for (int32_t it = 0;; it++) {
-        int32_t p[LB];
-        bool more = false;
-#pragma unroll
-        for (int j = 0; j < LB; j++) {
-            p[j] = N.parent(r[j]);
-            more |= p[j] != r[j];
-        }
-        if (!more) break;
+        const int32_t p = N.parent(r);
+        if (!ballot(p != r)) break;
         if (it > s.uf_n) { bad = true; break; }
-#pragma unroll
-        for (int j = 0; j < LB; j++) r[j] = p[j];
+        r = p;
     }
-#pragma unroll
-    for (int j = 0; j < LB; j++) {
-        if (q[j] != 0 && r[j] != q[j]) N.set_parent(q[j], r[j]);
-        r[j] = q[j] != 0 ? r[j] : -1;
-    }
-    return cnt;
+    if (q >= 0 && r != q) N.set_parent(q, r);
+    return q >= 0 ? r : -1;
 }
 
-// Neighbourhood cost under h_DTR^eq from the full adjacency [b, e) (used when
-// the candidate's cache overflowed or a cached node sits deep in its set):
-// summed running costs of the distinct sets of its evicted neighbours.  A
-// set counts at its first neighbour; chunks after the first compare against
-// the roots of the chunks before them.
+// Neighbourhood cost under h_DTR^eq from the full adjacency [b, e) (uniform;
+// used when a candidate's cache overflowed or a cached node sits deep in its
+// set): summed running costs of the distinct sets of its evicted neighbours,
+// 64 neighbours at a time by the whole wavefront.  A set counts at its first
+// neighbour; chunks after the first compare against the roots of the chunks
+// before them.  (A lane of its own took two dependent reads and a find per 8
+// neighbours, and as many again per pair of such chunks: 174,000 cycles a scan
+// of the transformer's pools, whose attention inputs have some 40 neighbours.)
 template <int HC, class NS>
 __device__ __forceinline__ int64_t eq_cost_full(const Sim<HC> &s, const NS &N, int32_t b, int32_t e, int64_t &ev_count,
                                                 bool &bad)
 {
-    int64_t sum = 0, cnt = 0;
-    for (int32_t k0 = b; k0 < e; k0 += LB) {
-        int32_t r[LB];
-        cnt += chunk_roots(s, N, k0, e, r, bad);
-        bool keep[LB];
-#pragma unroll
-        for (int j = 0; j < LB; j++) {
-            keep[j] = r[j] >= 0;
-#pragma unroll
-            for (int i = 0; i < j; i++) keep[j] = keep[j] && r[i] != r[j];
+    int64_t sum = 0;
+    int32_t cnt = 0;
+    for (int32_t k0 = b; k0 < e; k0 += WAVE) {
+        const int32_t r = neighbour_root(s, N, k0, e, bad);
+        const int64_t cost = N.cost(r >= 0 ? r : 0);
+        uint64_t m = ballot(r >= 0);
+        cnt += __popcll(m);
+        for (int32_t p0 = b; p0 < k0 && m; p0 += WAVE) {
+            const int32_t rp = neighbour_root(s, N, p0, e, bad);
+            for (uint64_t q = m; q;) {
+                const int32_t rj = __builtin_amdgcn_readlane(r, __builtin_ctzll(q));
+                const uint64_t same = ballot(r == rj);
+                if (ballot(rp == rj)) m &= ~same;
+                q &= ~same;
+            }
         }
-        for (int32_t p0 = b; p0 < k0; p0 += LB) {
-            int32_t rp[LB];
-            chunk_roots(s, N, p0, e, rp, bad);
-#pragma unroll
-            for (int j = 0; j < LB; j++)
-#pragma unroll
-                for (int i = 0; i < LB; i++) keep[j] = keep[j] && rp[i] != r[j];
+        while (m) {
+            const int32_t j = __builtin_ctzll(m);
+            sum += (int64_t)readlane64((uint64_t)cost, j);
+            m &= ~ballot(r == __builtin_amdgcn_readlane(r, j));
         }
-#pragma unroll
-        for (int j = 0; j < LB; j++) sum += keep[j] ? N.cost(r[j]) : 0;
     }
     ev_count = cnt;
     return sum;
@@ -944,7 +995,7 @@ __device__ __forceinline__ void take(Best &b, bool valid, float sc, uint64_t N, 
     const bool dec_worse = sc > b.hi;
     bool t = valid && (!b.have || dec_better);
     const bool close = valid && b.have && !dec_better && !dec_worse;
-    if (__ballot(close)) {
+    if (ballot(close)) {
         if (close) t = better_exact(N, da, db, id, b.N, b.da, b.db, b.id);
     }
     b.sc = t ? sc : b.sc;
@@ -986,8 +1037,8 @@ __device__ __forceinline__ Filter make_filter(Sim<HC> &s)
     if (s.search & SEARCH_IGNORE_SMALL) {
         uint64_t sum = 0;
         for (int32_t i = s.lane; i < s.pool_end; i += WAVE) {
-            const i32x4 *P = (const i32x4 *)&s.S.pool(i);
-            const i32x4 q0 = P[0], q1 = P[1];
+            i32x4 q0, q1;
+            s.S.pool_head(i, q0, q1);
             if (q0.x >= 0) sum += ((uint64_t)(uint32_t)q1.y << 32) | (uint32_t)q1.x;
         }
         for (int off = WAVE / 2; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, WAVE);
@@ -1103,7 +1154,7 @@ __device__ void walk_lanes(const TraceDev &t, const Slot<HC> &S, Tst<HC> tst, co
     for (int c = 0; c < NB_HEAD; c++) nb[c] = 0;
     for (;;) {
         const bool idle = x < 0;
-        const uint64_t mi = __ballot(idle);
+        const uint64_t mi = ballot(idle);
         uint32_t i = 0xffffffffu;
         if (mi && !drained) {
             uint32_t b;
@@ -1118,7 +1169,7 @@ __device__ void walk_lanes(const TraceDev &t, const Slot<HC> &S, Tst<HC> tst, co
             }
             if (b + (uint32_t)__popcll(mi) >= (uint32_t)P.end) drained = true;
             if (idle) i = b + (uint32_t)lane_rank(mi);
-        } else if (!__ballot(x >= 0)) {
+        } else if (!ballot(x >= 0)) {
             break;
         }
         if (i < (uint32_t)P.end) {
@@ -1209,7 +1260,7 @@ __device__ void walk_lanes(const TraceDev &t, const Slot<HC> &S, Tst<HC> tst, co
         }
         // the walk ends with the expansion that leaves nothing to expand
         const bool fin = x >= 0 && !over && k >= ke && head == tail;
-        if (__ballot(fin)) {
+        if (ballot(fin)) {
             const uint64_t N = (uint64_t)(c0x + sum);
             const uint64_t DA = P.use_m ? (uint64_t)size : 1;
             const uint64_t DB = P.use_s ? (uint64_t)(P.T - last) : 1;
@@ -1272,7 +1323,7 @@ __device__ int64_t walk_wave(const TraceDev &t, Tst<HC> tst, GAS uint32_t *bv, G
             nb[0] = n0.x; nb[1] = n0.y; nb[2] = n0.z; nb[3] = n0.w;
             nb[4] = n1.x; nb[5] = n1.y; nb[6] = n1.z; nb[7] = n1.w;
         }
-        for (int32_t c0 = 0; __ballot(kb + c0 < ke); c0 += WB) {
+        for (int32_t c0 = 0; ballot(kb + c0 < ke); c0 += WB) {
             int32_t v[WB];
             bool claim[WB];
             uint64_t w[WB];
@@ -1296,7 +1347,7 @@ __device__ int64_t walk_wave(const TraceDev &t, Tst<HC> tst, GAS uint32_t *bv, G
             }
 #pragma unroll
             for (int j = 0; j < WB; j++) {
-                const uint64_t m = __ballot(claim[j]);
+                const uint64_t m = ballot(claim[j]);
                 if (claim[j]) {
                     const int32_t s2 = side >= 0 ? side : (kb + c0 + j < np ? 0 : 1);
                     bq[tail + lane_rank(m)] = v[j] | (s2 << 31);
@@ -1347,8 +1398,8 @@ __device__ void walk_listed(const TraceDev &t, const Slot<HC> &S, Tst<HC> tst, c
         }
         if (k >= n_ovf) break;
         const int32_t sl = uni(gld(S.ovf + k));
-        const i32x4 *PS = (const i32x4 *)&S.pool(sl);
-        const i32x4 q0 = PS[0], q1 = PS[1];
+        i32x4 q0, q1;
+        S.pool_head(sl, q0, q1);
         const int32_t x = uni(q0.x);
         const int64_t last = uni64((int64_t)(((uint64_t)(uint32_t)q0.w << 32) | (uint32_t)q0.z));
         const int64_t size = uni64((int64_t)(((uint64_t)(uint32_t)q1.y << 32) | (uint32_t)q1.x));
@@ -1459,7 +1510,7 @@ __device__ uint64_t sweep_side(const Sweep &W, bool up, int32_t lane, bool has, 
         sweep_chunk(m0, m1, s0, s1, c0, sum, cnt);
         // neighbours in other chunks
         const int32_t nx = (m0 | m1) ? (up ? (int32_t)(R.info.z & 0xFFFF) : (int32_t)(R.info.z >> 16)) : 0;
-        if (__ballot(nx > 0)) {
+        if (ballot(nx > 0)) {
             const uint64_t Mi = (uint64_t)m0 | ((uint64_t)m1 << 32);
             const uint64_t hd = up ? R.hp : R.hc;
             const LAS uint32_t *EW = (const LAS uint32_t *)W.ev;
@@ -1476,7 +1527,7 @@ __device__ uint64_t sweep_side(const Sweep &W, bool up, int32_t lane, bool has, 
                     __hip_atomic_fetch_or(W.M + p[j], Mi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                     to |= ONE << (p[j] >> 6);
                 }
-            for (int32_t j = SWEEP_HEAD; __ballot(j < nx); j++) {
+            for (int32_t j = SWEEP_HEAD; ballot(j < nx); j++) {
                 if (j >= nx) continue;
                 const uint32_t pj = gld(W.sx + R.info.y + (up ? 0 : (int32_t)(R.info.z & 0xFFFF)) + j);
                 if ((EW[pj >> 5] >> (pj & 31)) & 1) {
@@ -1518,9 +1569,9 @@ __device__ __forceinline__ int32_t sweep_list(const Sim<HC> &s, const Sweep &W)
         for (int j = 0; j < B; j++) {
             const int32_t o = (c0 + j) * WAVE + s.lane;
             if ((c0 + j) * WAVE >= F) break;
-            const uint64_t ev = __ballot(o < F && ts_sw(w[j]) >= 0);
+            const uint64_t ev = ballot(o < F && ts_sw(w[j]) >= 0);
             const bool in = o < F && ts_in_pool(w[j]);
-            const uint64_t m = __ballot(in);
+            const uint64_t m = ballot(in);
             if (s.lane == 0) W.ev[c0 + j] = ev;
             if (in) W.list[n + lane_rank(m)] = ts_pos(w[j]) << SWEEP_POS_SHIFT | (uint32_t)o;
             n += __popcll(m);
@@ -1550,13 +1601,7 @@ __device__ void sweep_groups(const Slot<HC> &S, const Sweep &W, const WalkParams
         const uint32_t e = W.list[has ? k : 0];
         slot = (int32_t)(e >> SWEEP_POS_SHIFT);
         i32x4 q0, q1;
-        if (slot < POOL_LDS) {
-            const LAS i32x4 *PS = (const LAS i32x4 *)S.lpool_l + PQL * slot;
-            q0 = PS[0]; q1 = PS[1];
-        } else {
-            const GAS i32x4 *PS = (const GAS i32x4 *)S.gpool + PQ * (size_t)slot;
-            q0 = PS[0]; q1 = PS[1];
-        }
+        S.pool_head(slot, q0, q1);
         id = q0.x;
         deg = q0.y >> 8;
         last = (int64_t)(((uint64_t)(uint32_t)q0.w << 32) | (uint32_t)q0.z);
@@ -1601,10 +1646,9 @@ __device__ void sweep_groups(const Slot<HC> &S, const Sweep &W, const WalkParams
 __device__ WaveBest wave_best(const Best &best)
 {
     WaveBest r;
-    float mn = best.have ? best.sc : __builtin_inff();
-    for (int off = WAVE / 2; off >= 1; off >>= 1) mn = fminf(mn, __shfl_xor(mn, off, WAVE));
+    const float mn = wave_min(best.have ? best.sc : __builtin_inff());
     const float thr = mn * FILTER_HI;
-    uint64_t m = __ballot(best.have && !(best.sc > thr));     // NaN estimates stay in
+    uint64_t m = ballot(best.have && !(best.sc > thr));     // NaN estimates stay in
     r.have = m ? 1 : 0;
     r.N = 0;
     r.da = r.db = 1;
@@ -1725,7 +1769,7 @@ __device__ void walk_scan(Sim<HC> &s, const Filter &F, Best &best, int64_t &scor
         const bool h = w >= 1 && C->res[w].have;
         const uint64_t N = h ? C->res[w].N : 0, da = h ? C->res[w].da : 1, db = h ? C->res[w].db : 1;
         const int32_t id = h ? C->res[w].id : 0, sl = h ? C->res[w].slot : 0;
-        if (__ballot(h)) take(best, h, h ? score_est(N, da, db) : 0.0f, N, da, db, id, sl);
+        if (ballot(h)) take(best, h, h ? score_est(N, da, db) : 0.0f, N, da, db, id, sl);
         if (w >= 1) {
             nbr += C->res[w].nbr;
             adj += C->res[w].adj;
@@ -1887,19 +1931,22 @@ __device__ __forceinline__ void scan_rounds(Sim<HC> &s, const Filter &F, Best &b
                 // wave allows it
                 if (lds_nodes) {
                     const LAS UfNode *NL = s.S.nodes.lds_l;
-                    if (!__ballot(c > 2)) sum[u] = cached_sum<2>(NL, nb[u], deep);
-                    else if (!__ballot(c > 4)) sum[u] = cached_sum<4>(NL, nb[u], deep);
+                    if (!ballot(c > 2)) sum[u] = cached_sum<2>(NL, nb[u], deep);
+                    else if (!ballot(c > 4)) sum[u] = cached_sum<4>(NL, nb[u], deep);
                     else sum[u] = cached_sum<K>(NL, nb[u], deep);
                 } else {
                     int32_t r[K];
                     int64_t cost[K];
 #pragma unroll
-                    for (int k = 0; k < K; k++) r[k] = s.S.nodes[nb[u][k]].parent;
+                    for (int k = 0; k < K; k++) r[k] = s.S.nodes.parent(nb[u][k]);
 #pragma unroll
                     for (int k = 0; k < K; k++) {
-                        const UfNode n2 = s.S.nodes[r[k]];
-                        cost[k] = n2.cost;
-                        deep |= n2.parent != r[k];
+                        int32_t up;
+                        s.S.nodes.at(r[k], [&](auto *n2) {
+                            cost[k] = n2->cost;
+                            up = n2->parent;
+                        });
+                        deep |= up != r[k];
                     }
                     int64_t t = 0;
 #pragma unroll
@@ -1927,20 +1974,24 @@ __device__ __forceinline__ void scan_rounds(Sim<HC> &s, const Filter &F, Best &b
                 for (int u = 0; u < U; u++) s.prof_global_nodes += ok[u] && (pd[u] & 0xFF) > K ? 1 : 0;
             }
 #endif
-            if (__ballot(any_slow)) {
-                if (lds_nodes) {
-                    LdsNodes NL;
-                    NL.p = s.S.nodes.lds_l;
+            if (ballot(any_slow)) {
 #pragma unroll
-                    for (int u = 0; u < U; u++)
-                        if (slow[u]) sum[u] = eq_cost_full(s, NL, ab[u], ab[u] + (pd[u] >> 8), ev[u], bad);
-                } else {
-                    AnyNodes NA;
-                    NA.n = s.S.nodes;
-#pragma unroll
-                    for (int u = 0; u < U; u++)
-                        if (slow[u]) sum[u] = eq_cost_full(s, NA, ab[u], ab[u] + (pd[u] >> 8), ev[u], bad);
-                }
+                for (int u = 0; u < U; u++)
+                    for (uint64_t m = ballot(slow[u]); m; m &= m - 1) {
+                        const int32_t j = __builtin_ctzll(m);
+                        const int32_t jb = __builtin_amdgcn_readlane(ab[u], j);
+                        const int32_t je = jb + (__builtin_amdgcn_readlane(pd[u], j) >> 8);
+                        int64_t sj, ej;
+                        if (lds_nodes) {
+                            LdsNodes NL;
+                            NL.p = s.S.nodes.lds_l;
+                            sj = eq_cost_full(s, NL, jb, je, ej, bad);
+                        } else {
+                            sj = eq_cost_full(s, s.S.nodes, jb, je, ej, bad);
+                        }
+                        sum[u] = lane == j ? sj : sum[u];
+                        ev[u] = lane == j ? ej : ev[u];
+                    }
             }
 #pragma unroll
             for (int u = 0; u < U; u++) {
@@ -1967,7 +2018,7 @@ __device__ __forceinline__ void scan_rounds(Sim<HC> &s, const Filter &F, Best &b
 #pragma unroll
         for (int u = 0; u < U; u++) {
             take(best, ok[u], score_est(N[u], DA[u], DB[u]), N[u], DA[u], DB[u], id[u], (int32_t)slot[u]);
-            if (approx(HC)) scored += __popcll(__ballot(ok[u]));
+            if (approx(HC)) scored += __popcll(ballot(ok[u]));
         }
     }
 }
@@ -1985,13 +2036,12 @@ __device__ __forceinline__ int32_t scan(Sim<HC> &s, int32_t &victim_slot, const 
     best.have = 0;
     if constexpr (cls(HC) == HC_WALK) walk_scan<HC>(s, F, best, scored);
     else scan_rounds<HC>(s, F, best, scored, bad);
-    if (__ballot(bad)) { set_status(s, ST_CAPACITY); return -1; }
+    if (ballot(bad)) { set_status(s, ST_CAPACITY); return -1; }
     // cross-lane minimum: the smallest estimate bounds the winner; only the
     // lanes within the filter margin of it (usually one) are compared exactly
-    float mn = best.have ? best.sc : __builtin_inff();
-    for (int off = WAVE / 2; off >= 1; off >>= 1) mn = fminf(mn, __shfl_xor(mn, off, WAVE));
+    const float mn = wave_min(best.have ? best.sc : __builtin_inff());
     const float thr = mn * FILTER_HI;
-    uint64_t m = __ballot(best.have && !(best.sc > thr));     // NaN estimates stay in
+    uint64_t m = ballot(best.have && !(best.sc > thr));     // NaN estimates stay in
     if (!m) return -1;
     int32_t j = __ffsll((long long)m) - 1;
     m &= m - 1;
@@ -2084,7 +2134,7 @@ __device__ __forceinline__ void lock_inputs(Sim<HC> &s, const int32_t *ids, int3
             if (l + 1 == LOCKS_SAT) s.S.lockx[u] = (int32_t)LOCKS_SAT;
             else if (l == LOCKS_SAT) s.S.lockx[u] = s.S.lockx[u] + 1;
             if (ts_in_pool(w)) {
-                s.S.pool((int32_t)ts_pos(w)).id = -1;
+                s.S.pool_kill((int32_t)ts_pos(w));
                 killed = true;
             }
             s.S.tst[u] = nw;
@@ -2093,7 +2143,7 @@ __device__ __forceinline__ void lock_inputs(Sim<HC> &s, const int32_t *ids, int3
             f.u = u;
             f.w = nw;
         }
-        s.pool_live -= __popcll(__ballot(killed));
+        s.pool_live -= __popcll(ballot(killed));
     }
 }
 
@@ -2148,13 +2198,13 @@ template <int HC>
 __device__ __forceinline__ int32_t next_evicted(const Sim<HC> &s, int32_t b, int32_t e, int32_t from, const Frame &f)
 {
     const bool ev0 = s.lane >= from && b + s.lane < e && ts_sw(f.w) >= 0;
-    const uint64_t m0 = __ballot(ev0);
+    const uint64_t m0 = ballot(ev0);
     if (m0) return __ffsll((long long)m0) - 1;
     for (int32_t k0 = b + WAVE; k0 < e; k0 += WAVE) {
         const int32_t k = k0 + s.lane;
         bool ev = false;
         if (k < e && k - b >= from) ev = ts_sw(s.S.tst[gld(s.t.in + k)]) >= 0;
-        const uint64_t m = __ballot(ev);
+        const uint64_t m = ballot(ev);
         if (m) return k0 - b + __ffsll((long long)m) - 1;
     }
     return e - b;
@@ -2185,8 +2235,7 @@ __device__ __forceinline__ bool execute(Sim<HC> &s, int32_t t, const TRec &rt, b
             const int32_t r = find_compress(s, NL, old);
             NL.set_cost(r, uni64(NL.cost(r)) - c);
         } else {
-            AnyNodes NA;
-            NA.n = s.S.nodes;
+            const NodeStore &NA = s.S.nodes;
             const int32_t r = find_compress(s, NA, old);
             NA.set_cost(r, uni64(NA.cost(r)) - c);
         }
@@ -2198,7 +2247,7 @@ __device__ __forceinline__ bool execute(Sim<HC> &s, int32_t t, const TRec &rt, b
                 if (ts_in_pool(wx) && !list_remove(s, (int32_t)ts_pos(wx), old)) lost = true;
             }
         }
-        if (__ballot(lost)) set_status(s, ST_CAPACITY);
+        if (ballot(lost)) set_status(s, ST_CAPACITY);
     }
     s.S.tst[t] = ts_make(S_RESIDENT, 0, locks);
     if (s.T >= CLOCK_LIMIT) { set_status(s, ST_CLOCK); return false; }
@@ -2219,7 +2268,7 @@ __device__ __forceinline__ void try_banish(Sim<HC> &s, int32_t t)
     for (int32_t k0 = b; k0 < e && !blocked; k0 += WAVE) {
         const int32_t k = k0 + s.lane;
         const bool ev = k < e && ts_sw(s.S.tst[gld(s.t.ch + k)]) >= 0;
-        blocked = __ballot(ev) != 0;
+        blocked = ballot(ev) != 0;
     }
     if (blocked) {
         if (s.lane == 0) s.S.pending[t] = 1;
@@ -2229,7 +2278,7 @@ __device__ __forceinline__ void try_banish(Sim<HC> &s, int32_t t)
     const int32_t sw = ts_sw(w);
     if (sw == S_RESIDENT || sw == S_PINNED || sw == S_CONST) s.mem -= rec_u(s, t).size;
     if (ts_in_pool(w)) {
-        if (s.lane == 0) s.S.pool((int32_t)ts_pos(w)).id = -1;
+        if (s.lane == 0) s.S.pool_kill((int32_t)ts_pos(w));
         s.pool_live--;
     }
     s.S.tst[t] = ts_make(S_BANISHED, 0, 0);
@@ -2242,11 +2291,11 @@ __device__ __forceinline__ void try_banish(Sim<HC> &s, int32_t t)
             const uint64_t wc = s.S.tst[c];
             if (ts_sw(wc) == S_RESIDENT) {
                 killed = ts_in_pool(wc);
-                if (killed) s.S.pool((int32_t)ts_pos(wc)).id = -1;
+                if (killed) s.S.pool_kill((int32_t)ts_pos(wc));
                 s.S.tst[c] = ts_make(S_PINNED, ts_pos(wc), ts_locks(wc));
             }
         }
-        s.pool_live -= __popcll(__ballot(killed));
+        s.pool_live -= __popcll(ballot(killed));
     }
 }
 
@@ -2264,7 +2313,7 @@ __device__ __forceinline__ void retry_banish(Sim<HC> &s, int32_t b, int32_t e)
             p = gld(s.t.in + k);
             pend = s.S.pending[p] != 0;
         }
-        uint64_t m = __ballot(pend);
+        uint64_t m = ballot(pend);
         while (m) {
             const int32_t j = __ffsll((long long)m) - 1;
             m &= m - 1;
@@ -2273,8 +2322,6 @@ __device__ __forceinline__ void retry_banish(Sim<HC> &s, int32_t b, int32_t e)
     }
 }
 
-__device__ __forceinline__ GAS int32_t *words(GAS i32x4 *p) { return (GAS int32_t *)p; }
-__device__ __forceinline__ LAS int32_t *words(LAS i32x4 *p) { return (LAS int32_t *)p; }
 constexpr int FQ = (int)(sizeof(StackFrame) / 16);    // 16-byte quads per stack frame
 
 // push the current frame (tensor t, next input to check, its record); lane k
@@ -2424,7 +2471,7 @@ __device__ __forceinline__ bool release(Sim<HC> &s, int32_t o)
             ev = ts_in_pool(w);
             pos = (int32_t)ts_pos(w);
         }
-        uint64_t m = __ballot(ev);
+        uint64_t m = ballot(ev);
         while (m) {
             const int32_t j = __ffsll((long long)m) - 1;
             m &= m - 1;
@@ -2492,11 +2539,9 @@ __device__ __forceinline__ void run_sim(const KernelArgs &a, int32_t sim, const 
     if (cls(HC) != HC_EQ && s.policy == POLICY_BANISH)
         for (int32_t x = lane; x < n; x += WAVE) s.S.pending[x] = 0;
     if (cls(HC) == HC_EQ && lane == 0) {
-        UfNode z;
-        z.cost = 0;
-        z.parent = 0;
-        z.size = 1;
-        s.S.nodes[0] = z;
+        s.S.nodes.set_cost(0, 0);
+        s.S.nodes.set_parent(0, 0);
+        s.S.nodes.set_size(0, 1);
     }
     slot_sync<HC>();
     s.mem = s.t.const_mem;
@@ -2585,9 +2630,7 @@ __device__ __forceinline__ void eq_waves(const KernelArgs &a, UfNode *lds_nodes,
     const int32_t slot = (int32_t)blockIdx.x * lds_waves(HC) + wave;
     if (slot >= a.n_slots) return;
     Slot<HC> S = slot_at<HC>(a, slot, lds_small + wave * small_lds_bytes(a.small_n));
-    S.nodes.lds = lds_nodes + wave * UF_LDS;
     S.nodes.lds_l = (LAS UfNode *)lds_nodes + wave * UF_LDS;
-    S.lpool = lds_pool + wave * POOL_LDS;
     S.lpool_l = (LAS PoolSlotL *)lds_pool + wave * POOL_LDS;
     for (;;) {
         uint32_t k = 0;
@@ -2624,9 +2667,7 @@ __global__ void __launch_bounds__(cls(HC) == HC_WALK ? MAX_WALK_WAVES * WAVE : l
     }
     const int32_t nw = cls(HC) == HC_WALK ? (int32_t)a.L.walk_waves : 1;
     Slot<HC> S = slot_at<HC>(a, blockIdx.x, (LAS uint8_t *)lds_dyn + (cls(HC) == HC_WALK ? sweep_lds_bytes(a.sweep_chunks, nw) : 0));
-    S.nodes.lds = lds_nodes;
     S.nodes.lds_l = (LAS UfNode *)lds_nodes;
-    S.lpool = lds_pool;
     S.lpool_l = (LAS PoolSlotL *)lds_pool;
     LAS WalkCtl *ctl = (LAS WalkCtl *)lds_nodes;
     if constexpr (cls(HC) == HC_WALK) {

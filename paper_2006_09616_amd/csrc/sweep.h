@@ -8,6 +8,9 @@
 
 namespace dtr {
 
+// the lanes whose predicate holds (straight from the compare's mask)
+__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+
 // a wave-uniform lane mask as this lane's predicate
 __device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
@@ -34,7 +37,7 @@ __device__ __forceinline__ void sweep_chunk(uint32_t &m0, uint32_t &m1, uint32_t
     constexpr int STEP = 8;
 #pragma unroll
     for (int st = 0; st < WAVE / STEP; st++) {
-        const uint64_t act = __ballot((m0 | m1) != 0);
+        const uint64_t act = ballot((m0 | m1) != 0);
         if (!((act >> (STEP * st)) & ((1u << STEP) - 1))) continue;
         uint32_t part = 0;           // eight costs below 2^28 each
 #pragma unroll
@@ -56,7 +59,7 @@ __device__ __forceinline__ void sweep_chunk(uint32_t &m0, uint32_t &m1, uint32_t
 // all lanes' bits joined into pend (uniform)
 __device__ __forceinline__ void join_masks(uint64_t &pend, uint64_t to)
 {
-    for (uint64_t q; (q = __ballot(to != 0));) {
+    for (uint64_t q; (q = ballot(to != 0));) {
         const int32_t j = __builtin_ctzll(q);
         const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)to, j);
         const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(to >> 32), j);
