@@ -592,7 +592,9 @@ __device__ __forceinline__ void pool_compact(Sim<HC> &s)
 
 // Every lane with `want` appends tensor x (resident, unlocked) with last
 // access `last`; returns its slot (or -1).  The caller stores x's new state.
-// `known`: x's record when the caller holds it already (uniform x).
+// `known`: x's record when the caller holds it already: x (uniform) is then the
+// output of a trace operation's first run, none of whose neighbours is evicted
+// (its inputs are resident, its children not computed).
 template <int HC>
 __device__ __forceinline__ int32_t pool_append(Sim<HC> &s, bool want, int32_t x, int64_t last, const TRec *known = nullptr)
 {
@@ -608,7 +610,7 @@ __device__ __forceinline__ int32_t pool_append(Sim<HC> &s, bool want, int32_t x,
     i32x4 hd[2] = {};
     if (want) {
         const GAS i32x4 *px = (const GAS i32x4 *)&s.t.rec[x];
-        if (cls(HC) != HC_SIMPLE) {
+        if (cls(HC) == HC_WALK || (cls(HC) == HC_EQ && !known)) {
             hd[0] = px[2];
             hd[1] = px[3];
         }
@@ -617,7 +619,14 @@ __device__ __forceinline__ int32_t pool_append(Sim<HC> &s, bool want, int32_t x,
     // walk heuristics: the low byte holds the parent count (255: read the record)
     int32_t deg = (r.adj_e - r.adj_b) << 8 | (cls(HC) == HC_WALK ? min(r.in_e - r.in_b, 255) : 0);
     NbCache nb;
-    if (cls(HC) == HC_EQ) nb = list_build(s, r.adj_b, r.adj_e, deg, hd);
+    if (cls(HC) == HC_EQ) {
+        if (known) {
+#pragma unroll
+            for (int k = 0; k < KQ; k++) nb.q[k] = 0;
+        } else {
+            nb = list_build(s, r.adj_b, r.adj_e, deg, hd);
+        }
+    }
     int32_t i = -1;
     if (want) {
         i = s.pool_end + lane_rank(m);
