@@ -162,6 +162,37 @@ __device__ __forceinline__ float wave_min(float x)
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), WAVE - 1));
 }
 
+// x summed over the lanes (uniform), as wave_min
+__device__ __forceinline__ uint64_t wave_add(uint64_t x)
+{
+    auto step = [&](auto ctrl, auto rows) {
+        const int lo = (int)(uint32_t)x, hi = (int)(uint32_t)(x >> 32);
+        const uint32_t a = (uint32_t)__builtin_amdgcn_update_dpp(0, lo, ctrl.value, rows.value, 0xF, false);
+        const uint32_t b = (uint32_t)__builtin_amdgcn_update_dpp(0, hi, ctrl.value, rows.value, 0xF, false);
+        x += (uint64_t)a | ((uint64_t)b << 32);
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>(), integral_constant<int, 0xF>());
+    step(integral_constant<int, 0x112>(), integral_constant<int, 0xF>());
+    step(integral_constant<int, 0x114>(), integral_constant<int, 0xF>());
+    step(integral_constant<int, 0x118>(), integral_constant<int, 0xF>());
+    step(integral_constant<int, 0x142>(), integral_constant<int, 0xA>());
+    step(integral_constant<int, 0x143>(), integral_constant<int, 0xC>());
+    return readlane64(x, WAVE - 1);
+}
+
+// floor(a / d) for a < 2^62 with a quotient below 2^36: the quotient in double
+// precision is off by at most one (relative error below 2^-51), which the
+// exact remainder shows; a 64-bit division takes several times as long.
+__device__ __forceinline__ uint64_t div_small(uint64_t a, uint32_t d)
+{
+    uint64_t q = (uint64_t)((double)a / (double)d);
+    const int64_t r = (int64_t)(a - q * d);
+    if (r < 0) q--;
+    else if (r >= (int64_t)d) q++;
+    return q;
+}
+
 // a strictly better (lower score) than b; ties go to the smaller id
 __device__ __forceinline__ bool better(uint64_t na, u128 da, int32_t ia, uint64_t nb, u128 db, int32_t ib)
 {
@@ -316,12 +347,28 @@ struct Sim {
     int64_t evict_no;
     int64_t total, base, remat_cost, executed, remats, evictions, eager, scores;
     int64_t nbr, adj;     // per-lane partial sums, reduced at the end
+    uint64_t pool_size;   // per-lane partial sums of the pool's sizes (SEARCH_IGNORE_SMALL), kept as tensors come
+                          // and go: summing the pool at every decision took 4,800 cycles at 430 candidates
 #ifdef DTR_PROFILE
     int64_t prof_scan_cycles, prof_scans, prof_rounds;
     int64_t prof_slow, prof_global_nodes, prof_uf_compact, prof_pool_compact;
     int64_t prof_ph[PROF_PHASES];
 #endif
 };
+
+// slot i's tensor leaves the pool (called by the lane, or lanes, it concerns)
+template <int HC>
+__device__ __forceinline__ void pool_leave(Sim<HC> &s, int32_t i)
+{
+    uint64_t size = 0;
+    s.S.pool(i, [&](auto *Q) {
+        auto *w = words(Q);
+        if (approx(HC) && (s.search & SEARCH_IGNORE_SMALL))
+            size = (uint64_t)(uint32_t)w[4] | ((uint64_t)(uint32_t)w[5] << 32);
+        w[0] = -1;
+    });
+    if (approx(HC)) s.pool_size -= size;
+}
 
 // phase timers (DTR_PROFILE builds only)
 #ifdef DTR_PROFILE
@@ -647,6 +694,7 @@ __device__ __forceinline__ int32_t pool_append(Sim<HC> &s, bool want, int32_t x,
             for (int k = 0; k < KQ; k++)
                 if (cls(HC) != HC_SIMPLE) Q[2 + k] = cls(HC) == HC_EQ ? nb.q[k] : hd[k];
         });
+        if (approx(HC)) s.pool_size += (uint64_t)r.size;
     }
     s.pool_end += cnt;
     s.pool_live += cnt;
@@ -874,6 +922,7 @@ __device__ __forceinline__ bool evict(Sim<HC> &s, int32_t v, int32_t slot, bool 
         rv.adj_e = rv.adj_b + uni(q0.y >> 8);
     }
     s.S.pool_kill(slot);
+    if (approx(HC) && s.lane == 0) s.pool_size -= (uint64_t)rv.size;
     s.pool_live--;
     s.mem -= rv.size;
     if (eager) s.eager++;
@@ -1044,16 +1093,9 @@ __device__ __forceinline__ Filter make_filter(Sim<HC> &s)
     const uint32_t n0 = (uint32_t)s.pool_live;
     F.min_size = 0;
     if (s.search & SEARCH_IGNORE_SMALL) {
-        uint64_t sum = 0;
-        for (int32_t i = s.lane; i < s.pool_end; i += WAVE) {
-            i32x4 q0, q1;
-            s.S.pool_head(i, q0, q1);
-            if (q0.x >= 0) sum += ((uint64_t)(uint32_t)q1.y << 32) | (uint32_t)q1.x;
-        }
-        for (int off = WAVE / 2; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, WAVE);
-        sum = (uint64_t)uni64((int64_t)sum);
-        const uint64_t d = 100 * (uint64_t)n0;
-        F.min_size = (sum + d - 1) / d;
+        const uint64_t sum = wave_add(s.pool_size);
+        const uint32_t d = 100 * n0;                      // n0 < 2^24
+        F.min_size = div_small(sum + d - 1, d);           // below 2^36 / 100 + 1
     }
     F.sample = false;
     F.tau = 0;
@@ -1064,8 +1106,8 @@ __device__ __forceinline__ Filter make_filter(Sim<HC> &s)
         if (k < n0) {
             // tau = floor(k 2^64 / n0) by long division in two 32-bit digits
             const uint64_t a = (uint64_t)k << 32;
-            const uint64_t q1 = a / n0, r1 = a % n0;
-            const uint64_t q2 = (r1 << 32) / n0;
+            const uint64_t q1 = div_small(a, n0), r1 = a - q1 * n0;
+            const uint64_t q2 = div_small(r1 << 32, n0);
             F.tau = (q1 << 32) + q2;
             F.sample = true;
         }
@@ -1681,11 +1723,7 @@ __device__ WaveBest wave_best(const Best &best)
     return r;
 }
 
-__device__ __forceinline__ int64_t wave_sum(int64_t v)
-{
-    for (int off = WAVE / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, WAVE);
-    return uni64(v);
-}
+__device__ __forceinline__ int64_t wave_sum(int64_t v) { return (int64_t)wave_add((uint64_t)v); }
 
 // The walk scan of the simulating wavefront.  Helper wavefronts (if any) are
 // given the scan's parameters at a workgroup barrier; all wavefronts walk
@@ -2143,7 +2181,7 @@ __device__ __forceinline__ void lock_inputs(Sim<HC> &s, const int32_t *ids, int3
             if (l + 1 == LOCKS_SAT) s.S.lockx[u] = (int32_t)LOCKS_SAT;
             else if (l == LOCKS_SAT) s.S.lockx[u] = s.S.lockx[u] + 1;
             if (ts_in_pool(w)) {
-                s.S.pool_kill((int32_t)ts_pos(w));
+                pool_leave(s, (int32_t)ts_pos(w));
                 killed = true;
             }
             s.S.tst[u] = nw;
@@ -2287,7 +2325,7 @@ __device__ __forceinline__ void try_banish(Sim<HC> &s, int32_t t)
     const int32_t sw = ts_sw(w);
     if (sw == S_RESIDENT || sw == S_PINNED || sw == S_CONST) s.mem -= rec_u(s, t).size;
     if (ts_in_pool(w)) {
-        if (s.lane == 0) s.S.pool_kill((int32_t)ts_pos(w));
+        if (s.lane == 0) pool_leave(s, (int32_t)ts_pos(w));
         s.pool_live--;
     }
     s.S.tst[t] = ts_make(S_BANISHED, 0, 0);
@@ -2300,7 +2338,7 @@ __device__ __forceinline__ void try_banish(Sim<HC> &s, int32_t t)
             const uint64_t wc = s.S.tst[c];
             if (ts_sw(wc) == S_RESIDENT) {
                 killed = ts_in_pool(wc);
-                if (killed) s.S.pool_kill((int32_t)ts_pos(wc));
+                if (killed) pool_leave(s, (int32_t)ts_pos(wc));
                 s.S.tst[c] = ts_make(S_PINNED, ts_pos(wc), ts_locks(wc));
             }
         }
@@ -2535,6 +2573,7 @@ __device__ __forceinline__ void run_sim(const KernelArgs &a, int32_t sim, const 
     s.evict_no = 0;
     s.total = s.base = s.remat_cost = s.executed = s.remats = s.evictions = s.eager = s.scores = 0;
     s.nbr = s.adj = 0;
+    s.pool_size = 0;
 #ifdef DTR_PROFILE
     const int64_t t_start = (int64_t)__builtin_readcyclecounter();
     s.prof_scan_cycles = s.prof_scans = s.prof_rounds = 0;
