@@ -52,6 +52,7 @@ struct Lowered {
     std::vector<uint8_t> s_const;
     std::vector<int32_t> par_off, par, ch_off, ch, dt_off, dt;
     std::vector<int32_t> born_off, born;   // per operator: edges its first run creates (parent, storage)
+    int32_t sweep = 0;                     // LogProgDev::sweep
     // tensors
     std::vector<int32_t> t_storage, t_op;
     std::vector<uint8_t> t_alias;
@@ -376,6 +377,10 @@ private:
                 }
                 L.born_off[o + 1] = (int32_t)(L.born.size() / 2);
             }
+            // walks are swept in id order when every edge goes upwards (views
+            // that read storages younger than their own can close cycles)
+            L.sweep = S <= dtr::SWEEP_STORAGES;
+            for (size_t z = 0; z + 1 < L.born.size(); z += 2) L.sweep &= L.born[z] < L.born[z + 1];
             csr(S, pk, pv, L.par_off, L.par);       // a stable fill keeps creation order
             csr(S, ck, cv, L.ch_off, L.ch);
         }
@@ -418,6 +423,7 @@ struct LogPlan {
     dtr::LogSlotLayout L{};
     int32_t n_slots = 1;
     int32_t lds_bytes = 0, lds_state = 0, lds_wm = 0, lds_po = 0, lds_co = 0, lds_pa = 0, lds_ca = 0, wm_words = 0;
+    int32_t lds_ev = 0, lds_rows = 0;
     int32_t lds_c0 = 0, lds_cand = 0, lds_stk = 0, lds_ctr = 0, lds_sz = 0, lds_last = 0, lds_rsum = 0, lds_rcnt = 0;
     int32_t lds_pcnt = 0, lds_ccnt = 0, lds_ctl = 0, waves = 1;
     std::vector<size_t> log_off;
@@ -438,7 +444,7 @@ int log_plan_make(const dtr_log *logs, int32_t n_logs, const dtr_sim_spec *sims,
         Lowerer lw(logs[i], i, p->logs[i]);
         if (int rc = lw.run()) return give_up(rc);
     }
-    bool need_uf = false, need_walk = false;
+    bool need_uf = false, need_walk = false, any_swept = false, any_walked = false;
     int64_t S_max = 1, T_max = 1, F_max = 1, E_max = 0;
     for (int32_t i = 0; i < n_sims; i++) {
         const dtr_sim_spec &s = sims[i];
@@ -451,6 +457,7 @@ int log_plan_make(const dtr_log *logs, int32_t n_logs, const dtr_sim_spec *sims,
         T_max = std::max<int64_t>(T_max, d.T);
         F_max = std::max<int64_t>(F_max, d.F);
         E_max = std::max<int64_t>(E_max, (int64_t)d.par.size());
+        if (heuristic_class(s.heuristic) == 1) (d.sweep ? any_swept : any_walked) = true;
     }
     p->sims.assign(sims, sims + n_sims);
     // walk state in LDS when the largest log fits: storage states, visited
@@ -478,9 +485,12 @@ int log_plan_make(const dtr_log *logs, int32_t n_logs, const dtr_sim_spec *sims,
             at(p->lds_ca, 2 * (size_t)E_max);
             at(p->lds_c0, 8 * (size_t)S_max);
             at(p->lds_cand, 2 * (size_t)S_max);
-            at(p->lds_stk, 2 * (size_t)dtr::LOG_LDS_STACK * lanes);
+            at(p->lds_stk, any_walked ? 2 * (size_t)dtr::LOG_LDS_STACK * lanes : 0);
+            const size_t chunks = ((size_t)S_max + dtr::WAVE - 1) / dtr::WAVE;
+            at(p->lds_ev, any_swept ? 8 * chunks : 0);
+            at(p->lds_rows, any_swept ? 16 * dtr::WAVE * chunks : 0);
             at(p->lds_ctr, 4);
-            at(p->lds_ctl, 16);
+            at(p->lds_ctl, 32);
             at(p->lds_sz, 8 * (size_t)S_max);
             at(p->lds_last, 8 * (size_t)S_max);
             at(p->lds_rsum, 8 * (size_t)S_max);
@@ -598,6 +608,8 @@ int log_plan_upload(LogPlan *p, uint8_t *ws, hipStream_t st)
         D.T = d.T;
         D.F = d.F;
         D.n_req = (int32_t)d.req.size();
+        D.sweep = d.sweep;
+        D.pad = 0;
         D.s_size = put(d.s_size);
         D.s_c0 = put(d.s_c0);
         D.s_const = put(d.s_const);
@@ -656,6 +668,8 @@ int log_plan_launch(const LogPlan *p, uint8_t *ws, hipStream_t st)
     a.lds_co = p->lds_co;
     a.lds_pa = p->lds_pa;
     a.lds_ca = p->lds_ca;
+    a.lds_ev = p->lds_ev;
+    a.lds_rows = p->lds_rows;
     a.wm_words = p->wm_words;
     a.lds_c0 = p->lds_c0;
     a.lds_cand = p->lds_cand;

@@ -32,6 +32,7 @@ struct LogProgDev {
     const int32_t *out_off, *out; // output tensors
     const int32_t *rel_off, *rel; // storages released after each operator, in log order
     const int32_t *req;           // [n_req] tensors still referenced at the end, ascending
+    int32_t sweep, pad;           // every edge goes from a smaller storage id to a larger: walks are swept
     const int32_t *born_off, *born; // per operator: (parent, storage) edges its first run creates
 };
 
@@ -94,11 +95,17 @@ struct LogKernelArgs {
     int32_t lds_rsum, lds_rcnt;  // per listed candidate: walked cost, count
     int32_t lds_pcnt, lds_ccnt;  // edges created so far per storage
     int32_t wm_words;         // 32-bit words per visited bitset (a multiple of 4)
+    // sweeps (logs with LogProgDev::sweep): the masks of evicted storages (a
+    // 64-bit word per chunk of 64) and each storage's parents and children in
+    // its own chunk (rowp, rowc); the waves' reach masks take the place of the
+    // visited bitsets (both are all zero between scans)
+    int32_t lds_ev, lds_rows;
     // LDS variant: waves per workgroup (1 .. MAX_LOG_WAVES; the first replays,
     // the others help with walk scans) and the offset of the control words
     int32_t waves, lds_ctl;
 };
 
+constexpr int SWEEP_STORAGES = 4096;      // 64 chunks: the pending chunks are one 64-bit mask
 constexpr int LOG_LDS_STACK = 32;
 constexpr int MAX_LOG_WAVES = 4;
 

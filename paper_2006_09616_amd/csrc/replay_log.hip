@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "layout_log.h"
+#include "sweep.h"
 
 namespace dtr {
 namespace logk {
@@ -51,7 +52,7 @@ __device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_read
 // workgroup control words in LDS (multi-wave workgroups): the replay index,
 // the command for the helper waves, the candidate count and the e* flag of a
 // walk scan
-enum { CTL_K = 0, CTL_CMD = 1, CTL_N = 2, CTL_BOTH = 3 };
+enum { CTL_K = 0, CTL_CMD = 1, CTL_N = 2, CTL_BOTH = 3, CTL_SWEEP = 4 };
 enum { CMD_WALK = 1, CMD_DONE = 2 };
 
 // Order this wave's LDS and global accesses before and after (what a
@@ -121,6 +122,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // the lowered program's tables, read with global (never flat) loads
 struct ProgG {
     int32_t S, T, F, n_req;
+    int32_t sweep;
     const GAS int64_t *s_size, *s_c0;
     const GAS uint8_t *s_const;
     const GAS int32_t *par_off, *par, *ch_off, *ch, *dt_off, *dt;
@@ -138,6 +140,7 @@ __device__ __forceinline__ ProgG prog_global(const LogProgDev &d)
     g.T = d.T;
     g.F = d.F;
     g.n_req = d.n_req;
+    g.sweep = d.sweep;
     g.s_size = (const GAS int64_t *)d.s_size;
     g.s_c0 = (const GAS int64_t *)d.s_c0;
     g.s_const = (const GAS uint8_t *)d.s_const;
@@ -184,7 +187,12 @@ struct Sim {
     LAS int64_t *rsum;         // per listed candidate: walked cost and count
     LAS int32_t *rcnt;
     LAS int32_t *ctl;          // workgroup control words (LogCtl)
+    // sweeps (L only): evicted storages (a word per chunk), the storages'
+    // neighbours in their own chunk (parents, children), this wave's reach
+    // masks (in the place of the visited bitsets)
+    LAS uint64_t *ev, *rows, *reach;
     int32_t nw;                // waves in the workgroup (the others help with walks)
+    int32_t n_storages;        // bound of the storage arrays in LDS
     int32_t wmw;               // words per visited bitset
     // slot memory
     GAS uint8_t *pinned, *pending;
@@ -538,6 +546,108 @@ __device__ void walk_candidates(Sim<L> &s, int32_t n, bool both)
     }
 }
 
+// The evicted ancestors (up) or descendants of up to 64 candidates at once,
+// one candidate (storage x, when `has`) per lane, on a graph whose edges all
+// go from smaller to larger storage ids.  `reach` holds for each storage the
+// set of candidates whose walk has reached it, a bit per lane; chunks of 64
+// storages are taken in the edges' order (ancestors from the last chunk down,
+// with the lanes reversed), each by sweep_chunk, after which its sets join
+// those of their evicted neighbours in later chunks.  Chunks that nothing has
+// reached are skipped.  Adds the walked cost and count to sum and cnt.
+//
+// Bound by the issue of the chunk step: a replay's decision costs a few
+// thousand cycles per chunk reached and group of 64 candidates, where the
+// walks took some 900 cycles per member of the longest set (up to 900 of them
+// on the ResNet log, whose dead gradient chains stay in the graph).
+template <bool L>
+__device__ void sweep_side(const Sim<L> &s, bool up, bool has, int32_t x, uint64_t &sum, int32_t &cnt)
+{
+    constexpr uint64_t ONE = uint64_t(1);
+    const int32_t at = up ? WAVE - 1 - s.lane : s.lane;
+    uint64_t pend = 0;
+    if (has) s.reach[x] = ONE << s.lane;
+    lds_order();
+    join_masks(pend, has ? ONE << (x >> 6) : 0);
+    const auto off = up ? s.po : s.co;
+    const auto adj = up ? s.pa : s.ca;
+    const auto num = up ? s.pcnt : s.ccnt;
+    while (pend) {
+        const int32_t c = up ? 63 - __builtin_clzll(pend) : __builtin_ctzll(pend);
+        pend &= ~(ONE << c);
+        const int32_t u = c * WAVE + at;
+        const uint64_t Mv = s.reach[u];
+        s.reach[u] = 0;
+        uint64_t ev = s.ev[c];
+        const uint64_t row = s.rows[2 * u + (up ? 1 : 0)];     // the side's sources: children going up
+        const int64_t c0 = s.c0d[u < s.n_storages ? u : 0];
+        ev = (uint64_t)uni64((int64_t)(up ? __builtin_bitreverse64(ev) : ev));
+        const bool mine = lane_in(ev);
+        const uint64_t src = mine ? (up ? __builtin_bitreverse64(row) : row) : 0;
+        const uint64_t cost = mine ? (uint64_t)c0 : 0;
+        uint32_t m0 = (uint32_t)Mv, m1 = (uint32_t)(Mv >> 32);
+        sweep_chunk(m0, m1, (uint32_t)src, (uint32_t)(src >> 32), (uint32_t)cost & 0xFFFFFFFu, sum, cnt);
+        // a storage's cost sums operator costs and may pass 2^28
+        for (uint64_t q = __ballot((cost >> 28) != 0 && (m0 | m1) != 0); q; q &= q - 1) {
+            const int32_t k = __builtin_ctzll(q);
+            const uint64_t b = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(m0, k) |
+                               ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(m1, k) << 32);
+            const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(cost >> 28), k);
+            if (lane_in(b)) sum += (uint64_t)hi << 28;
+        }
+        // neighbours in other chunks, four reads at a time
+        const bool live = (m0 | m1) != 0;
+        int32_t e = 0, end = 0;
+        if (live) {
+            e = off[u];
+            end = e + num[u];
+        }
+        const uint64_t Mi = (uint64_t)m0 | ((uint64_t)m1 << 32);
+        uint64_t to = 0;
+        while (__ballot(e < end)) {
+            int32_t v[4];
+            uint8_t st[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) v[j] = e + j < end ? (int32_t)adj[e + j] : u;
+#pragma unroll
+            for (int j = 0; j < 4; j++) st[j] = s.state[v[j] < s.n_storages ? v[j] : 0];
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+                if (e + j < end && st[j] == ST_EVICTED && (v[j] >> 6) != c) {
+                    __hip_atomic_fetch_or(s.reach + v[j], Mi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    to |= ONE << (v[j] >> 6);
+                }
+            e += 4;
+        }
+        join_masks(pend, to);
+        lds_order();
+    }
+}
+
+// Sweep the listed candidates cand[0..n), 64 to a group: the waves take
+// (group, side) pairs from the shared counter and add each candidate's walked
+// cost and count to its entries (cleared when listed).
+template <bool L>
+__device__ void sweep_candidates(Sim<L> &s, int32_t n, bool both)
+{
+    const int32_t groups = (n + WAVE - 1) / WAVE, tasks = both ? 2 * groups : groups;
+    for (;;) {
+        uint32_t got = 0;
+        if (s.lane == 0) got = atomicAdd((uint32_t *)s.ctr, 1u);
+        const int32_t t = uni((int32_t)got);
+        if (t >= tasks) break;
+        const int32_t k = (both ? t >> 1 : t) * WAVE + s.lane;
+        const bool has = k < n;
+        uint64_t sum = 0;
+        int32_t cnt = 0;
+        sweep_side(s, !both || (t & 1) == 0, has, (int32_t)s.cand[has ? k : 0], sum, cnt);
+        if (has) {
+            // every candidate has counted itself (at no cost) once
+            __hip_atomic_fetch_add((LAS uint64_t *)s.rsum + k, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_fetch_add(s.rcnt + k, cnt - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+}
+
 template <bool L>
 __device__ void scan_walk_lds(Sim<L> &s, uint64_t min_size, bool sampling, uint64_t tau, uint64_t &bn,
                               u128 &bd, int32_t &bi)
@@ -559,6 +669,14 @@ __device__ void scan_walk_lds(Sim<L> &s, uint64_t min_size, bool sampling, uint6
             ok = mix64((s.seed ^ SAMPLE_STREAM) + GOLDEN * key) < tau;
         }
         const uint64_t m = __ballot(ok);
+        if (s.P.sweep) {
+            const uint64_t ev = __ballot(x < S && s.state[x < S ? x : 0] == ST_EVICTED);
+            if (s.lane == 0) s.ev[b / WAVE] = ev;
+            if (x < S) {
+                s.rsum[x] = 0;
+                s.rcnt[x] = 0;
+            }
+        }
         if (ok)
             s.cand[n + (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] = (uint16_t)x;
@@ -572,11 +690,13 @@ __device__ void scan_walk_lds(Sim<L> &s, uint64_t min_size, bool sampling, uint6
         s.ctl[CTL_CMD] = CMD_WALK;
         s.ctl[CTL_N] = n;
         s.ctl[CTL_BOTH] = both ? 1 : 0;
+        s.ctl[CTL_SWEEP] = s.P.sweep;
         __syncthreads();
     } else {
         wave_sync();
     }
-    walk_candidates(s, n, both);
+    if (s.P.sweep) sweep_candidates(s, n, both);
+    else walk_candidates(s, n, both);
     if (s.nw > 1) __syncthreads();
     else wave_sync();
     // score every walked candidate
@@ -782,6 +902,12 @@ __device__ void execute(Sim<L> &s, int32_t o, bool remat)
             const int32_t par = s.P.born[2 * b], st = s.P.born[2 * b + 1];
             s.pcnt[st] += 1;
             s.ccnt[par] += 1;
+            if constexpr (L) {
+                if (s.P.sweep && s.walk && (par >> 6) == (st >> 6)) {
+                    s.rows[2 * st] |= uint64_t(1) << (par & 63);
+                    s.rows[2 * par + 1] |= uint64_t(1) << (st & 63);
+                }
+            }
         }
     }
     if (s.clock >= CLOCK_LIMIT) { s.status = STATUS_CLOCK; return; }
@@ -865,6 +991,9 @@ __device__ void run_sim(const LogKernelArgs &a, int32_t sim, uint8_t *base, int3
         s.ctr = (LAS uint32_t *)(lds + a.lds_ctr);
         s.rsum = (LAS int64_t *)(lds + a.lds_rsum);
         s.rcnt = (LAS int32_t *)(lds + a.lds_rcnt);
+        s.ev = (LAS uint64_t *)(lds + a.lds_ev);
+        s.rows = (LAS uint64_t *)(lds + a.lds_rows);
+        s.reach = (LAS uint64_t *)(lds + a.lds_wm);
         s.ctl = (LAS int32_t *)(lds + a.lds_ctl);
         s.last = (Mem<L, int64_t>)(lds + a.lds_last);
         s.sz = (Mem<L, const int64_t>)(lds + a.lds_sz);
@@ -915,6 +1044,7 @@ __device__ void run_sim(const LogKernelArgs &a, int32_t sim, uint8_t *base, int3
     s.sp = 0;
 
     const int32_t S = s.P.S, T = s.P.T, F = s.P.F;
+    s.n_storages = S;
     for (int32_t i = lane; i < S; i += WAVE) {
         s.state[i] = ST_UNCOMPUTED;
         s.pinned[i] = s.P.s_const[i];
@@ -950,6 +1080,8 @@ __device__ void run_sim(const LogKernelArgs &a, int32_t sim, uint8_t *base, int3
             pa[e] = (Adj<L>)s.P.par[e];
             ca[e] = (Adj<L>)s.P.ch[e];
         }
+        if (s.P.sweep && s.walk)
+            for (int32_t i = lane; i < 2 * ((S + WAVE - 1) / WAVE * WAVE); i += WAVE) s.rows[i] = 0;
         Mem<L, int64_t> szl = (Mem<L, int64_t>)s.sz;
         for (int32_t i = lane; i < S; i += WAVE) szl[i] = s.P.s_size[i];
     }
@@ -1025,12 +1157,17 @@ __device__ void help_walks(const LogKernelArgs &a, uint8_t *base, int32_t lane, 
         s.ctr = (LAS uint32_t *)(lds + a.lds_ctr);
         s.rsum = (LAS int64_t *)(lds + a.lds_rsum);
         s.rcnt = (LAS int32_t *)(lds + a.lds_rcnt);
+        s.ev = (LAS uint64_t *)(lds + a.lds_ev);
+        s.rows = (LAS uint64_t *)(lds + a.lds_rows);
+        s.reach = (LAS uint64_t *)((LAS uint32_t *)(lds + a.lds_wm) + wave * WAVE * W);
+        s.n_storages = (int32_t)Y.S_max;
         s.queue = (GAS int32_t *)(gb + Y.queue) + (size_t)id * (size_t)(Y.S_max + 2);
         const LAS int32_t *ctl = (const LAS int32_t *)(lds + a.lds_ctl);
         for (;;) {
             __syncthreads();
             if (ctl[CTL_CMD] == CMD_DONE) break;
-            walk_candidates(s, ctl[CTL_N], ctl[CTL_BOTH] != 0);
+            if (ctl[CTL_SWEEP]) sweep_candidates(s, uni(ctl[CTL_N]), uni(ctl[CTL_BOTH]) != 0);
+            else walk_candidates(s, ctl[CTL_N], ctl[CTL_BOTH] != 0);
             __syncthreads();
         }
     }

@@ -209,6 +209,35 @@ def test_workgroup_shapes_of_the_lds_variant(gpu, oracle_lib):
     assert {(4, True), (2, True), (1, True), (1, False)} <= seen, seen
 
 
+def test_sweep_chunk_edges_logs(gpu, oracle_lib):
+    """Logs whose storage graph goes from smaller to larger ids are swept:
+    storage counts around the 64 of a chunk, wide operators (more than four
+    neighbours outside the chunk), storages whose summed cost passes 2^28,
+    more than 64 candidates, beside logs with cycles (walked lane by lane)."""
+    logs, rows = [], []
+    for s, F in enumerate((1, 62, 63, 64, 65, 128, 129, 500)):
+        logs.append(W.log_from_trace(W.random_program(7300 + s, n_ops=F, n_const=s % 3, max_in=2 + 6 * (s % 2),
+                                                      max_size=9, max_cost=9, permute_ids=False)))
+    for blocks in (1, 4, 9):
+        logs.append(W.resnet_log(seed=blocks, blocks=blocks))
+    heavy = W.random_program(7400, n_ops=90, max_size=9, max_cost=9, permute_ids=False)
+    heavy.op_cost = heavy.op_cost * 0 + (1 << 28)
+    logs.append(W.log_from_trace(heavy))
+    logs.append(W.random_log(7500, n_steps=200, n_const=2))
+    peaks = unlimited_peaks(oracle_lib, logs)
+    for i, pk in enumerate(peaks):
+        for h in (W.H_DTR, W.H_ESTAR, W.H_MSPS, W.h_family(W.C_ESTAR, 0, 0)):
+            for f in (0.3, 0.5, 0.8):
+                for pol in (W.POLICY_EAGER, W.POLICY_IGNORE, W.POLICY_BANISH):
+                    rows.append((i, h, max(1, int(pk * f)), 3 * i, pol, i % 4))
+    specs = W.make_specs(rows)
+    ref = oracle_lib.run_log(logs, specs)
+    assert int(ref["n_nbr_visits"].max()) > 0
+    compare(gpu.run_log(logs, specs), ref, specs, "swept and walked logs")
+    keep = specs["trace"] < 11                     # swept logs alone: no walk arrays in LDS
+    compare(gpu.run_log(logs[:11], specs[keep]), ref[keep], specs[keep], "swept logs")
+
+
 def test_more_storages_than_16_bit_ids(gpu, oracle_lib):
     """A log of 66000 storages (the Appendix A chain of 33000 layers written as
     a log): its neighbour ids do not fit the LDS variant's 16 bits, so it
