@@ -423,7 +423,7 @@ struct LogPlan {
     dtr::LogSlotLayout L{};
     int32_t n_slots = 1;
     int32_t lds_bytes = 0, lds_state = 0, lds_wm = 0, lds_po = 0, lds_co = 0, lds_pa = 0, lds_ca = 0, wm_words = 0;
-    int32_t lds_ev = 0, lds_rows = 0;
+    int32_t lds_ev = 0, lds_rows = 0, lds_pinned = 0, lds_locks = 0;
     int32_t lds_c0 = 0, lds_cand = 0, lds_stk = 0, lds_ctr = 0, lds_sz = 0, lds_last = 0, lds_rsum = 0, lds_rcnt = 0;
     int32_t lds_pcnt = 0, lds_ccnt = 0, lds_ctl = 0, waves = 1;
     std::vector<size_t> log_off;
@@ -491,6 +491,8 @@ int log_plan_make(const dtr_log *logs, int32_t n_logs, const dtr_sim_spec *sims,
             at(p->lds_rows, any_swept ? 16 * dtr::WAVE * chunks : 0);
             at(p->lds_ctr, 4);
             at(p->lds_ctl, 32);
+            at(p->lds_pinned, (size_t)S_max);
+            at(p->lds_locks, 4 * (size_t)S_max);
             at(p->lds_sz, 8 * (size_t)S_max);
             at(p->lds_last, 8 * (size_t)S_max);
             at(p->lds_rsum, 8 * (size_t)S_max);
@@ -670,6 +672,8 @@ int log_plan_launch(const LogPlan *p, uint8_t *ws, hipStream_t st)
     a.lds_ca = p->lds_ca;
     a.lds_ev = p->lds_ev;
     a.lds_rows = p->lds_rows;
+    a.lds_pinned = p->lds_pinned;
+    a.lds_locks = p->lds_locks;
     a.wm_words = p->wm_words;
     a.lds_c0 = p->lds_c0;
     a.lds_cand = p->lds_cand;

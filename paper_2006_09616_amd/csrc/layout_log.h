@@ -91,6 +91,7 @@ struct LogKernelArgs {
     // and for the walk scan: storage costs c0, the candidate list, 64
     // pending-storage stacks of LOG_LDS_STACK entries, the candidate counter
     int32_t lds_c0, lds_cand, lds_stk, lds_ctr;
+    int32_t lds_pinned, lds_locks;   // never-evictable flags and lock counts
     int32_t lds_sz, lds_last;  // storage sizes and last-access times
     int32_t lds_rsum, lds_rcnt;  // per listed candidate: walked cost, count
     int32_t lds_pcnt, lds_ccnt;  // edges created so far per storage

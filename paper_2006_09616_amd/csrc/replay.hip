@@ -42,11 +42,10 @@
 
 #include "../../include/dtr_sim.h"
 #include "layout.h"
+#include "score.h"
 #include "sweep.h"
 
 namespace dtr {
-
-typedef unsigned __int128 u128;
 
 enum { H_DTR = 0, H_EQ = 1, H_LOCAL = 2, H_LRU = 3, H_SIZE = 4, H_RAND = 5, H_ESTAR = 6, H_MSPS = 7,
        H_FAMILY = 16 };
@@ -102,14 +101,6 @@ __device__ __forceinline__ int64_t uni64(int64_t v)
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// lane j's value (j wave-uniform)
-__device__ __forceinline__ uint64_t readlane64(uint64_t v, int32_t j)
-{
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, j);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), j);
-    return ((uint64_t)hi << 32) | lo;
-}
-
 #define GAS __attribute__((address_space(1)))    // global memory
 #define LAS __attribute__((address_space(3)))    // LDS
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
@@ -144,43 +135,6 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z)
     return z ^ (z >> 31);
 }
 
-// x's minimum over the lanes that are not NaN (uniform): row shifts, then the
-// rows' results passed on, a few cycles a step where a shuffle goes through LDS
-__device__ __forceinline__ float wave_min(float x)
-{
-    auto step = [&](auto ctrl, auto rows) {
-        const int v = __builtin_bit_cast(int, x);
-        x = fminf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, ctrl.value, rows.value, 0xF, false)));
-    };
-    using std::integral_constant;
-    step(integral_constant<int, 0x111>(), integral_constant<int, 0xF>());    // row_shr:1
-    step(integral_constant<int, 0x112>(), integral_constant<int, 0xF>());    // row_shr:2
-    step(integral_constant<int, 0x114>(), integral_constant<int, 0xF>());    // row_shr:4
-    step(integral_constant<int, 0x118>(), integral_constant<int, 0xF>());    // row_shr:8
-    step(integral_constant<int, 0x142>(), integral_constant<int, 0xA>());    // row_bcast:15 into rows 1 and 3
-    step(integral_constant<int, 0x143>(), integral_constant<int, 0xC>());    // row_bcast:31 into rows 2 and 3
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), WAVE - 1));
-}
-
-// x summed over the lanes (uniform), as wave_min
-__device__ __forceinline__ uint64_t wave_add(uint64_t x)
-{
-    auto step = [&](auto ctrl, auto rows) {
-        const int lo = (int)(uint32_t)x, hi = (int)(uint32_t)(x >> 32);
-        const uint32_t a = (uint32_t)__builtin_amdgcn_update_dpp(0, lo, ctrl.value, rows.value, 0xF, false);
-        const uint32_t b = (uint32_t)__builtin_amdgcn_update_dpp(0, hi, ctrl.value, rows.value, 0xF, false);
-        x += (uint64_t)a | ((uint64_t)b << 32);
-    };
-    using std::integral_constant;
-    step(integral_constant<int, 0x111>(), integral_constant<int, 0xF>());
-    step(integral_constant<int, 0x112>(), integral_constant<int, 0xF>());
-    step(integral_constant<int, 0x114>(), integral_constant<int, 0xF>());
-    step(integral_constant<int, 0x118>(), integral_constant<int, 0xF>());
-    step(integral_constant<int, 0x142>(), integral_constant<int, 0xA>());
-    step(integral_constant<int, 0x143>(), integral_constant<int, 0xC>());
-    return readlane64(x, WAVE - 1);
-}
-
 // floor(a / d) for a < 2^62 with a quotient below 2^36: the quotient in double
 // precision is off by at most one (relative error below 2^-51), which the
 // exact remainder shows; a 64-bit division takes several times as long.
@@ -191,15 +145,6 @@ __device__ __forceinline__ uint64_t div_small(uint64_t a, uint32_t d)
     if (r < 0) q--;
     else if (r >= (int64_t)d) q++;
     return q;
-}
-
-// a strictly better (lower score) than b; ties go to the smaller id
-__device__ __forceinline__ bool better(uint64_t na, u128 da, int32_t ia, uint64_t nb, u128 db, int32_t ib)
-{
-    u128 l = (u128)na * db;
-    u128 r = (u128)nb * da;
-    if (l != r) return l < r;
-    return ia < ib;
 }
 
 // Union-find node store: ids below UF_LDS in this wavefront's LDS array, the
@@ -1009,64 +954,6 @@ __device__ __forceinline__ int64_t eq_cost_full(const Sim<HC> &s, const NS &N, i
     return sum;
 }
 
-// Scores are N / (da * db) with N < 2^64 and da * db < 2^76.  A float
-// estimate decides every comparison whose two estimates differ by more than a
-// factor 1 -+ 2^-16; the rest (near ties, exact ties, 0/0) are decided
-// exactly by 128-bit cross-multiplication, so the outcome is always that of
-// the exact comparison.  Error of the estimate: each u64f conversion rounds
-// twice (the high and low 32-bit halves, then the fused sum), under
-// (1 + 2^-24)^2 - 1 < 2^-22.9; the product da * db adds one rounding
-// (2^-24), v_rcp_f32 at most 1 ulp (2^-23) and the final product one
-// rounding (2^-24): in all below 3 * 2^-22.9 + 2^-23 + 2 * 2^-24 < 2^-20.4.
-// Two estimates within the margin can therefore never be ordered wrongly by
-// the float test: (1 - 2^-16) (1 + 2^-24) (1 + 2^-20.4)^2 < 1.
-constexpr float FILTER_LO = 1.0f - 0x1p-16f;
-constexpr float FILTER_HI = 1.0f + 0x1p-16f;
-
-__device__ __forceinline__ float u64f(uint64_t x)
-{
-    return fmaf((float)(uint32_t)(x >> 32), 4294967296.0f, (float)(uint32_t)x);
-}
-
-__device__ __forceinline__ float score_est(uint64_t N, uint64_t da, uint64_t db)
-{
-    return u64f(N) * __builtin_amdgcn_rcpf(u64f(da) * u64f(db));   // 0 -> inf, 0/0 -> NaN
-}
-
-__device__ __forceinline__ bool better_exact(uint64_t na, uint64_t daa, uint64_t dba, int32_t ia, uint64_t nb,
-                                             uint64_t dab, uint64_t dbb, int32_t ib)
-{
-    return better(na, (u128)daa * dba, ia, nb, (u128)dab * dbb, ib);
-}
-
-struct Best {
-    float sc, lo, hi;    // estimated score of the best and its decision bounds
-    uint64_t N, da, db;
-    int32_t id, slot, have;
-};
-
-// keep the candidate if valid and better than the current best
-__device__ __forceinline__ void take(Best &b, bool valid, float sc, uint64_t N, uint64_t da, uint64_t db, int32_t id,
-                                     int32_t slot)
-{
-    const bool dec_better = sc < b.lo;
-    const bool dec_worse = sc > b.hi;
-    bool t = valid && (!b.have || dec_better);
-    const bool close = valid && b.have && !dec_better && !dec_worse;
-    if (ballot(close)) {
-        if (close) t = better_exact(N, da, db, id, b.N, b.da, b.db, b.id);
-    }
-    b.sc = t ? sc : b.sc;
-    b.lo = t ? sc * FILTER_LO : b.lo;
-    b.hi = t ? sc * FILTER_HI : b.hi;
-    b.N = t ? N : b.N;
-    b.da = t ? da : b.da;
-    b.db = t ? db : b.db;
-    b.id = t ? id : b.id;
-    b.slot = t ? slot : b.slot;
-    b.have = t ? 1 : b.have;
-}
-
 // Which candidates an eviction decision searches (the prototype's search
 // approximations, Appendix E): those of size >= min_size (size at least 1% of
 // the pool's mean: 100 size n0 >= sum of sizes, i.e. size >= ceil(sum / (100
@@ -1697,29 +1584,15 @@ __device__ void sweep_groups(const Slot<HC> &S, const Sweep &W, const WalkParams
 __device__ WaveBest wave_best(const Best &best)
 {
     WaveBest r;
-    const float mn = wave_min(best.have ? best.sc : __builtin_inff());
-    const float thr = mn * FILTER_HI;
-    uint64_t m = ballot(best.have && !(best.sc > thr));     // NaN estimates stay in
-    r.have = m ? 1 : 0;
-    r.N = 0;
-    r.da = r.db = 1;
-    r.id = 0x7fffffff;
-    r.slot = -1;
+    const int32_t j = best_lane(best);
+    r.have = j >= 0 ? 1 : 0;
+    r.N = j >= 0 ? readlane64(best.N, j) : 0;
+    r.da = j >= 0 ? readlane64(best.da, j) : 1;
+    r.db = j >= 0 ? readlane64(best.db, j) : 1;
+    r.id = j >= 0 ? __builtin_amdgcn_readlane(best.id, j) : 0x7fffffff;
+    r.slot = j >= 0 ? __builtin_amdgcn_readlane(best.slot, j) : -1;
     r.pad = 0;
     r.nbr = r.adj = r.scored = 0;
-    while (m) {
-        const int32_t j = __ffsll((long long)m) - 1;
-        m &= m - 1;
-        const uint64_t cN = readlane64(best.N, j), cda = readlane64(best.da, j), cdb = readlane64(best.db, j);
-        const int32_t cid = __builtin_amdgcn_readlane(best.id, j), cslot = __builtin_amdgcn_readlane(best.slot, j);
-        if (r.slot < 0 || better_exact(cN, cda, cdb, cid, r.N, r.da, r.db, r.id)) {
-            r.N = cN;
-            r.da = cda;
-            r.db = cdb;
-            r.id = cid;
-            r.slot = cslot;
-        }
-    }
     return r;
 }
 
@@ -2084,31 +1957,10 @@ __device__ __forceinline__ int32_t scan(Sim<HC> &s, int32_t &victim_slot, const 
     if constexpr (cls(HC) == HC_WALK) walk_scan<HC>(s, F, best, scored);
     else scan_rounds<HC>(s, F, best, scored, bad);
     if (ballot(bad)) { set_status(s, ST_CAPACITY); return -1; }
-    // cross-lane minimum: the smallest estimate bounds the winner; only the
-    // lanes within the filter margin of it (usually one) are compared exactly
-    const float mn = wave_min(best.have ? best.sc : __builtin_inff());
-    const float thr = mn * FILTER_HI;
-    uint64_t m = ballot(best.have && !(best.sc > thr));     // NaN estimates stay in
-    if (!m) return -1;
-    int32_t j = __ffsll((long long)m) - 1;
-    m &= m - 1;
-    uint64_t wN = readlane64(best.N, j), wda = readlane64(best.da, j), wdb = readlane64(best.db, j);
-    int32_t wid = __builtin_amdgcn_readlane(best.id, j), wslot = __builtin_amdgcn_readlane(best.slot, j);
-    while (m) {
-        j = __ffsll((long long)m) - 1;
-        m &= m - 1;
-        const uint64_t cN = readlane64(best.N, j), cda = readlane64(best.da, j), cdb = readlane64(best.db, j);
-        const int32_t cid = __builtin_amdgcn_readlane(best.id, j), cslot = __builtin_amdgcn_readlane(best.slot, j);
-        if (better_exact(cN, cda, cdb, cid, wN, wda, wdb, wid)) {
-            wN = cN;
-            wda = cda;
-            wdb = cdb;
-            wid = cid;
-            wslot = cslot;
-        }
-    }
-    victim_slot = wslot;
-    return wid;
+    const int32_t j = best_lane(best);
+    if (j < 0) return -1;
+    victim_slot = __builtin_amdgcn_readlane(best.slot, j);
+    return __builtin_amdgcn_readlane(best.id, j);
 }
 
 // ----------------------------------------------------- operator calls --

@@ -31,12 +31,11 @@
 #include <type_traits>
 
 #include "layout_log.h"
+#include "score.h"
 #include "sweep.h"
 
 namespace dtr {
 namespace logk {
-
-typedef unsigned __int128 u128;
 
 enum { ST_UNCOMPUTED = 0, ST_RESIDENT = 1, ST_EVICTED = 2, ST_BANISHED = 3 };
 enum { STATUS_OK = 0, STATUS_OOM = 1, STATUS_CLOCK = 2, STATUS_CAPACITY = 3 };
@@ -78,28 +77,7 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z)
     return z ^ (z >> 31);
 }
 
-__device__ __forceinline__ uint64_t shfl64(uint64_t v, int lane_mask)
-{
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, lane_mask, WAVE);
-    const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), lane_mask, WAVE);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-__device__ __forceinline__ int64_t wave_sum(int64_t v)
-{
-    for (int m = WAVE / 2; m >= 1; m >>= 1) v += (int64_t)shfl64((uint64_t)v, m);
-    return uni64(v);
-}
-
-// a strictly better (lower score) than b; id -1 is no candidate
-__device__ __forceinline__ bool better(uint64_t na, u128 da, int32_t ia, uint64_t nb, u128 db, int32_t ib)
-{
-    if (ia < 0) return false;
-    if (ib < 0) return true;
-    const u128 l = (u128)na * db, r = (u128)nb * da;
-    if (l != r) return l < r;
-    return ia < ib;
-}
+__device__ __forceinline__ int64_t wave_sum(int64_t v) { return (int64_t)wave_add((uint64_t)v); }
 
 #define GAS __attribute__((address_space(1)))
 #define LAS __attribute__((address_space(3)))
@@ -195,8 +173,10 @@ struct Sim {
     int32_t n_storages;        // bound of the storage arrays in LDS
     int32_t wmw;               // words per visited bitset
     // slot memory
-    GAS uint8_t *pinned, *pending;
-    GAS int32_t *locks, *node;
+    Mem<L, uint8_t> pinned;    // never evictable (constants, banished storages' dependents)
+    Mem<L, int32_t> locks;
+    GAS uint8_t *pending;
+    GAS int32_t *node;
     GAS int64_t *sgen, *gen;
     GAS int32_t *ufp, *ufs, *remap;
     GAS int64_t *ufc, *uft;
@@ -232,7 +212,10 @@ __device__ __forceinline__ bool defined(const Sim<L> &s, int32_t t)
 template <bool L>
 __device__ __forceinline__ bool evictable(const Sim<L> &s, int32_t st)
 {
-    return s.state[st] == ST_RESIDENT && s.locks[st] == 0 && !s.pinned[st] && !s.P.s_const[st];
+    // every read issued before the first test
+    const uint8_t state = s.state[st], pin = s.pinned[st];
+    const int32_t locks = s.locks[st];
+    return (state == ST_RESIDENT) & (locks == 0) & (pin == 0);
 }
 
 // ----------------------------------------------------------- union-find --
@@ -298,7 +281,7 @@ __device__ void uf_compact(Sim<L> &s)
     for (int32_t b = 0; b < n; b += WAVE) {
         const int32_t i = b + s.lane;
         const bool keep = i < n && s.remap[i] != 0;
-        const uint64_t m = __ballot(keep);
+        const uint64_t m = ballot(keep);
         if (keep) {
             const int32_t k = kept + (int32_t)__builtin_amdgcn_mbcnt_hi(
                                          (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
@@ -392,7 +375,7 @@ __device__ int64_t eq_cost(Sim<L> &s, int32_t x, int64_t &cnt)
 }
 
 template <bool L>
-__device__ __forceinline__ void score(Sim<L> &s, int32_t x, uint64_t &N, u128 &D)
+__device__ __forceinline__ void score(Sim<L> &s, int32_t x, uint64_t &N, uint64_t &da, uint64_t &db)
 {
     const int64_t m = s.sz[x];
     const int64_t stale = s.clock - s.last[x];
@@ -408,7 +391,7 @@ __device__ __forceinline__ void score(Sim<L> &s, int32_t x, uint64_t &N, u128 &D
     default: {
         const uint64_t key = ((uint64_t)s.eviction_no << 32) + (uint64_t)(uint32_t)x;
         N = mix64(s.seed + GOLDEN * key);
-        D = 1;
+        da = db = 1;
         return;
     }
     }
@@ -416,7 +399,8 @@ __device__ __forceinline__ void score(Sim<L> &s, int32_t x, uint64_t &N, u128 &D
         s.nbr_l += cnt;
         s.adj_l += deg;
     }
-    D = (u128)(uint64_t)(s.use_m ? m : 1) * (u128)(uint64_t)(s.use_s ? stale : 1);
+    da = s.use_m ? (uint64_t)m : 1;
+    db = s.use_s ? (uint64_t)stale : 1;
 }
 
 // ----------------------------------------------------------- eviction --
@@ -483,7 +467,7 @@ __device__ void walk_candidates(Sim<L> &s, int32_t n, bool both)
     // each iteration: a finished walk clears a quad of its bitset; otherwise
     // an exhausted adjacency pops the next storage (or turns to the children,
     // or records the walk), then one edge is examined
-    while (__ballot(x >= 0) != 0) {
+    while (ballot(x >= 0) != 0) {
         if (x < 0) continue;
         if (clr >= 0) {
             *(LAS u32x4 *)&s.wm[clr] = u32x4{0, 0, 0, 0};
@@ -587,7 +571,7 @@ __device__ void sweep_side(const Sim<L> &s, bool up, bool has, int32_t x, uint64
         uint32_t m0 = (uint32_t)Mv, m1 = (uint32_t)(Mv >> 32);
         sweep_chunk(m0, m1, (uint32_t)src, (uint32_t)(src >> 32), (uint32_t)cost & 0xFFFFFFFu, sum, cnt);
         // a storage's cost sums operator costs and may pass 2^28
-        for (uint64_t q = __ballot((cost >> 28) != 0 && (m0 | m1) != 0); q; q &= q - 1) {
+        for (uint64_t q = ballot((cost >> 28) != 0 && (m0 | m1) != 0); q; q &= q - 1) {
             const int32_t k = __builtin_ctzll(q);
             const uint64_t b = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(m0, k) |
                                ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(m1, k) << 32);
@@ -603,7 +587,7 @@ __device__ void sweep_side(const Sim<L> &s, bool up, bool has, int32_t x, uint64
         }
         const uint64_t Mi = (uint64_t)m0 | ((uint64_t)m1 << 32);
         uint64_t to = 0;
-        while (__ballot(e < end)) {
+        while (ballot(e < end)) {
             int32_t v[4];
             uint8_t st[4];
 #pragma unroll
@@ -649,8 +633,7 @@ __device__ void sweep_candidates(Sim<L> &s, int32_t n, bool both)
 }
 
 template <bool L>
-__device__ void scan_walk_lds(Sim<L> &s, uint64_t min_size, bool sampling, uint64_t tau, uint64_t &bn,
-                              u128 &bd, int32_t &bi)
+__device__ void scan_walk_lds(Sim<L> &s, uint64_t min_size, bool sampling, uint64_t tau, Best &best)
 {
     const int32_t S = s.P.S;
     int32_t n = 0;
@@ -659,18 +642,18 @@ __device__ void scan_walk_lds(Sim<L> &s, uint64_t min_size, bool sampling, uint6
         bool ok = false;
         if (x < S) {
             // every read issued before the first test
-            const uint8_t st = s.state[x], pin = s.pinned[x], cst = s.P.s_const[x];
+            const uint8_t st = s.state[x], pin = s.pinned[x];
             const int32_t lk = s.locks[x];
             const uint64_t sz = (uint64_t)s.sz[x];
-            ok = (st == ST_RESIDENT) & (lk == 0) & (pin == 0) & (cst == 0) & (sz >= min_size);
+            ok = (st == ST_RESIDENT) & (lk == 0) & (pin == 0) & (sz >= min_size);
         }
         if (ok && sampling) {
             const uint64_t key = ((uint64_t)s.eviction_no << 32) + (uint64_t)(uint32_t)x;
             ok = mix64((s.seed ^ SAMPLE_STREAM) + GOLDEN * key) < tau;
         }
-        const uint64_t m = __ballot(ok);
+        const uint64_t m = ballot(ok);
         if (s.P.sweep) {
-            const uint64_t ev = __ballot(x < S && s.state[x < S ? x : 0] == ST_EVICTED);
+            const uint64_t ev = ballot(x < S && s.state[x < S ? x : 0] == ST_EVICTED);
             if (s.lane == 0) s.ev[b / WAVE] = ev;
             if (x < S) {
                 s.rsum[x] = 0;
@@ -700,16 +683,20 @@ __device__ void scan_walk_lds(Sim<L> &s, uint64_t min_size, bool sampling, uint6
     if (s.nw > 1) __syncthreads();
     else wave_sync();
     // score every walked candidate
-    for (int32_t q = s.lane; q < n; q += WAVE) {
-        const int32_t y = s.cand[q];
+    for (int32_t b = 0; b < n; b += WAVE) {
+        const int32_t q = b + s.lane;
+        const bool has = q < n;
+        const int32_t y = s.cand[has ? q : 0];
         const int64_t m = s.sz[y];
         const int64_t stale = s.clock - s.last[y];
-        const uint64_t N = (uint64_t)(s.c0d[y] + s.rsum[q]);
-        const u128 D = (u128)(uint64_t)(s.use_m ? m : 1) * (u128)(uint64_t)(s.use_s ? stale : 1);
-        if (better(N, D, y, bn, bd, bi)) { bn = N; bd = D; bi = y; }
-        s.scores_l++;
-        s.nbr_l += s.rcnt[q];
-        s.adj_l += s.pcnt[y] + s.ccnt[y];
+        const uint64_t N = (uint64_t)(s.c0d[y] + s.rsum[has ? q : 0]);
+        const uint64_t da = s.use_m ? (uint64_t)m : 1, db = s.use_s ? (uint64_t)stale : 1;
+        take(best, has, score_est(N, da, db), N, da, db, y, 0);
+        if (has) {
+            s.scores_l++;
+            s.nbr_l += s.rcnt[q];
+            s.adj_l += s.pcnt[y] + s.ccnt[y];
+        }
     }
     wave_sync();
 }
@@ -752,41 +739,41 @@ __device__ void allocate(Sim<L> &s, int64_t need)
                 }
             }
         }
-        uint64_t bn = 0;
-        u128 bd = 0;
+        Best best;
+        best.sc = best.lo = best.hi = 0.0f;
+        best.N = 0;
+        best.da = best.db = 1;
+        best.id = best.slot = -1;
+        best.have = 0;
         int32_t bi = -1;
         for (int pass = 0; pass < 2; pass++) {
             if (pass == 1 && !(s.search & SEARCH_SAMPLE)) break;
             const bool sampling = pass == 0 && sample;
             if constexpr (L) {
                 if (s.walk) {
-                    scan_walk_lds(s, min_size, sampling, tau, bn, bd, bi);
+                    scan_walk_lds(s, min_size, sampling, tau, best);
                     goto reduce;
                 }
             }
-            for (int32_t x = s.lane; x < S; x += WAVE) {
-                if (!evictable(s, x)) continue;
-                if ((uint64_t)s.sz[x] < min_size) continue;
-                if (sampling) {
+            for (int32_t b = 0; b < S; b += WAVE) {
+                const int32_t x = b + s.lane;
+                bool ok = x < S && evictable(s, x);
+                if (!ballot(ok)) continue;
+                ok = ok && (uint64_t)s.sz[ok ? x : 0] >= min_size;
+                if (ok && sampling) {
                     const uint64_t key = ((uint64_t)s.eviction_no << 32) + (uint64_t)(uint32_t)x;
-                    if (mix64((s.seed ^ SAMPLE_STREAM) + GOLDEN * key) >= tau) continue;
+                    ok = mix64((s.seed ^ SAMPLE_STREAM) + GOLDEN * key) < tau;
                 }
-                uint64_t N;
-                u128 D;
-                score(s, x, N, D);
-                s.scores_l++;
-                if (better(N, D, x, bn, bd, bi)) { bn = N; bd = D; bi = x; }
+                uint64_t N = 0, da = 1, db = 1;
+                if (ok) {
+                    score(s, x, N, da, db);
+                    s.scores_l++;
+                }
+                take(best, ok, score_est(N, da, db), N, da, db, x, 0);
             }
         reduce:
-            // exact minimum across the wave
-            for (int m = WAVE / 2; m >= 1; m >>= 1) {
-                const uint64_t on = shfl64(bn, m);
-                const uint64_t dlo = shfl64((uint64_t)bd, m), dhi = shfl64((uint64_t)(bd >> 64), m);
-                const int32_t oi = __shfl_xor(bi, m, WAVE);
-                const u128 od = ((u128)dhi << 64) | dlo;
-                if (better(on, od, oi, bn, bd, bi)) { bn = on; bd = od; bi = oi; }
-            }
-            bi = uni(bi);
+            const int32_t j = best_lane(best);
+            bi = j >= 0 ? __builtin_amdgcn_readlane(best.id, j) : -1;
             if (bi >= 0) break;
         }
         if (bi < 0) { s.status = STATUS_OOM; return; }
@@ -812,7 +799,7 @@ __device__ void try_banish(Sim<L> &s, int32_t st)
             const int32_t v = s.P.dt[q + s.lane];
             bad = !defined(s, v) && s.state[s.P.t_storage[v]] != ST_BANISHED;
         }
-        blocked = __ballot(bad) != 0;
+        blocked = ballot(bad) != 0;
     }
     if (blocked) { s.pending[st] = 1; return; }
     s.pending[st] = 0;
@@ -934,7 +921,7 @@ __device__ void call(Sim<L> &s, int32_t o, int32_t remat)
         for (int32_t e = f_next; e < end; e += WAVE) {
             const int32_t i = e + s.lane;
             const bool undef = i < end && !defined(s, s.P.in[i]);
-            const uint64_t m = __ballot(undef);
+            const uint64_t m = ballot(undef);
             if (m) { found = e + (int32_t)__builtin_ctzll(m); break; }
         }
         found = uni(found);
@@ -957,9 +944,7 @@ __device__ void run_sim(const LogKernelArgs &a, int32_t sim, uint8_t *base, int3
     s.P = prog_global(a.progs[sp.trace]);
     const LogSlotLayout &Y = a.L;
     GAS uint8_t *gb = (GAS uint8_t *)base;
-    s.pinned = gb + Y.pinned;
     s.pending = gb + Y.pending;
-    s.locks = (GAS int32_t *)(gb + Y.locks);
     s.node = (GAS int32_t *)(gb + Y.node);
     s.sgen = (GAS int64_t *)(gb + Y.sgen);
     s.gen = (GAS int64_t *)(gb + Y.gen);
@@ -995,6 +980,8 @@ __device__ void run_sim(const LogKernelArgs &a, int32_t sim, uint8_t *base, int3
         s.rows = (LAS uint64_t *)(lds + a.lds_rows);
         s.reach = (LAS uint64_t *)(lds + a.lds_wm);
         s.ctl = (LAS int32_t *)(lds + a.lds_ctl);
+        s.pinned = (Mem<L, uint8_t>)(lds + a.lds_pinned);
+        s.locks = (Mem<L, int32_t>)(lds + a.lds_locks);
         s.last = (Mem<L, int64_t>)(lds + a.lds_last);
         s.sz = (Mem<L, const int64_t>)(lds + a.lds_sz);
     } else {
@@ -1004,6 +991,8 @@ __device__ void run_sim(const LogKernelArgs &a, int32_t sim, uint8_t *base, int3
         s.co = (Mem<L, const int32_t>)s.P.ch_off;
         s.pa = (Mem<L, const Adj<L>>)s.P.par;
         s.ca = (Mem<L, const Adj<L>>)s.P.ch;
+        s.pinned = (Mem<L, uint8_t>)(gb + Y.pinned);
+        s.locks = (Mem<L, int32_t>)(gb + Y.locks);
         s.last = (Mem<L, int64_t>)(gb + Y.last);
         s.sz = s.P.s_size;
         s.c0d = (Mem<L, int64_t>)(gb + Y.c0d);
