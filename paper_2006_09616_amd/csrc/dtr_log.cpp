@@ -52,6 +52,8 @@ struct Lowered {
     std::vector<uint8_t> s_const;
     std::vector<int32_t> par_off, par, ch_off, ch, dt_off, dt;
     std::vector<int32_t> born_off, born;   // per operator: edges its first run creates (parent, storage)
+    std::vector<dtr::LogOp> op;
+    std::vector<dtr::LogRef> inr, outr;
     int32_t sweep = 0;                     // LogProgDev::sweep
     // tensors
     std::vector<int32_t> t_storage, t_op;
@@ -377,6 +379,26 @@ private:
                 }
                 L.born_off[o + 1] = (int32_t)(L.born.size() / 2);
             }
+            // the records the kernel reads
+            L.op.resize(F);
+            for (int32_t o = 0; o < F; o++) {
+                dtr::LogOp &r = L.op[o];
+                std::memset(&r, 0, sizeof(r));
+                r.cost = L.op_cost[o];
+                r.need = L.op_need[o];
+                r.in_b = L.in_off[o];
+                r.in_e = L.in_off[o + 1];
+                r.ls_b = L.ls_off[o];
+                r.ls_e = L.ls_off[o + 1];
+                r.out_b = L.out_off[o];
+                r.out_e = L.out_off[o + 1];
+                r.rel_b = L.rel_off[o];
+                r.rel_e = L.rel_off[o + 1];
+                r.born_b = L.born_off[o];
+                r.born_e = L.born_off[o + 1];
+            }
+            for (int32_t t : L.in) L.inr.push_back({t, L.t_storage[t], L.t_op[t], 0});
+            for (int32_t t : L.out) L.outr.push_back({t, L.t_storage[t], L.t_alias[t], 0});
             // walks are swept in id order when every edge goes upwards (views
             // that read storages younger than their own can close cycles)
             L.sweep = S <= dtr::SWEEP_STORAGES;
@@ -411,7 +433,7 @@ size_t log_bytes(const Lowered &d)
            bytes_of(d.t_op) + bytes_of(d.t_alias) + bytes_of(d.op_cost) + bytes_of(d.op_need) +
            bytes_of(d.in_off) + bytes_of(d.in) + bytes_of(d.ls_off) + bytes_of(d.ls) + bytes_of(d.out_off) +
            bytes_of(d.out) + bytes_of(d.rel_off) + bytes_of(d.rel) + bytes_of(d.req) + bytes_of(d.born_off) +
-           bytes_of(d.born) + 26 * ALIGN;
+           bytes_of(d.born) + bytes_of(d.op) + bytes_of(d.inr) + bytes_of(d.outr) + 29 * ALIGN;
 }
 
 }  // namespace
@@ -610,6 +632,9 @@ int log_plan_upload(LogPlan *p, uint8_t *ws, hipStream_t st)
         D.T = d.T;
         D.F = d.F;
         D.n_req = (int32_t)d.req.size();
+        D.op = put(d.op);
+        D.inr = put(d.inr);
+        D.outr = put(d.outr);
         D.sweep = d.sweep;
         D.pad = 0;
         D.s_size = put(d.s_size);

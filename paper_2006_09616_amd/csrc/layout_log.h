@@ -11,6 +11,19 @@ namespace dtr {
 // A lowered operator log (read-only during a run).  Storages are the unit of
 // eviction; tensors are a storage's root or views of it; operators may have
 // several outputs.  CSR offsets are int32 (validated sizes).
+// An operator's numbers in one 64-byte record (one load: a word per lane), and
+// an input or output tensor with its storage and, for an input, its operator,
+// for an output, whether it is a view.
+struct __attribute__((aligned(16))) LogOp {
+    int64_t cost, need;
+    int32_t in_b, in_e, ls_b, ls_e, out_b, out_e, rel_b, rel_e, born_b, born_e, pad0, pad1;
+};
+static_assert(sizeof(LogOp) == 64, "operator record layout");
+struct __attribute__((aligned(16))) LogRef {
+    int32_t t, st, x, pad;
+};
+static_assert(sizeof(LogRef) == 16, "tensor reference layout");
+
 struct LogProgDev {
     int32_t S, T, F, n_req;
     // storages
@@ -32,6 +45,8 @@ struct LogProgDev {
     const int32_t *out_off, *out; // output tensors
     const int32_t *rel_off, *rel; // storages released after each operator, in log order
     const int32_t *req;           // [n_req] tensors still referenced at the end, ascending
+    const LogOp *op;              // [F]
+    const LogRef *inr, *outr;     // the operators' inputs and outputs
     int32_t sweep, pad;           // every edge goes from a smaller storage id to a larger: walks are swept
     const int32_t *born_off, *born; // per operator: (parent, storage) edges its first run creates
 };

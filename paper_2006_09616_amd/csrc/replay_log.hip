@@ -8,8 +8,10 @@
 //   * the eviction search scores one storage per lane per round and reduces
 //     the exact (score, id) minimum across the wave (scores N/D compared by
 //     128-bit cross-multiplication, ties to the smaller storage id);
-//   * h_DTR / h_{e*} / h_MSPS walk each candidate's evicted neighbourhood
-//     (e* or the evicted ancestors e_R, Appendix C.2; Section 4.1) with a
+//   * h_DTR / h_{e*} / h_MSPS: where the storage graph's edges all go from
+//     smaller to larger ids, the evicted neighbourhoods (e* or the evicted
+//     ancestors e_R, Appendix C.2; Section 4.1) of 64 candidates at a time are
+//     swept in id order; else each lane walks its candidate's with a
 //     lane-private queue and a lane-private visited bitset, cleared after
 //     each walk from the queue; when the batch's largest log fits, the
 //     storage states, the bitsets and the storage graph live in LDS
@@ -101,6 +103,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct ProgG {
     int32_t S, T, F, n_req;
     int32_t sweep;
+    const GAS LogOp *op;
+    const GAS LogRef *inr, *outr;
     const GAS int64_t *s_size, *s_c0;
     const GAS uint8_t *s_const;
     const GAS int32_t *par_off, *par, *ch_off, *ch, *dt_off, *dt;
@@ -119,6 +123,9 @@ __device__ __forceinline__ ProgG prog_global(const LogProgDev &d)
     g.F = d.F;
     g.n_req = d.n_req;
     g.sweep = d.sweep;
+    g.op = (const GAS LogOp *)d.op;
+    g.inr = (const GAS LogRef *)d.inr;
+    g.outr = (const GAS LogRef *)d.outr;
     g.s_size = (const GAS int64_t *)d.s_size;
     g.s_c0 = (const GAS int64_t *)d.s_c0;
     g.s_const = (const GAS uint8_t *)d.s_const;
@@ -195,7 +202,7 @@ struct Sim {
     int64_t clock, memory, peak;
     int64_t total, base, remat_cost, executed, remats, evictions, eager;
     int64_t eviction_no, cur_op;
-    int32_t status, uf_n, sp;
+    int32_t status, uf_n;
     // per-lane
     int32_t lane;
     uint32_t epoch;
@@ -825,32 +832,70 @@ __device__ void release(Sim<L> &s, int32_t st)
 
 // ---------------------------------------------------------- operators --
 
+// An operator's record in one register: lane l holds its word l & 15.
 template <bool L>
-__device__ void push(Sim<L> &s, int32_t o, int32_t remat)
+__device__ __forceinline__ int32_t op_load(const Sim<L> &s, int32_t o)
 {
-    if (s.sp >= s.P.F + 2) { s.status = STATUS_CAPACITY; return; }
-    for (int32_t e = s.P.ls_off[o]; e < s.P.ls_off[o + 1]; e++) s.locks[s.P.ls[e]] += 1;
-    GAS LogFrame *f = &s.stack[s.sp];
-    f->op = o;
-    f->next = s.P.in_off[o];
-    f->remat = remat;
-    f->pad = 0;
-    s.sp++;
+    return ((const GAS int32_t *)(s.P.op + o))[s.lane & 15];
+}
+enum { OP_COST = 0, OP_NEED = 2, OP_IN = 4, OP_LS = 6, OP_OUT = 8, OP_REL = 10, OP_BORN = 12 };
+__device__ __forceinline__ int32_t op_word(int32_t rv, int k) { return __builtin_amdgcn_readlane(rv, k); }
+__device__ __forceinline__ int64_t op_word64(int32_t rv, int k)
+{
+    return (int64_t)((uint64_t)(uint32_t)op_word(rv, k) | ((uint64_t)(uint32_t)op_word(rv, k + 1) << 32));
 }
 
-// run operator o once its inputs are defined: allocate its new storages, run,
-// free the copies of outputs already defined, unlock (Appendix C.4)
-template <bool L>
-__device__ void execute(Sim<L> &s, int32_t o, bool remat)
+// entry i of a list of tensor references, for the lanes that want one
+__device__ __forceinline__ LogRef ref_load(const GAS LogRef *list, bool want, int32_t i)
 {
-    const int64_t need = s.P.op_need[o];
+    u32x4 v = {0, 0, 0, 0};
+    if (want) v = *(const GAS u32x4 *)(list + i);
+    return LogRef{(int32_t)v.x, (int32_t)v.y, (int32_t)v.z, 0};
+}
+
+// the locks of an operator's distinct input storages, one lane each
+template <bool L>
+__device__ __forceinline__ void lock_storages(Sim<L> &s, int32_t rv, int32_t d)
+{
+    const int32_t e = op_word(rv, OP_LS + 1);
+    for (int32_t k = op_word(rv, OP_LS) + s.lane; k < e; k += WAVE) s.locks[s.P.ls[k]] += d;
+}
+
+// run operator o (record rv) once its inputs are defined: allocate its new
+// storages, run, free the copies of outputs already defined, unlock (Appendix
+// C.4).  Its outputs and input storages are read by a lane each before the
+// allocation, so that the search hides the reads; more than 64 of them take
+// the rest from memory.
+template <bool L>
+__device__ void execute(Sim<L> &s, int32_t rv, bool remat)
+{
+    const int64_t need = op_word64(rv, OP_NEED);
+    const int32_t ob = op_word(rv, OP_OUT), oe = op_word(rv, OP_OUT + 1);
+    const int32_t lb = op_word(rv, OP_LS), le = op_word(rv, OP_LS + 1);
+    const LogRef out = ref_load(s.P.outr, s.lane < oe - ob, ob + s.lane);
+    int32_t in_st = lb + s.lane < le ? s.P.ls[lb + s.lane] : -1;
     allocate(s, need);
     if (s.status) return;
-    const int32_t ib = s.P.in_off[o], ie = s.P.in_off[o + 1];
-    const int32_t ob = s.P.out_off[o], oe = s.P.out_off[o + 1];
-    for (int32_t e = s.P.ls_off[o]; e < s.P.ls_off[o + 1]; e++) s.last[s.P.ls[e]] = s.clock;
-    for (int32_t q = ob; q < oe; q++) s.last[s.P.t_storage[s.P.out[q]]] = s.clock;
-    const int64_t c = s.P.op_cost[o];
+    auto out_at = [&](int32_t q, int32_t &t, int32_t &st, int32_t &alias) {
+        const int32_t k = q - ob;
+        if (k < WAVE) {
+            t = __builtin_amdgcn_readlane(out.t, k);
+            st = __builtin_amdgcn_readlane(out.st, k);
+            alias = __builtin_amdgcn_readlane(out.x, k);
+        } else {
+            t = uni(s.P.outr[q].t);
+            st = uni(s.P.outr[q].st);
+            alias = uni(s.P.outr[q].x);
+        }
+    };
+    if (in_st >= 0) s.last[in_st] = s.clock;
+    for (int32_t k = lb + WAVE + s.lane; k < le; k += WAVE) s.last[s.P.ls[k]] = s.clock;
+    int32_t t, st, alias;
+    for (int32_t q = ob; q < oe; q++) {
+        out_at(q, t, st, alias);
+        s.last[st] = s.clock;
+    }
+    const int64_t c = op_word64(rv, OP_COST);
     s.clock += c;
     s.total += c;
     s.executed++;
@@ -859,15 +904,14 @@ __device__ void execute(Sim<L> &s, int32_t o, bool remat)
     s.memory += need;
     if (s.memory > s.peak) s.peak = s.memory;
     for (int32_t q = ob; q < oe; q++) {
-        const int32_t v = s.P.out[q];
-        if (s.P.t_alias[v]) continue;
-        const int32_t st = s.P.t_storage[v];
-        const uint8_t was = s.state[st];
-        if (was == ST_RESIDENT) { s.memory -= s.sz[st]; continue; }
+        out_at(q, t, st, alias);
+        if (alias) continue;
+        const uint8_t was = (uint8_t)uni(s.state[st]);
+        if (was == ST_RESIDENT) { s.memory -= uni64(s.sz[st]); continue; }
         s.state[st] = ST_RESIDENT;
         const int64_t g = s.sgen[st] + 1;
         s.sgen[st] = g;
-        s.gen[v] = g;
+        s.gen[t] = g;
         if (s.uf && was == ST_EVICTED) {
             const int32_t r = uf_find(s, s.node[st]);
             s.ufc[r] -= s.c0d[st];
@@ -875,64 +919,88 @@ __device__ void execute(Sim<L> &s, int32_t o, bool remat)
         }
     }
     for (int32_t q = ob; q < oe; q++) {
-        const int32_t v = s.P.out[q];
-        if (s.P.t_alias[v]) s.gen[v] = s.sgen[s.P.t_storage[v]];
+        out_at(q, t, st, alias);
+        if (alias) s.gen[t] = s.sgen[st];
     }
     if (!remat) {
         // the operator's first run creates its tensors: their costs join
         // their storages' and their edges join the graph (Appendix C.2)
         for (int32_t q = ob; q < oe; q++) {
-            const int32_t st = s.P.t_storage[s.P.out[q]];
+            out_at(q, t, st, alias);
             if (!s.P.s_const[st]) s.c0d[st] += c;
         }
-        for (int32_t b = s.P.born_off[o]; b < s.P.born_off[o + 1]; b++) {
-            const int32_t par = s.P.born[2 * b], st = s.P.born[2 * b + 1];
-            s.pcnt[st] += 1;
+        const int32_t be = op_word(rv, OP_BORN + 1);
+        for (int32_t b = op_word(rv, OP_BORN); b < be; b++) {
+            const int32_t par = s.P.born[2 * b], ch = s.P.born[2 * b + 1];
+            s.pcnt[ch] += 1;
             s.ccnt[par] += 1;
             if constexpr (L) {
-                if (s.P.sweep && s.walk && (par >> 6) == (st >> 6)) {
-                    s.rows[2 * st] |= uint64_t(1) << (par & 63);
-                    s.rows[2 * par + 1] |= uint64_t(1) << (st & 63);
+                if (s.P.sweep && s.walk && (par >> 6) == (ch >> 6)) {
+                    s.rows[2 * ch] |= uint64_t(1) << (par & 63);
+                    s.rows[2 * par + 1] |= uint64_t(1) << (ch & 63);
                 }
             }
         }
     }
     if (s.clock >= CLOCK_LIMIT) { s.status = STATUS_CLOCK; return; }
-    for (int32_t e = s.P.ls_off[o]; e < s.P.ls_off[o + 1]; e++) s.locks[s.P.ls[e]] -= 1;
+    if (in_st >= 0) s.locks[in_st] -= 1;
+    for (int32_t k = lb + WAVE + s.lane; k < le; k += WAVE) s.locks[s.P.ls[k]] -= 1;
     if (remat && s.policy == POLICY_BANISH)
-        for (int32_t e = ib; e < ie; e++) {
-            const int32_t st = s.P.t_storage[s.P.in[e]];
-            if (s.pending[st]) try_banish(s, st);
+        for (int32_t e = op_word(rv, OP_IN), ie = op_word(rv, OP_IN + 1); e < ie; e++) {
+            const int32_t in = s.P.inr[e].st;
+            if (s.pending[in]) try_banish(s, in);
         }
 }
 
 // call operator o (a rematerialization if remat), defining undefined inputs
-// first, in listed order, by calling their operators
+// first, in listed order, by calling their operators.  The current call is in
+// registers; the stack holds the calls it interrupts.
 template <bool L>
 __device__ void call(Sim<L> &s, int32_t o, int32_t remat)
 {
-    const int32_t floor = s.sp;
-    push(s, o, remat);
-    while (s.sp > floor && !s.status) {
-        const GAS LogFrame *top = &s.stack[s.sp - 1];
-        const int32_t f_op = top->op, f_next = top->next, f_remat = top->remat;
-        const int32_t end = s.P.in_off[f_op + 1];
-        int32_t found = -1;
-        for (int32_t e = f_next; e < end; e += WAVE) {
+    int32_t depth = 0;
+    int32_t rv = op_load(s, o), next = op_word(rv, OP_IN);
+    lock_storages(s, rv, 1);
+    for (;;) {
+        const int32_t end = op_word(rv, OP_IN + 1);
+        int32_t found = -1, found_op = 0;
+        for (int32_t e = next; e < end; e += WAVE) {
             const int32_t i = e + s.lane;
-            const bool undef = i < end && !defined(s, s.P.in[i]);
+            const LogRef in = ref_load(s.P.inr, i < end, i);
+            bool undef = false;
+            if (i < end) {
+                const int64_t g = s.gen[in.t], sg = s.sgen[in.st];
+                undef = !((s.state[in.st] == ST_RESIDENT) & (g == sg));
+            }
             const uint64_t m = ballot(undef);
-            if (m) { found = e + (int32_t)__builtin_ctzll(m); break; }
+            if (m) {
+                const int32_t j = (int32_t)__builtin_ctzll(m);
+                found = e + j;
+                found_op = __builtin_amdgcn_readlane(in.x, j);
+                break;
+            }
         }
-        found = uni(found);
         if (found >= 0) {
-            s.stack[s.sp - 1].next = found + 1;
-            push(s, s.P.t_op[s.P.in[found]], 1);
+            if (depth >= s.P.F + 2) { s.status = STATUS_CAPACITY; return; }
+            GAS LogFrame *f = &s.stack[depth++];
+            f->op = o;
+            f->next = found + 1;
+            f->remat = remat;
+            f->pad = 0;
+            o = found_op;
+            remat = 1;
+            rv = op_load(s, o);
+            next = op_word(rv, OP_IN);
+            lock_storages(s, rv, 1);
             continue;
         }
-        execute(s, f_op, f_remat != 0);
-        if (s.status) return;
-        s.sp--;
+        execute(s, rv, remat != 0);
+        if (s.status || depth == 0) return;
+        const GAS LogFrame *f = &s.stack[--depth];
+        o = uni(f->op);
+        next = uni(f->next);
+        remat = uni(f->remat);
+        rv = op_load(s, o);
     }
 }
 
@@ -1030,7 +1098,6 @@ __device__ void run_sim(const LogKernelArgs &a, int32_t sim, uint8_t *base, int3
     s.eviction_no = s.cur_op = 0;
     s.status = STATUS_OK;
     s.uf_n = 0;
-    s.sp = 0;
 
     const int32_t S = s.P.S, T = s.P.T, F = s.P.F;
     s.n_storages = S;
