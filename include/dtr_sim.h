@@ -176,9 +176,10 @@ typedef struct {
 /* Traces only, testing aids for the walk heuristics (h_DTR, h_{e*}, h_MSPS
  * and the family members with the e* cost): bits 8-11 set the wavefronts per
  * workgroup (1..8; 0 = chosen from the trace sizes), and
- * DTR_OPT_WALK_QUEUE_SMALL gives each lane a queue of 16 members, so that
- * larger neighbourhoods take the whole-wavefront walk.  Results are
- * identical either way. */
+ * DTR_OPT_WALK_QUEUE_SMALL walks candidates lane by lane on traces of every
+ * size (short ones are swept otherwise) and gives each lane a queue of 16
+ * members, so that larger neighbourhoods take the whole-wavefront walk.
+ * Results are identical either way. */
 #define DTR_OPT_WALK_QUEUE_SMALL 4
 #define DTR_OPT_WALK_WAVES_SHIFT 8
 #define DTR_OPT_WALK_WAVES(w) ((w) << DTR_OPT_WALK_WAVES_SHIFT)
@@ -323,8 +324,8 @@ int dtr_log_create(const dtr_log *logs, int32_t n_logs,
  *                  others join its e* / e_R walk scans; else 4 for traces
  *                  with exact h_DTR^eq simulations (a simulation per
  *                  wavefront);
- * lds_bytes        dynamic LDS per workgroup (0: the kernels' static LDS only,
- *                  or walk state in device memory).
+ * lds_bytes        operator logs: dynamic LDS per workgroup (0: walk state in
+ *                  device memory); traces: 0.
  * Returns DTR_EINVAL for a NULL argument.  No device work. */
 typedef struct {
     int32_t n_slots;

@@ -356,7 +356,8 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     take(L.uf_remap, need_uf ? 4 * ((size_t)L.ucap + dtr::UF_LDS) : 0);
     take(L.stack, sizeof(dtr::StackFrame) * (size_t)(n + 1));
     // walk heuristics: wavefronts per workgroup (more for large traces, whose
-    // pools are long), a visited bitmap and a member queue per lane
+    // pools are long; two for the smallest, one for each side of a sweep), a
+    // visited bitmap and a member queue per lane
     int32_t ww = opt ? (opt->flags >> DTR_OPT_WALK_WAVES_SHIFT) & 15 : 0;
     if (ww == 0) ww = n_max >= 8192 ? dtr::MAX_WALK_WAVES : n_max >= 1024 ? 4 : p.sweep_chunks > 0 ? 2 : 1;
     L.walk_waves = need_walk ? ww : 1;
@@ -438,8 +439,9 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     for (int c = 0; c < dtr::N_GROUPS; c++) p.class_count[c] = 0;
     for (int32_t i = 0; i < n_sims; i++) p.class_count[cls(i)]++;
     // groups whose traces are all small keep their state words in LDS; under
-    // h_DTR^eq only if the group is resident at once that way (a workgroup per
-    // compute unit, or more)
+    // h_DTR^eq only if the group is resident at once that way: above 96
+    // tensors a compute unit holds one workgroup of four simulations instead
+    // of two, which a larger batch would pay for with its throughput
     int32_t group_n[dtr::N_GROUPS] = {0, 0, 0, 0, 0, 0};
     for (int32_t i = 0; i < n_sims; i++)
         group_n[cls(i)] = std::max(group_n[cls(i)], p.traces[sims[i].trace].n);

@@ -26,9 +26,12 @@
 //    an evicted tensor are found in parallel and merged at once;
 //    rematerialization subtracts c0 and detaches the tensor (split
 //    approximation); the node pool is compacted when full;
-//  * h_DTR / h_{e*}: each lane walks its candidate's evicted ancestors and
-//    descendants (e*, Appendix C.2) with lane-private epoch stamps, taking the
-//    next candidate as soon as its walk ends.
+//  * h_DTR / h_{e*} / h_MSPS: the evicted ancestors and descendants (e*,
+//    Appendix C.2) of 64 candidates at a time are swept in operation order
+//    (traces of up to SWEEP_OPS operations); on longer traces each lane walks
+//    its candidate's, taking the next one as soon as its walk ends;
+//  * small traces (SMALL_TENSORS) keep the state words and the top of the
+//    rematerialization stack in LDS, in kernels of their own.
 //
 // Scores N/D are compared exactly by 128-bit cross-multiplication; ties go to
 // the smaller tensor id.  Last-access times are not kept per tensor: a tensor
@@ -2664,9 +2667,13 @@ static hipError_t launch(const dtr::KernelArgs &a, hipStream_t stream)
     int64_t lds = small_lds_bytes(small(HC) ? a.small_n : 0) * lds_waves(HC);
     if (cls(HC) == HC_WALK) lds += sweep_lds_bytes(a.sweep_chunks, waves);
     if (lds > 0) {
-        // (a workgroup may take more than the default 64 KB, static LDS included)
+        // a workgroup may take more than the default 64 KB, static LDS
+        // included; always allowed all that the static LDS leaves of a compute
+        // unit's, so that launches of several threads agree
+        constexpr int rest = (160 << 10) - (int)(sizeof(UfNode) * (cls(HC) == HC_EQ ? UF_LDS * lds_waves(HC) : CTL_NODES) +
+                                                 sizeof(PoolSlotL) * POOL_LDS * lds_waves(HC));
         const hipError_t e = hipFuncSetAttribute((const void *)replay_kernel<HC>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, rest);
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(replay_kernel<HC>, grid, blk, (uint32_t)lds, stream, a);
