@@ -356,10 +356,16 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     take(L.uf_remap, need_uf ? 4 * ((size_t)L.ucap + dtr::UF_LDS) : 0);
     take(L.stack, sizeof(dtr::StackFrame) * (size_t)(n + 1));
     // walk heuristics: wavefronts per workgroup (more for large traces, whose
-    // pools are long; two for the smallest, one for each side of a sweep), a
-    // visited bitmap and a member queue per lane
+    // pools are long), a visited bitmap and a member queue per lane.  Where
+    // traces are swept: two, one for each side, while a scan has at most 64
+    // candidates (a chain of 66 tensors 0.42 ms with 2, 0.43 with 4), four from
+    // 256 tensors on (ResNet, 604: without releases 24.1 ms with 2, 18.6 with 4
+    // and with 8; transformer, 1108: 21.3, 17.4 and 23.5, whose eight reach
+    // masks leave room for one workgroup a compute unit)
     int32_t ww = opt ? (opt->flags >> DTR_OPT_WALK_WAVES_SHIFT) & 15 : 0;
-    if (ww == 0) ww = n_max >= 8192 ? dtr::MAX_WALK_WAVES : n_max >= 1024 ? 4 : p.sweep_chunks > 0 ? 2 : 1;
+    if (ww == 0) ww = n_max >= 8192 ? dtr::MAX_WALK_WAVES : n_max >= (p.sweep_chunks > 0 ? 256 : 1024) ? 4
+                                                          : p.sweep_chunks > 0                            ? 2
+                                                                                                          : 1;
     L.walk_waves = need_walk ? ww : 1;
     const size_t lanes = (size_t)L.walk_waves * dtr::WAVE;
     L.vis_words = (int64_t)((n + 127) / 128 * 4);
