@@ -454,10 +454,10 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     for (int c = 0; c < dtr::N_GROUPS; c++) {
         if (group_n[c] > dtr::SMALL_TENSORS || (c % 3 == 1 && !sweep)) continue;
         const int32_t sn = std::max(2, (group_n[c] + 1) / 2 * 2);
-        if (c == 0) {
-            const int64_t wg = dtr::EQ_WAVES * (dtr::small_lds_bytes(sn) + dtr::eq_wave_lds_bytes());
-            if (p.class_count[c] > cus * dtr::EQ_WAVES * ((160 << 10) / wg)) continue;
-        }
+        // eight reach masks of a long trace leave no room for the state words
+        const int64_t wg = dtr::static_lds_bytes(c) + dtr::dynamic_lds_bytes(c, p.sweep_chunks, L.walk_waves, sn);
+        if (wg > dtr::LDS_BYTES) continue;
+        if (c == 0 && p.class_count[c] > cus * dtr::EQ_WAVES * (dtr::LDS_BYTES / wg)) continue;
         p.small_n[c] = sn;
     }
 

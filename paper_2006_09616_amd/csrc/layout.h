@@ -195,9 +195,6 @@ struct __attribute__((aligned(16))) UfNode {
     int32_t size;
 };
 
-// static LDS of an h_DTR^eq wavefront: nodes and (padded) pool slots
-constexpr int64_t eq_wave_lds_bytes() { return UF_LDS * (int64_t)sizeof(UfNode) + POOL_LDS * 80; }
-
 // simulation groups, one kernel specialisation each: heuristic class
 // (union-find neighbourhood, neighbourhood walk, none), plus 3 with the
 // search approximations on
@@ -222,6 +219,26 @@ constexpr int64_t sweep_lds_bytes(int64_t chunks, int64_t waves)
 constexpr int SMALL_TENSORS = 2048;
 constexpr int SMALL_STACK = 16;
 constexpr int64_t small_lds_bytes(int64_t n) { return n > 0 ? (8 * n + 15) / 16 * 16 + SMALL_STACK * (int64_t)sizeof(StackFrame) : 0; }
+
+// LDS of a compute unit, and the most one workgroup may take
+constexpr int64_t LDS_BYTES = 160 << 10;
+constexpr int64_t WALK_CTL_BYTES = 2656;       // the walk heuristics' control block, in whole UfNodes
+// simulations per workgroup of a group's kernel
+constexpr int group_sims(int group) { return group == 0 ? EQ_WAVES : 1; }
+// a workgroup's static LDS: the pool head of each of its simulations, and
+// their union-find nodes or the walks' control block
+constexpr int64_t static_lds_bytes(int group)
+{
+    return group_sims(group) * ((group % 3 == 0 ? UF_LDS * (int64_t)sizeof(UfNode) : 0) + POOL_LDS * 80) +
+           (group % 3 == 1 ? WALK_CTL_BYTES : 0);
+}
+// its dynamic LDS: the sweeps' arrays (walk heuristics), then the state words
+// and stack top of each of its simulations (small traces)
+constexpr int64_t dynamic_lds_bytes(int group, int64_t sweep_chunks, int64_t walk_waves, int64_t small_n)
+{
+    return (group % 3 == 1 ? sweep_lds_bytes(sweep_chunks, walk_waves) : 0) +
+           group_sims(group) * small_lds_bytes(small_n);
+}
 
 struct KernelArgs {
     const TraceDev *traces;

@@ -519,6 +519,7 @@ struct WalkCtl {
 };
 enum { CMD_WALK = 1, CMD_DONE = 2 };
 constexpr int CTL_NODES = (int)((sizeof(WalkCtl) + sizeof(UfNode) - 1) / sizeof(UfNode));
+static_assert(CTL_NODES * sizeof(UfNode) == WALK_CTL_BYTES, "the plan's LDS sums count the control block");
 
 // Order this wavefront's LDS and global accesses (what a workgroup barrier
 // gives a one-wave workgroup) without waiting for the other wavefronts.
@@ -531,6 +532,7 @@ __device__ __forceinline__ void wave_sync()
 // wavefronts per workgroup that hold simulations of their own (each with its
 // own LDS pool and node arrays): the exact h_DTR^eq kernel's four, else one
 __host__ __device__ constexpr int lds_waves(int hc) { return cls(hc) == HC_EQ && !approx(hc) ? EQ_WAVES : 1; }
+static_assert(lds_waves(HC_EQ) == group_sims(0) && lds_waves(HC_EQ | HC_APPROX) == group_sims(3), "workgroup shapes");
 
 // the simulating wavefront's synchronization: wavefront-local where its
 // workgroup holds other wavefronts (walk heuristics, h_DTR^eq), a workgroup
@@ -2664,16 +2666,15 @@ static hipError_t launch(const dtr::KernelArgs &a, hipStream_t stream)
     const int64_t waves = cls(HC) == HC_WALK ? a.L.walk_waves : lds_waves(HC);
     // h_DTR^eq: a slot per wavefront; the others: one per workgroup
     const dim3 grid((uint32_t)((a.n_slots + lds_waves(HC) - 1) / lds_waves(HC))), blk((uint32_t)(WAVE * waves));
-    int64_t lds = small_lds_bytes(small(HC) ? a.small_n : 0) * lds_waves(HC);
-    if (cls(HC) == HC_WALK) lds += sweep_lds_bytes(a.sweep_chunks, waves);
+    constexpr int group = cls(HC) + (approx(HC) ? 3 : 0);
+    const int64_t lds = dynamic_lds_bytes(group, a.sweep_chunks, waves, small(HC) ? a.small_n : 0);
     if (lds > 0) {
         // a workgroup may take more than the default 64 KB, static LDS
         // included; always allowed all that the static LDS leaves of a compute
         // unit's, so that launches of several threads agree
-        constexpr int rest = (160 << 10) - (int)(sizeof(UfNode) * (cls(HC) == HC_EQ ? UF_LDS * lds_waves(HC) : CTL_NODES) +
-                                                 sizeof(PoolSlotL) * POOL_LDS * lds_waves(HC));
         const hipError_t e = hipFuncSetAttribute((const void *)replay_kernel<HC>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, rest);
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)(LDS_BYTES - static_lds_bytes(group)));
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(replay_kernel<HC>, grid, blk, (uint32_t)lds, stream, a);

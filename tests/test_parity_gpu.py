@@ -538,6 +538,26 @@ def test_small_trace_limits(gpu, oracle_lib):
         compare(gpu.run(traces, specs), oracle_lib.run(traces, specs), specs, f"small traces {key}")
 
 
+@pytest.mark.parametrize("waves,long", [(8, False), (0, True)])
+def test_long_swept_traces_at_eight_wavefronts(gpu, oracle_lib, waves, long):
+    """Swept traces of 1921 to 2048 operations and at most 2048 tensors with
+    eight wavefronts a workgroup: asked for by the option, or beside a trace
+    of 8192 tensors under another class of heuristics; and with the search
+    approximations beside an exact group."""
+    traces = [W.random_program(5600 + s, n_ops=F, max_in=3, max_size=9, max_cost=9, window=40)
+              for s, F in enumerate((1921, 2047, 2048, 1440))]
+    rows = [(i, h, int(W.natural_peak(t) * 0.85), i, W.POLICY_EAGER, search) for i, t in enumerate(traces)
+            for h in (W.H_DTR, W.H_MSPS) for search in (0, 3) if search == 0 or i != 1]
+    if long:
+        traces.append(W.chain_trace(4096))
+        assert traces[-1].n_tensors == 8192
+        rows += [(4, W.H_LRU, 2000, 0, W.POLICY_EAGER, 0), (4, W.H_EQ, 3000, 0, W.POLICY_EAGER, 0)]
+    specs = specs_of(rows)
+    print(f"long swept traces, waves {waves}, long {long}: {len(specs)} sims", flush=True)
+    compare(gpu.run(traces, specs, flags=gpu.opt_walk_waves(waves)), oracle_lib.run(traces, specs), specs,
+            f"long swept traces waves={waves} long={long}")
+
+
 _EQ_BATCH = {}
 
 

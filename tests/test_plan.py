@@ -1,0 +1,89 @@
+"""What a batch launches, computed on the CPU: the library's host code built
+against a recorded device (tests/host_plan.cpp), so that limits of workgroups
+and LDS are checked for batches of every shape without a GPU."""
+import ctypes as C
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2006_09616_amd import dtr as D
+from paper_2006_09616_amd import workloads as W
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CSRC = os.path.join(ROOT, "paper_2006_09616_amd", "csrc")
+LDS = 160 * 1024
+FIELDS = ["group", "sims", "slots", "slot_bytes", "waves", "sweep_chunks", "small_n", "lds_static", "lds_dynamic"]
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    if not shutil.which("g++") or not os.path.isdir("/opt/rocm/include"):
+        pytest.skip("no g++ or HIP headers")
+    so = tmp_path_factory.mktemp("plan") / "libplan.so"
+    res = subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__",
+                          "-include", "dtr_sim.h", "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+                          "-I", CSRC, "-o", str(so), os.path.join(HERE, "host_plan.cpp"),
+                          os.path.join(CSRC, "dtr_sim.cpp"), os.path.join(CSRC, "dtr_log.cpp")],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-3000:]
+    lib = C.CDLL(str(so))
+    lib.dtr_sim_last_error.restype = C.c_char_p
+    vp, i32, sz = C.c_void_p, C.c_int32, C.c_size_t
+    for kind in ("dtr_sim", "dtr_log"):
+        getattr(lib, kind + "_workspace_bytes").argtypes = [vp, i32, vp, i32, vp, C.POINTER(sz)]
+        getattr(lib, kind + "_create").argtypes = [vp, i32, vp, i32, vp, vp, sz, vp, C.POINTER(vp)]
+    for f in (lib.dtr_sim_run, lib.dtr_sim_run_static):
+        f.argtypes = [vp, vp]
+    lib.dtr_sim_destroy.argtypes = [vp]
+    lib.plan_launches.argtypes = [vp, i32]
+
+    def launches(programs, specs, logs=False, flags=0):
+        opts = {"flags": flags} if flags else None
+        p = (D._PackedLogs if logs else D._Packed)(programs, specs, opts)
+        size, h = sz(0), vp()
+        kind = "dtr_log" if logs else "dtr_sim"
+        check = lambda rc: pytest.fail(lib.dtr_sim_last_error().decode()) if rc else None
+        check(getattr(lib, kind + "_workspace_bytes")(*p.args(), C.byref(size)))
+        ws = np.empty(size.value + 256, np.uint8)               # only the tables at its head are touched
+        at = (ws.ctypes.data + 255) // 256 * 256
+        check(getattr(lib, kind + "_create")(*p.args(), at, size, None, C.byref(h)))
+        check((lib.dtr_sim_run_static if flags & D.OPT_STATIC_SCRATCH else lib.dtr_sim_run)(h, None))
+        out = (C.c_int64 * (len(FIELDS) * 16))()
+        n = lib.plan_launches(out, 16)
+        lib.dtr_sim_destroy(h)
+        rows = [dict(zip(FIELDS, out[len(FIELDS) * i:])) for i in range(n)]
+        assert n > 0 and sum(r["sims"] for r in rows) == len(specs)
+        for r in rows:
+            assert r["lds_static"] + r["lds_dynamic"] <= LDS, r
+        return rows
+
+    return launches
+
+
+def _batch(*parts):
+    """Specs of (trace, heuristic, simulations[, search]) parts."""
+    return W.make_specs([(t, h, 50 + k, k, W.POLICY_EAGER, s[0] if s else 0)
+                         for t, h, n, *s in parts for k in range(n)])
+
+
+LONG = W.chain_trace(4096)                   # 8192 tensors
+
+
+@pytest.mark.parametrize("n", [945, 959, 960, 999, 1000, 1023])
+def test_workgroups_fit_at_every_wavefront_count(plan, n):
+    """Chains of 1892 to 2048 operations, swept with their state in LDS at few
+    wavefronts, stay within a workgroup's LDS at every number of wavefronts,
+    alone, with the search approximations, and beside a trace of 8192 tensors
+    under a heuristic of any class."""
+    tr = W.chain_trace(n)
+    assert tr.n_tensors <= 2048 and tr.n_ops <= 2048
+    for search in (0, 3):
+        for waves in (0, 1, 2, 4, 5, 6, 7, 8):
+            plan([tr], _batch((0, W.H_DTR, 3, search)), flags=D.opt_walk_waves(waves))
+        for h in (W.H_EQ, W.H_LRU, W.H_DTR):
+            plan([tr, LONG], _batch((0, W.H_DTR, 3, search), (1, h, 2)))
+            plan([tr, LONG, W.chain_trace(700)], _batch((0, W.H_MSPS, 3), (1, h, 2), (2, W.H_DTR, 2, 3)))
