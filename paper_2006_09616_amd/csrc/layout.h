@@ -205,9 +205,10 @@ constexpr int PROGRESS_OFFSET = 32;
 constexpr int COUNTER_WORDS = PROGRESS_OFFSET / 4 + 2;
 constexpr int PROGRESS_STEP = 4096;
 
+// a multiple of 16 (what follows it holds 16-byte quads)
 constexpr int64_t sweep_lds_bytes(int64_t chunks, int64_t waves)
 {
-    return chunks * (8 + 4 * WAVE + waves * 8 * WAVE);
+    return (chunks * (8 + 4 * WAVE + waves * 8 * WAVE) + 15) / 16 * 16;
 }
 
 // Traces of up to this many tensors keep their state words and the first

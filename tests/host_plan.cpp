@@ -15,6 +15,7 @@
 struct PlanLaunch {
     int64_t group;           // -1: operator logs
     int64_t sims, slots, slot_bytes, waves, sweep_chunks, small_n, lds_static, lds_dynamic;
+    int64_t small_at;        // where the state words and stacks start in the dynamic LDS
 };
 static std::vector<PlanLaunch> launches;
 static std::vector<uint8_t> scratch(DTR_STATIC_SCRATCH_BYTES + 256);
@@ -52,12 +53,13 @@ hipError_t dtr_launch_group(const dtr::KernelArgs *a, int32_t group, hipStream_t
 {
     launches.push_back({group, a->n_sims, a->n_slots, a->L.bytes, group % 3 == 1 ? a->L.walk_waves : 1, a->sweep_chunks,
                         a->small_n, dtr::static_lds_bytes(group),
-                        dtr::dynamic_lds_bytes(group, a->sweep_chunks, a->L.walk_waves, a->small_n)});
+                        dtr::dynamic_lds_bytes(group, a->sweep_chunks, a->L.walk_waves, a->small_n),
+                        dtr::dynamic_lds_bytes(group, a->sweep_chunks, a->L.walk_waves, 0)});
     return hipSuccess;
 }
 hipError_t dtr_launch_log(const dtr::LogKernelArgs *a, hipStream_t)
 {
-    launches.push_back({-1, a->n_sims, a->n_slots, a->L.bytes, a->waves, 0, 0, 0, a->lds_bytes});
+    launches.push_back({-1, a->n_sims, a->n_slots, a->L.bytes, a->waves, 0, 0, 0, a->lds_bytes, 0});
     return hipSuccess;
 }
 

@@ -558,6 +558,20 @@ def test_long_swept_traces_at_eight_wavefronts(gpu, oracle_lib, waves, long):
             f"long swept traces waves={waves} long={long}")
 
 
+@pytest.mark.parametrize("layers", [16, 90, 150, 600])
+def test_odd_chunk_counts(gpu, oracle_lib, layers):
+    """Deep rematerialization under the walk heuristics on chains whose
+    operations fill an odd number of 64-operation chunks (the stack follows
+    the sweeps' arrays in LDS), exact and approximate search."""
+    tr = W.chain_trace(layers)
+    assert (tr.n_ops + 63) // 64 % 2 == 1
+    for search in (0, 3):
+        specs = specs_of([(0, h, b, b, W.POLICY_EAGER, search) for h in WALK_H
+                          for b in (layers // 8 + 4, layers // 4 + 4, layers)])
+        print(f"odd chunks {layers} {search}: {len(specs)} sims", flush=True)
+        compare(gpu.run([tr], specs), oracle_lib.run([tr], specs), specs, f"odd chunks {layers} search {search}")
+
+
 _EQ_BATCH = {}
 
 

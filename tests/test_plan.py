@@ -16,7 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(ROOT, "paper_2006_09616_amd", "csrc")
 LDS = 160 * 1024
-FIELDS = ["group", "sims", "slots", "slot_bytes", "waves", "sweep_chunks", "small_n", "lds_static", "lds_dynamic"]
+FIELDS = ["group", "sims", "slots", "slot_bytes", "waves", "sweep_chunks", "small_n", "lds_static", "lds_dynamic",
+          "small_at"]
 
 
 @pytest.fixture(scope="module")
@@ -87,3 +88,14 @@ def test_workgroups_fit_at_every_wavefront_count(plan, n):
         for h in (W.H_EQ, W.H_LRU, W.H_DTR):
             plan([tr, LONG], _batch((0, W.H_DTR, 3, search), (1, h, 2)))
             plan([tr, LONG, W.chain_trace(700)], _batch((0, W.H_MSPS, 3), (1, h, 2), (2, W.H_DTR, 2, 3)))
+
+
+@pytest.mark.parametrize("n", [8, 31, 32, 64, 96, 600, 992, 1000])
+@pytest.mark.parametrize("waves", [0, 1, 3, 4])
+def test_stacks_in_lds_start_at_a_quad(plan, n, waves):
+    """The state words and stacks (16-byte quads) follow the sweeps' arrays at
+    a multiple of 16 bytes, for odd and even numbers of 64-operation chunks."""
+    for search in (0, 3):
+        (row,) = plan([W.chain_trace(n)], _batch((0, W.H_DTR, 2, search)), flags=D.opt_walk_waves(waves))
+        assert row["small_n"] > 0 and row["sweep_chunks"] == (2 * n + 63) // 64
+        assert row["small_at"] % 16 == 0, row
