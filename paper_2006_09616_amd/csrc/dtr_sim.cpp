@@ -287,10 +287,10 @@ struct Plan {
     dtr::SlotLayout L{};
     int32_t n_slots = 0;
     bool static_only = false;        // runs only through dtr_sim_run_static: no slots in the workspace
-    int32_t small_n[dtr::N_GROUPS] = {0, 0, 0, 0, 0, 0};   // per group: state words kept in LDS (0: in the slot)
-    int32_t sweep_chunks = 0;        // of the longest swept trace (0: none)
+    // per group: simulations, wavefronts per workgroup (walk heuristics),
+    // chunks of the longest swept trace, state words kept in LDS (0: in the slot)
+    int32_t count[dtr::N_GROUPS] = {}, waves[dtr::N_GROUPS] = {}, chunks[dtr::N_GROUPS] = {}, small_n[dtr::N_GROUPS] = {};
     std::vector<int32_t> order;
-    int32_t class_count[dtr::N_GROUPS] = {0, 0, 0, 0, 0, 0};
 };
 
 template <class T>
@@ -324,6 +324,8 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     // a small lane queue asks for the lane walks and the whole-wavefront ones
     const bool sweep = !(opt && (opt->flags & DTR_OPT_WALK_QUEUE_SMALL));
     int32_t n_max = 1;
+    std::vector<int32_t> group(n_sims);
+    int32_t group_n[dtr::N_GROUPS] = {};             // tensors of each group's largest trace
     for (int32_t i = 0; i < n_sims; i++) {
         const dtr_sim_spec &s = sims[i];
         if (s.trace < 0 || s.trace >= n_traces)
@@ -332,13 +334,38 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
         need_banish |= s.policy == DTR_POLICY_BANISH;
         need_uf |= heuristic_class(s.heuristic) == 0;
         need_walk |= heuristic_class(s.heuristic) == 1;
-        n_max = std::max(n_max, p.traces[s.trace].n);
         Derived &d = p.traces[s.trace];
-        if (heuristic_class(s.heuristic) == 1 && sweep && d.F > 0 && d.F <= dtr::SWEEP_OPS &&
-            2 * (int64_t)d.n + 128 <= dtr::SWEEP_MAX_POOL) {
-            if (d.sw.empty()) make_sweep(d);
-            p.sweep_chunks = std::max(p.sweep_chunks, (d.F + dtr::WAVE - 1) / dtr::WAVE);
+        n_max = std::max(n_max, d.n);
+        int32_t g = heuristic_class(s.heuristic) == 0 ? dtr::GROUP_EQ : dtr::GROUP_SIMPLE;
+        if (heuristic_class(s.heuristic) == 1) {
+            const bool swept = sweep && d.F <= dtr::SWEEP_OPS && 2 * (int64_t)d.n + 128 <= dtr::SWEEP_MAX_POOL;
+            g = swept ? dtr::GROUP_SWEEP : dtr::GROUP_WALK;
+            if (swept && d.sw.empty()) make_sweep(d);
         }
+        if (s.search) g += dtr::N_CLASSES;
+        group[i] = g;
+        p.count[g]++;
+        group_n[g] = std::max(group_n[g], d.n);
+        if (g % dtr::N_CLASSES == dtr::GROUP_SWEEP)
+            p.chunks[g] = std::max(p.chunks[g], (d.F + dtr::WAVE - 1) / dtr::WAVE);
+    }
+    // walk heuristics: wavefronts per workgroup, from each group's largest
+    // trace.  Lane walks: more for large traces, whose pools are long.  Sweeps:
+    // two, one for each side, while a scan has at most 64 candidates (a chain
+    // of 66 tensors 0.42 ms with 2, 0.43 with 4), four from 256 tensors on
+    // (ResNet, 604: without releases 24.1 ms with 2, 18.6 with 4 and with 8;
+    // transformer, 1108: 21.3, 17.4 and 23.5, whose eight reach masks leave
+    // room for one workgroup a compute unit)
+    int32_t ww_max = 1, ww_min = dtr::MAX_WALK_WAVES;
+    for (int g = 0; g < dtr::N_GROUPS; g++) {
+        p.waves[g] = 1;
+        if (!dtr::group_walks(g) || p.count[g] == 0) continue;
+        int32_t ww = opt ? (opt->flags >> DTR_OPT_WALK_WAVES_SHIFT) & 15 : 0;
+        if (ww == 0 && g % dtr::N_CLASSES == dtr::GROUP_SWEEP) ww = group_n[g] >= 256 ? 4 : 2;
+        else if (ww == 0) ww = group_n[g] >= 8192 ? dtr::MAX_WALK_WAVES : group_n[g] >= 1024 ? 4 : 1;
+        p.waves[g] = ww;
+        ww_max = std::max(ww_max, ww);
+        ww_min = std::min(ww_min, ww);
     }
     // slot layout
     dtr::SlotLayout &L = p.L;
@@ -355,18 +382,8 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     take(L.nodes, sizeof(dtr::UfNode) * (size_t)L.ucap);
     take(L.uf_remap, need_uf ? 4 * ((size_t)L.ucap + dtr::UF_LDS) : 0);
     take(L.stack, sizeof(dtr::StackFrame) * (size_t)(n + 1));
-    // walk heuristics: wavefronts per workgroup (more for large traces, whose
-    // pools are long), a visited bitmap and a member queue per lane.  Where
-    // traces are swept: two, one for each side, while a scan has at most 64
-    // candidates (a chain of 66 tensors 0.42 ms with 2, 0.43 with 4), four from
-    // 256 tensors on (ResNet, 604: without releases 24.1 ms with 2, 18.6 with 4
-    // and with 8; transformer, 1108: 21.3, 17.4 and 23.5, whose eight reach
-    // masks leave room for one workgroup a compute unit)
-    int32_t ww = opt ? (opt->flags >> DTR_OPT_WALK_WAVES_SHIFT) & 15 : 0;
-    if (ww == 0) ww = n_max >= 8192 ? dtr::MAX_WALK_WAVES : n_max >= (p.sweep_chunks > 0 ? 256 : 1024) ? 4
-                                                          : p.sweep_chunks > 0                            ? 2
-                                                                                                          : 1;
-    L.walk_waves = need_walk ? ww : 1;
+    // a visited bitmap and a member queue per lane of the walk heuristics
+    L.walk_waves = ww_max;
     const size_t lanes = (size_t)L.walk_waves * dtr::WAVE;
     L.vis_words = (int64_t)((n + 127) / 128 * 4);
     L.vis_bytes = (int64_t)((n + 15) / 16 * 16);
@@ -395,7 +412,7 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
         return true;
     }();
     int64_t slots = opt && opt->slots > 0 ? opt->slots
-                                          : (int64_t)cus * (walk_only ? std::max<int64_t>(1, 16 / L.walk_waves) : 16);
+                                          : (int64_t)cus * (walk_only ? std::max<int64_t>(1, 16 / ww_min) : 16);
     const int64_t cap_bytes = int64_t(48) << 30;     // bound slot memory
     slots = std::min<int64_t>(slots, std::max<int64_t>(1, cap_bytes / std::max<int64_t>(1, L.bytes)));
     slots = std::min<int64_t>(slots, std::max<int32_t>(1, n_sims));
@@ -409,23 +426,22 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     // then the rest trace by trace (longest first), each trace's tightest
     // first, so that the simulations of one trace run side by side and share
     // its tables in the caches.
-    auto cls = [&](int32_t i) { return heuristic_class(sims[i].heuristic) + (sims[i].search ? 3 : 0); };
     auto bucket = [&](int32_t i) {
         const uint64_t pk = (uint64_t)std::max<int64_t>(1, p.traces[sims[i].trace].peak);
         return (unsigned __int128)(uint64_t)sims[i].budget * 1024u / pk;
     };
     std::map<std::pair<int32_t, int32_t>, unsigned __int128> tightest;     // (trace, group) -> bucket
     for (int32_t i = 0; i < n_sims; i++) {
-        const auto key = std::make_pair(sims[i].trace, cls(i));
+        const auto key = std::make_pair(sims[i].trace, group[i]);
         const auto it = tightest.find(key);
         if (it == tightest.end() || bucket(i) < it->second) tightest[key] = bucket(i);
     }
     std::vector<uint8_t> first(n_sims);
-    for (int32_t i = 0; i < n_sims; i++) first[i] = bucket(i) == tightest[std::make_pair(sims[i].trace, cls(i))];
+    for (int32_t i = 0; i < n_sims; i++) first[i] = bucket(i) == tightest[std::make_pair(sims[i].trace, group[i])];
     p.order.resize(n_sims);
     std::iota(p.order.begin(), p.order.end(), 0);
     std::stable_sort(p.order.begin(), p.order.end(), [&](int32_t a, int32_t b) {
-        if (cls(a) != cls(b)) return cls(a) < cls(b);
+        if (group[a] != group[b]) return group[a] < group[b];
         if (first[a] != first[b]) return first[a] > first[b];
         const Derived &ta = p.traces[sims[a].trace], &tb = p.traces[sims[b].trace];
         if (!first[a]) {
@@ -442,23 +458,18 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
         if (ra != rb) return ra < rb;
         return sims[a].budget < sims[b].budget;
     });
-    for (int c = 0; c < dtr::N_GROUPS; c++) p.class_count[c] = 0;
-    for (int32_t i = 0; i < n_sims; i++) p.class_count[cls(i)]++;
     // groups whose traces are all small keep their state words in LDS; under
     // h_DTR^eq only if the group is resident at once that way: above 96
     // tensors a compute unit holds one workgroup of four simulations instead
     // of two, which a larger batch would pay for with its throughput
-    int32_t group_n[dtr::N_GROUPS] = {0, 0, 0, 0, 0, 0};
-    for (int32_t i = 0; i < n_sims; i++)
-        group_n[cls(i)] = std::max(group_n[cls(i)], p.traces[sims[i].trace].n);
-    for (int c = 0; c < dtr::N_GROUPS; c++) {
-        if (group_n[c] > dtr::SMALL_TENSORS || (c % 3 == 1 && !sweep)) continue;
-        const int32_t sn = std::max(2, (group_n[c] + 1) / 2 * 2);
+    for (int g = 0; g < dtr::N_GROUPS; g++) {
+        if (group_n[g] > dtr::SMALL_TENSORS || g % dtr::N_CLASSES == dtr::GROUP_WALK) continue;
+        const int32_t sn = std::max(2, (group_n[g] + 1) / 2 * 2);
         // eight reach masks of a long trace leave no room for the state words
-        const int64_t wg = dtr::static_lds_bytes(c) + dtr::dynamic_lds_bytes(c, p.sweep_chunks, L.walk_waves, sn);
+        const int64_t wg = dtr::static_lds_bytes(g) + dtr::dynamic_lds_bytes(g, p.chunks[g], p.waves[g], sn);
         if (wg > dtr::LDS_BYTES) continue;
-        if (c == 0 && p.class_count[c] > cus * dtr::EQ_WAVES * (dtr::LDS_BYTES / wg)) continue;
-        p.small_n[c] = sn;
+        if (g == dtr::GROUP_EQ && p.count[g] > cus * dtr::EQ_WAVES * (dtr::LDS_BYTES / wg)) continue;
+        p.small_n[g] = sn;
     }
 
     size_t w = align_up(64);   // header: work counter
@@ -601,11 +612,11 @@ int dtr_sim_create(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec
     if (n_sims) std::memcpy(H + p.order_off, p.order.data(), sizeof(int32_t) * n_sims);
     hipStream_t st = (hipStream_t)stream;
     int groups = 0;
-    for (int c = 0; c < dtr::N_GROUPS; c++) groups += p.class_count[c] > 0;
+    for (int c = 0; c < dtr::N_GROUPS; c++) groups += p.count[c] > 0;
     if (groups > 1) {
         bool okk = hipEventCreateWithFlags(&h->fork, hipEventDisableTiming) == hipSuccess;
         for (int c = 0; okk && c < dtr::N_GROUPS; c++)
-            if (p.class_count[c] > 0)
+            if (p.count[c] > 0)
                 okk = hipStreamCreateWithFlags(&h->aux[c], hipStreamNonBlocking) == hipSuccess &&
                       hipEventCreateWithFlags(&h->join[c], hipEventDisableTiming) == hipSuccess;
         if (!okk) {
@@ -639,16 +650,16 @@ int launch_traces(dtr_sim *h, void *stream, uint8_t *slots, uint32_t *queue, int
     const int64_t total = std::max<int64_t>(1, std::min<int64_t>(p.n_slots, max_slots));
     int32_t groups[dtr::N_GROUPS], ng = 0;
     for (int c = 0; c < dtr::N_GROUPS; c++)
-        if (p.class_count[c] > 0) groups[ng++] = c;
+        if (p.count[c] > 0) groups[ng++] = c;
     // concurrent groups take disjoint slot ranges, each at least one slot;
     // with fewer slots than groups the groups run one after another on the
     // caller's stream, each over every slot
     const bool fan = ng > 1 && h->fork && total >= ng;
-    int64_t share[dtr::N_GROUPS] = {0, 0, 0, 0, 0, 0};
+    int64_t share[dtr::N_GROUPS] = {};
     for (int k = 0; k < ng; k++) {
         const int c = groups[k];
-        share[c] = !fan ? total : std::max<int64_t>(1, total * p.class_count[c] / std::max(1, h->n_sims));
-        share[c] = std::min<int64_t>(share[c], p.class_count[c]);
+        share[c] = !fan ? total : std::max<int64_t>(1, total * p.count[c] / std::max(1, h->n_sims));
+        share[c] = std::min<int64_t>(share[c], p.count[c]);
     }
     for (; fan;) {      // trim the largest shares until the ranges fit
         int64_t sum = 0;
@@ -672,15 +683,16 @@ int launch_traces(dtr_sim *h, void *stream, uint8_t *slots, uint32_t *queue, int
         a[c].progress = (unsigned long long *)((uint8_t *)queue + dtr::PROGRESS_OFFSET);
         a[c].slots = slots + (size_t)off * (size_t)p.L.bytes;
         a[c].L = p.L;
-        a[c].n_sims = p.class_count[c];
+        a[c].L.walk_waves = p.waves[c];
+        a[c].n_sims = p.count[c];
         a[c].n_slots = (int32_t)std::max<int64_t>(1, share[c]);
-        a[c].sweep_chunks = p.sweep_chunks;
+        a[c].sweep_chunks = p.chunks[c];
         a[c].small_n = p.small_n[c];
         a[c].prof = nullptr;
 #ifdef DTR_PROFILE
         a[c].prof = (int64_t *)(h->ws + p.prof_off);
 #endif
-        first += p.class_count[c];
+        first += p.count[c];
         if (fan) off += share[c];
     }
     hipError_t e = dtr_launch_reset(queue, st);
@@ -824,9 +836,11 @@ int dtr_sim_launch_info(const dtr_sim *h, dtr_launch_info *out)
         dtrhost::log_plan_info(h->log, &out->n_slots, &out->waves_per_group, &out->lds_bytes);
     } else {
         out->n_slots = h->plan.n_slots;
-        out->waves_per_group = h->plan.class_count[1] + h->plan.class_count[4] > 0 ? (int32_t)h->plan.L.walk_waves
-                               : h->plan.class_count[0] > 0                      ? dtr::EQ_WAVES
-                                                                                 : 1;
+        const Plan &p = h->plan;
+        out->waves_per_group = p.count[dtr::GROUP_EQ] > 0 ? dtr::EQ_WAVES : 1;
+        bool walks = false;
+        for (int g = 0; g < dtr::N_GROUPS; g++) walks |= dtr::group_walks(g) && p.count[g] > 0;
+        if (walks) out->waves_per_group = (int32_t)p.L.walk_waves;
         if (h->plan.static_only)
             out->n_slots = (int32_t)std::max<int64_t>(1, std::min<int64_t>(
                 out->n_slots, (int64_t)((DTR_STATIC_SCRATCH_BYTES - STATIC_HEADER) / (size_t)h->plan.L.bytes)));

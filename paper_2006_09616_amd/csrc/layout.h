@@ -162,7 +162,7 @@ struct SlotLayout {
     int64_t vis_words;       // 32-bit words of one wavefront's visited bitmap (a multiple of 4)
     int64_t vis_bytes;       // bytes of one lane's visited flags (a multiple of 16)
     int64_t wq_cap;          // entries of one lane's member queue
-    int64_t walk_waves;      // wavefronts per workgroup of the walk heuristics
+    int64_t walk_waves;      // wavefronts per workgroup of the walk heuristics (of the group, in its launch)
 };
 // workgroups of the walk heuristics hold up to this many wavefronts: the
 // first runs the simulation, the others join its eviction scans
@@ -195,13 +195,17 @@ struct __attribute__((aligned(16))) UfNode {
     int32_t size;
 };
 
-// simulation groups, one kernel specialisation each: heuristic class
-// (union-find neighbourhood, neighbourhood walk, none), plus 3 with the
-// search approximations on
-constexpr int N_GROUPS = 6;
+// simulation groups, one kernel specialisation each: union-find
+// neighbourhood, neighbourhood walk (lane by lane, or swept: by trace), none;
+// plus N_CLASSES with the search approximations on
+enum { GROUP_EQ = 0, GROUP_WALK = 1, GROUP_SWEEP = 2, GROUP_SIMPLE = 3 };
+constexpr int N_CLASSES = 4;
+constexpr int N_GROUPS = 2 * N_CLASSES;
+constexpr bool group_walks(int group) { return group % N_CLASSES == GROUP_WALK || group % N_CLASSES == GROUP_SWEEP; }
 // work-counter block at the head of the working memory: one 32-bit counter
 // per group, then (at byte PROGRESS_OFFSET) the 64-bit progress counter
 constexpr int PROGRESS_OFFSET = 32;
+static_assert(4 * N_GROUPS <= PROGRESS_OFFSET, "a counter per group");
 constexpr int COUNTER_WORDS = PROGRESS_OFFSET / 4 + 2;
 constexpr int PROGRESS_STEP = 4096;
 
@@ -225,19 +229,19 @@ constexpr int64_t small_lds_bytes(int64_t n) { return n > 0 ? (8 * n + 15) / 16 
 constexpr int64_t LDS_BYTES = 160 << 10;
 constexpr int64_t WALK_CTL_BYTES = 2656;       // the walk heuristics' control block, in whole UfNodes
 // simulations per workgroup of a group's kernel
-constexpr int group_sims(int group) { return group == 0 ? EQ_WAVES : 1; }
+constexpr int group_sims(int group) { return group == GROUP_EQ ? EQ_WAVES : 1; }
 // a workgroup's static LDS: the pool head of each of its simulations, and
 // their union-find nodes or the walks' control block
 constexpr int64_t static_lds_bytes(int group)
 {
-    return group_sims(group) * ((group % 3 == 0 ? UF_LDS * (int64_t)sizeof(UfNode) : 0) + POOL_LDS * 80) +
-           (group % 3 == 1 ? WALK_CTL_BYTES : 0);
+    return group_sims(group) * ((group % N_CLASSES == GROUP_EQ ? UF_LDS * (int64_t)sizeof(UfNode) : 0) + POOL_LDS * 80) +
+           (group_walks(group) ? WALK_CTL_BYTES : 0);
 }
-// its dynamic LDS: the sweeps' arrays (walk heuristics), then the state words
+// its dynamic LDS: the sweeps' arrays (swept traces), then the state words
 // and stack top of each of its simulations (small traces)
 constexpr int64_t dynamic_lds_bytes(int group, int64_t sweep_chunks, int64_t walk_waves, int64_t small_n)
 {
-    return (group % 3 == 1 ? sweep_lds_bytes(sweep_chunks, walk_waves) : 0) +
+    return (group % N_CLASSES == GROUP_SWEEP ? sweep_lds_bytes(sweep_chunks, walk_waves) : 0) +
            group_sims(group) * small_lds_bytes(small_n);
 }
 
@@ -252,9 +256,9 @@ struct KernelArgs {
     SlotLayout L;
     int32_t n_sims;
     int32_t n_slots;
-    // walk heuristics: chunks of the largest trace that is swept (0: none); the
-    // workgroup's dynamic LDS holds the evicted masks, the candidate list and
-    // each wavefront's reach masks for that many
+    // the swept groups: chunks of the largest trace; the workgroup's dynamic
+    // LDS holds the evicted masks, the candidate list and each wavefront's
+    // reach masks for that many
     int32_t sweep_chunks;
     int32_t small_n;         // the small-trace kernels: state words of a simulation in LDS
     int64_t *prof;           // DTR_PROFILE builds: PROF_FIELDS counters per sim

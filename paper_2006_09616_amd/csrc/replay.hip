@@ -30,7 +30,7 @@
 //    Appendix C.2) of 64 candidates at a time are swept in operation order
 //    (traces of up to SWEEP_OPS operations); on longer traces each lane walks
 //    its candidate's, taking the next one as soon as its walk ends;
-//  * small traces (SMALL_TENSORS) keep the state words and the top of the
+//  * small traces (SMALL_TENSORS; not those walked lane by lane) keep the state words and the top of the
 //    rematerialization stack in LDS, in kernels of their own.
 //
 // Scores N/D are compared exactly by 128-bit cross-multiplication; ties go to
@@ -79,11 +79,15 @@ static_assert(LB == NB_HEAD, "a cache build may take its first chunk from the re
 // kernel specialisations by heuristic class (register budgets differ widely),
 // each with exact search or with the search approximations (HC | HC_APPROX)
 // and, for traces of up to SMALL_TENSORS tensors, with the state words and the
-// top of the rematerialization stack in LDS (| HC_SMALL)
-enum { HC_EQ = 0, HC_WALK = 1, HC_SIMPLE = 2, HC_APPROX = 4, HC_SMALL = 8 };
+// top of the rematerialization stack in LDS (| HC_SMALL).  Walks are swept
+// (HC_WALK | HC_SWEEP) or go lane by lane (HC_WALK), in kernels and groups of
+// their own: one kernel with both took 245 registers and 408 bytes of scratch
+// a lane, where the lane walks alone take 197 and none.
+enum { HC_EQ = 0, HC_WALK = 1, HC_SIMPLE = 2, HC_APPROX = 4, HC_SMALL = 8, HC_SWEEP = 16 };
 __host__ __device__ constexpr int cls(int hc) { return hc & 3; }
 __host__ __device__ constexpr bool approx(int hc) { return (hc & HC_APPROX) != 0; }
 __host__ __device__ constexpr bool small(int hc) { return (hc & HC_SMALL) != 0; }
+__host__ __device__ constexpr bool swept(int hc) { return (hc & HC_SWEEP) != 0; }
 // candidates per lane per scan round (their reads are issued together); the
 // h_DTR^eq round is instruction-issue bound, so a second candidate per lane
 // only doubles the round
@@ -532,7 +536,7 @@ __device__ __forceinline__ void wave_sync()
 // wavefronts per workgroup that hold simulations of their own (each with its
 // own LDS pool and node arrays): the exact h_DTR^eq kernel's four, else one
 __host__ __device__ constexpr int lds_waves(int hc) { return cls(hc) == HC_EQ && !approx(hc) ? EQ_WAVES : 1; }
-static_assert(lds_waves(HC_EQ) == group_sims(0) && lds_waves(HC_EQ | HC_APPROX) == group_sims(3), "workgroup shapes");
+static_assert(lds_waves(HC_EQ) == group_sims(GROUP_EQ) && lds_waves(HC_EQ | HC_APPROX) == group_sims(GROUP_EQ + N_CLASSES), "workgroup shapes");
 
 // the simulating wavefront's synchronization: wavefront-local where its
 // workgroup holds other wavefronts (walk heuristics, h_DTR^eq), a workgroup
@@ -1604,11 +1608,11 @@ __device__ WaveBest wave_best(const Best &best)
 __device__ __forceinline__ int64_t wave_sum(int64_t v) { return (int64_t)wave_add((uint64_t)v); }
 
 // The walk scan of the simulating wavefront.  Helper wavefronts (if any) are
-// given the scan's parameters at a workgroup barrier; all wavefronts walk
-// candidates lane by lane from the shared counter; after a second barrier
-// they take the listed (large) walks one per wavefront; after a third, the
-// helpers' bests enter this wavefront's lanes 1.. and their counters are
-// added.
+// given the scan's parameters at a workgroup barrier; all wavefronts take
+// groups of the listed candidates to sweep, or walk candidates lane by lane
+// from the shared counter and, after a second barrier, the listed (large)
+// walks one per wavefront; after a third, the helpers' bests enter this
+// wavefront's lanes 1.. and their counters are added.
 template <int HC>
 __device__ void walk_scan(Sim<HC> &s, const Filter &F, Best &best, int64_t &scored)
 {
@@ -1625,10 +1629,9 @@ __device__ void walk_scan(Sim<HC> &s, const Filter &F, Best &best, int64_t &scor
     P.seed = s.seed;
     LAS WalkCtl *C = s.ctl;
     const bool multi = s.nw > 1;
-    const bool swept = small(HC) || s.t.sw != nullptr;
     Sweep W;
     int32_t ncand = 0;
-    if (swept) {
+    if constexpr (swept(HC)) {
         W = sweep_at(s.sweep_lds, s.sweep_chunks, 0, s.t);
         ncand = sweep_list(s, W);
     }
@@ -1663,19 +1666,22 @@ __device__ void walk_scan(Sim<HC> &s, const Filter &F, Best &best, int64_t &scor
     // the helpers, of the whole-wavefront walks, and their number
     const int64_t w1 = (int64_t)__builtin_readcyclecounter();
 #endif
-    if (swept) {
+    if constexpr (swept(HC))
         sweep_groups<HC>(s.S, W, P, ncand, s.lane, 0, s.nw, C, best, nbr, adj, nscored);
-    } else if constexpr (!small(HC)) {
+    else
         walk_lanes<HC>(s.t, s.S, s.S.tst, P, s.lane, s.lane, multi ? (LAS uint32_t *)&C->ctr : nullptr,
                        (LAS uint32_t *)&C->ovf, best, nbr, adj, nscored);
+#ifdef DTR_PROFILE
+    const int64_t w2 = (int64_t)__builtin_readcyclecounter();
+#endif
+    if constexpr (!swept(HC)) {
         if (multi) __syncthreads();
         else wave_sync();
     }
 #ifdef DTR_PROFILE
-    const int64_t w2 = (int64_t)__builtin_readcyclecounter();
-    const int64_t w3 = w2;
+    const int64_t w3 = (int64_t)__builtin_readcyclecounter();
 #endif
-    if constexpr (!small(HC)) if (!swept)
+    if constexpr (!swept(HC))
         walk_listed<HC>(s.t, s.S, s.S.tst, P, s.lane, 0, uni((int32_t)C->ovf),
                         multi ? (LAS uint32_t *)&C->ctr2 : nullptr, best, nbr, adj, nscored);
 #ifdef DTR_PROFILE
@@ -1710,7 +1716,7 @@ __device__ void walk_scan(Sim<HC> &s, const Filter &F, Best &best, int64_t &scor
 // wavefront's walk scans (the three workgroup barriers of each) until it is
 // released at the end of the simulation.
 template <int HC>
-__device__ void help_walks(const KernelArgs &a, const Slot<HC> &S, int32_t lane, int32_t wave, LAS WalkCtl *C,
+__device__ __forceinline__ void help_walks(const KernelArgs &a, const Slot<HC> &S, int32_t lane, int32_t wave, LAS WalkCtl *C,
                            LAS uint8_t *sweep_lds)
 {
     for (;;) {
@@ -1736,10 +1742,10 @@ __device__ void help_walks(const KernelArgs &a, const Slot<HC> &S, int32_t lane,
         best.slot = -1;
         best.have = 0;
         int64_t nbr = 0, adj = 0, nscored = 0;
-        if (small(HC) || t.sw) {
+        if constexpr (swept(HC)) {
             sweep_groups<HC>(S, sweep_at(sweep_lds, a.sweep_chunks, wave, t), P, uni((int32_t)C->ncand), lane, wave,
                              (int32_t)a.L.walk_waves, C, best, nbr, adj, nscored);
-        } else if constexpr (!small(HC)) {
+        } else {
             walk_lanes<HC>(t, S, S.tst, P, lane, wave * WAVE + lane, (LAS uint32_t *)&C->ctr, (LAS uint32_t *)&C->ovf,
                            best, nbr, adj, nscored);
             __syncthreads();
@@ -2557,7 +2563,7 @@ __global__ void __launch_bounds__(cls(HC) == HC_WALK ? MAX_WALK_WAVES * WAVE : l
     __attribute__((amdgpu_waves_per_eu(2))) replay_kernel(KernelArgs a)
 {
     constexpr int LW = lds_waves(HC);
-    // the sweeps' arrays (walk heuristics), then each simulation's state
+    // the sweeps' arrays (swept traces), then each simulation's state
     // words and stack top (small traces)
     extern __shared__ __align__(16) uint8_t lds_dyn[];
     // union-find nodes (h_DTR^eq: one array per wavefront), or the walk
@@ -2571,23 +2577,24 @@ __global__ void __launch_bounds__(cls(HC) == HC_WALK ? MAX_WALK_WAVES * WAVE : l
         return;
     }
     const int32_t nw = cls(HC) == HC_WALK ? (int32_t)a.L.walk_waves : 1;
-    Slot<HC> S = slot_at<HC>(a, blockIdx.x, (LAS uint8_t *)lds_dyn + (cls(HC) == HC_WALK ? sweep_lds_bytes(a.sweep_chunks, nw) : 0));
+    Slot<HC> S = slot_at<HC>(a, blockIdx.x, (LAS uint8_t *)lds_dyn + (swept(HC) ? sweep_lds_bytes(a.sweep_chunks, nw) : 0));
     S.nodes.lds_l = (LAS UfNode *)lds_nodes;
     S.lpool_l = (LAS PoolSlotL *)lds_pool;
     LAS WalkCtl *ctl = (LAS WalkCtl *)lds_nodes;
     if constexpr (cls(HC) == HC_WALK) {
-        if constexpr (!small(HC)) {
-            // visited bitmaps start clear (every walk clears what it set)
+        if constexpr (swept(HC)) {
+            // this wavefront's reach masks start clear (every sweep clears what it set)
+            LAS uint64_t *M = (LAS uint64_t *)((LAS uint8_t *)lds_dyn + (8 + 4 * WAVE) * a.sweep_chunks) +
+                              wave * WAVE * a.sweep_chunks;
+            for (int32_t i = lane; i < WAVE * a.sweep_chunks; i += WAVE) M[i] = 0;
+        } else {
+            // and so do the walks' visited bitmaps
             // (the flags 16 bytes at a time: vis_bytes is a multiple of 16)
             GAS u32x4 *V = (GAS u32x4 *)(S.visb + (size_t)(wave * WAVE) * (size_t)S.vis_bytes);
             for (size_t i = lane; i < (size_t)WAVE * (size_t)S.vis_bytes / 16; i += WAVE) V[i] = u32x4{0u, 0u, 0u, 0u};
             GAS uint32_t *B = S.bigvis + (size_t)wave * (size_t)S.vis_words;
             for (int32_t i = lane; i < S.vis_words; i += WAVE) B[i] = 0u;
         }
-        // and so do this wavefront's reach masks
-        LAS uint64_t *M = (LAS uint64_t *)((LAS uint8_t *)lds_dyn + (8 + 4 * WAVE) * a.sweep_chunks) +
-                          wave * WAVE * a.sweep_chunks;
-        for (int32_t i = lane; i < WAVE * a.sweep_chunks; i += WAVE) M[i] = 0;
         wave_sync();
     }
     for (;;) {
@@ -2648,9 +2655,8 @@ extern "C" hipError_t dtr_static_scratch(void **ptr, size_t *bytes)
 }
 
 // Launch entries used by the host library (same shared object): the work
-// counters of the groups are cleared by a kernel, then each group g (heuristic
-// class: union-find; neighbourhood walk; none; + 3 with the search
-// approximations) runs its own kernel specialisation, each on the stream the
+// counters of the groups are cleared by a kernel, then each group (GROUP_*)
+// runs its own kernel specialisation, each on the stream the
 // host gives it (the groups use disjoint slots, so they may run at once).
 extern "C" hipError_t dtr_launch_reset(uint32_t *queue, hipStream_t stream)
 {
@@ -2666,7 +2672,9 @@ static hipError_t launch(const dtr::KernelArgs &a, hipStream_t stream)
     const int64_t waves = cls(HC) == HC_WALK ? a.L.walk_waves : lds_waves(HC);
     // h_DTR^eq: a slot per wavefront; the others: one per workgroup
     const dim3 grid((uint32_t)((a.n_slots + lds_waves(HC) - 1) / lds_waves(HC))), blk((uint32_t)(WAVE * waves));
-    constexpr int group = cls(HC) + (approx(HC) ? 3 : 0);
+    constexpr int group = (cls(HC) == HC_EQ ? GROUP_EQ : cls(HC) == HC_SIMPLE ? GROUP_SIMPLE
+                           : swept(HC)      ? GROUP_SWEEP
+                                            : GROUP_WALK) + (approx(HC) ? N_CLASSES : 0);
     const int64_t lds = dynamic_lds_bytes(group, a.sweep_chunks, waves, small(HC) ? a.small_n : 0);
     if (lds > 0) {
         // a workgroup may take more than the default 64 KB, static LDS
@@ -2686,18 +2694,20 @@ extern "C" hipError_t dtr_launch_group(const dtr::KernelArgs *a, int32_t group, 
     using namespace dtr;
     if (a->n_sims <= 0) return hipSuccess;
     switch (group + (a->small_n > 0 ? N_GROUPS : 0)) {
-    case 0: return launch<HC_EQ>(*a, stream);
-    case 1: return launch<HC_WALK>(*a, stream);
-    case 2: return launch<HC_SIMPLE>(*a, stream);
-    case 3: return launch<HC_EQ | HC_APPROX>(*a, stream);
-    case 4: return launch<HC_WALK | HC_APPROX>(*a, stream);
-    case 5: return launch<HC_SIMPLE | HC_APPROX>(*a, stream);
-    case 6: return launch<HC_EQ | HC_SMALL>(*a, stream);
-    case 7: return launch<HC_WALK | HC_SMALL>(*a, stream);
-    case 8: return launch<HC_SIMPLE | HC_SMALL>(*a, stream);
-    case 9: return launch<HC_EQ | HC_APPROX | HC_SMALL>(*a, stream);
-    case 10: return launch<HC_WALK | HC_APPROX | HC_SMALL>(*a, stream);
-    case 11: return launch<HC_SIMPLE | HC_APPROX | HC_SMALL>(*a, stream);
+    case GROUP_EQ: return launch<HC_EQ>(*a, stream);
+    case GROUP_WALK: return launch<HC_WALK>(*a, stream);
+    case GROUP_SWEEP: return launch<HC_WALK | HC_SWEEP>(*a, stream);
+    case GROUP_SIMPLE: return launch<HC_SIMPLE>(*a, stream);
+    case N_CLASSES + GROUP_EQ: return launch<HC_EQ | HC_APPROX>(*a, stream);
+    case N_CLASSES + GROUP_WALK: return launch<HC_WALK | HC_APPROX>(*a, stream);
+    case N_CLASSES + GROUP_SWEEP: return launch<HC_WALK | HC_SWEEP | HC_APPROX>(*a, stream);
+    case N_CLASSES + GROUP_SIMPLE: return launch<HC_SIMPLE | HC_APPROX>(*a, stream);
+    case N_GROUPS + GROUP_EQ: return launch<HC_EQ | HC_SMALL>(*a, stream);
+    case N_GROUPS + GROUP_SWEEP: return launch<HC_WALK | HC_SWEEP | HC_SMALL>(*a, stream);
+    case N_GROUPS + GROUP_SIMPLE: return launch<HC_SIMPLE | HC_SMALL>(*a, stream);
+    case N_GROUPS + N_CLASSES + GROUP_EQ: return launch<HC_EQ | HC_APPROX | HC_SMALL>(*a, stream);
+    case N_GROUPS + N_CLASSES + GROUP_SWEEP: return launch<HC_WALK | HC_SWEEP | HC_APPROX | HC_SMALL>(*a, stream);
+    case N_GROUPS + N_CLASSES + GROUP_SIMPLE: return launch<HC_SIMPLE | HC_APPROX | HC_SMALL>(*a, stream);
     default: return hipErrorInvalidValue;
     }
 }

@@ -51,7 +51,7 @@ hipError_t dtr_static_scratch(void **p, size_t *bytes)
 hipError_t dtr_launch_reset(uint32_t *, hipStream_t) { return hipSuccess; }
 hipError_t dtr_launch_group(const dtr::KernelArgs *a, int32_t group, hipStream_t)
 {
-    launches.push_back({group, a->n_sims, a->n_slots, a->L.bytes, group % 3 == 1 ? a->L.walk_waves : 1, a->sweep_chunks,
+    launches.push_back({group, a->n_sims, a->n_slots, a->L.bytes, a->L.walk_waves, a->sweep_chunks,
                         a->small_n, dtr::static_lds_bytes(group),
                         dtr::dynamic_lds_bytes(group, a->sweep_chunks, a->L.walk_waves, a->small_n),
                         dtr::dynamic_lds_bytes(group, a->sweep_chunks, a->L.walk_waves, 0)});

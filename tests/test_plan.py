@@ -99,3 +99,25 @@ def test_stacks_in_lds_start_at_a_quad(plan, n, waves):
         (row,) = plan([W.chain_trace(n)], _batch((0, W.H_DTR, 2, search)), flags=D.opt_walk_waves(waves))
         assert row["small_n"] > 0 and row["sweep_chunks"] == (2 * n + 63) // 64
         assert row["small_at"] % 16 == 0, row
+
+
+def test_swept_and_lane_walked_traces_are_separate_groups(plan):
+    """One batch's traces do not set each other's workgroups: lane walks hold
+    no sweep arrays, and a long trace of any group leaves the wavefronts, the
+    chunks and the LDS state of the swept ones as they are alone."""
+    short, long_ = W.chain_trace(150), W.chain_trace(1100)
+    key = lambda r: {f: r[f] for f in ("waves", "sweep_chunks", "small_n", "lds_dynamic")}
+    (alone,) = plan([short], _batch((0, W.H_DTR, 4)))
+    (lanes,) = plan([long_], _batch((0, W.H_DTR, 4)))
+    assert alone["sweep_chunks"] == 5 and alone["waves"] == 4 and alone["small_n"] > 0
+    assert lanes["sweep_chunks"] == 0 and lanes["lds_dynamic"] == 0 and lanes["group"] != alone["group"]
+    for other in (W.H_DTR, W.H_MSPS, W.H_LRU, W.H_EQ):
+        for search in (0, 3):
+            rows = plan([short, long_, LONG], _batch((0, W.H_DTR, 4), (1, W.H_DTR, 4), (2, other, 1, search)))
+            mine = [r for r in rows if r["group"] == alone["group"]]
+            assert len(mine) == 1 and key(mine[0]) == key(alone)
+            mixed = [r for r in rows if r["group"] == lanes["group"]]
+            assert len(mixed) == 1 and mixed[0]["lds_dynamic"] == 0
+            assert mixed[0]["waves"] == (8 if other in (W.H_DTR, W.H_MSPS) and not search else lanes["waves"])
+    both = plan([short, W.chain_trace(1000)], _batch((0, W.H_DTR, 2, 1), (1, W.H_DTR, 2)))
+    assert sorted(r["sweep_chunks"] for r in both) == [5, 32]
