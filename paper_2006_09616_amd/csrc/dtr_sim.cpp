@@ -356,7 +356,7 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     // (ResNet, 604: without releases 24.1 ms with 2, 18.6 with 4 and with 8;
     // transformer, 1108: 21.3, 17.4 and 23.5, whose eight reach masks leave
     // room for one workgroup a compute unit)
-    int32_t ww_max = 1, ww_min = dtr::MAX_WALK_WAVES;
+    int32_t ww_max = 1, ww_min = dtr::MAX_WALK_WAVES, lane_waves = 0;
     for (int g = 0; g < dtr::N_GROUPS; g++) {
         p.waves[g] = 1;
         if (!dtr::group_walks(g) || p.count[g] == 0) continue;
@@ -366,6 +366,7 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
         p.waves[g] = ww;
         ww_max = std::max(ww_max, ww);
         ww_min = std::min(ww_min, ww);
+        if (g % dtr::N_CLASSES == dtr::GROUP_WALK) lane_waves = std::max(lane_waves, ww);
     }
     // slot layout
     dtr::SlotLayout &L = p.L;
@@ -382,18 +383,21 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     take(L.nodes, sizeof(dtr::UfNode) * (size_t)L.ucap);
     take(L.uf_remap, need_uf ? 4 * ((size_t)L.ucap + dtr::UF_LDS) : 0);
     take(L.stack, sizeof(dtr::StackFrame) * (size_t)(n + 1));
-    // a visited bitmap and a member queue per lane of the walk heuristics
+    // a visited bitmap and a member queue per lane of the lane walks, nothing
+    // for the sweeps (their sets are in LDS): a ResNet slot (604 tensors) takes
+    // 169 KB, with four wavefronts' bitmaps and queues 603, so that the static
+    // working memory keeps 1586 simulations resident instead of 445
     L.walk_waves = ww_max;
-    const size_t lanes = (size_t)L.walk_waves * dtr::WAVE;
+    const size_t lanes = (size_t)lane_waves * dtr::WAVE;
     L.vis_words = (int64_t)((n + 127) / 128 * 4);
     L.vis_bytes = (int64_t)((n + 15) / 16 * 16);
     L.wq_cap = (opt && (opt->flags & DTR_OPT_WALK_QUEUE_SMALL)) ? 16
                                                                   : std::min<int64_t>((int64_t)n + 1, dtr::WALK_QUEUE_CAP);
-    take(L.vis, need_walk ? (size_t)L.vis_bytes * lanes : 0);
-    take(L.wq, need_walk ? 4 * (size_t)L.wq_cap * lanes : 0);
-    take(L.bigvis, need_walk ? 4 * (size_t)L.vis_words * (size_t)L.walk_waves : 0);
-    take(L.bigq, need_walk ? 4 * (n + 1) * (size_t)L.walk_waves : 0);
-    take(L.ovf, need_walk ? 4 * pc : 0);
+    take(L.vis, (size_t)L.vis_bytes * lanes);
+    take(L.wq, 4 * (size_t)L.wq_cap * lanes);
+    take(L.bigvis, 4 * (size_t)L.vis_words * (size_t)lane_waves);
+    take(L.bigq, 4 * (n + 1) * (size_t)lane_waves);
+    take(L.ovf, lane_waves ? 4 * pc : 0);
     take(L.pending, need_banish ? n : 0);
     L.bytes = (int64_t)o;
     if (p.static_only && (size_t)L.bytes > DTR_STATIC_SCRATCH_BYTES - STATIC_HEADER)

@@ -121,3 +121,21 @@ def test_swept_and_lane_walked_traces_are_separate_groups(plan):
             assert mixed[0]["waves"] == (8 if other in (W.H_DTR, W.H_MSPS) and not search else lanes["waves"])
     both = plan([short, W.chain_trace(1000)], _batch((0, W.H_DTR, 2, 1), (1, W.H_DTR, 2)))
     assert sorted(r["sweep_chunks"] for r in both) == [5, 32]
+
+
+def test_slots_hold_lane_walk_arrays_only_for_lane_walks(plan):
+    """Sweeps keep their sets in LDS: a batch whose walks are all swept has the
+    slots of a batch without walks, however many wavefronts sweep; a batch
+    with a lane-walked trace pays for that group's wavefronts."""
+    rn = W.resnet_trace(seed=1, blocks=50)
+    slot = lambda specs, tr=(rn,), flags=0: plan(list(tr), specs, flags=flags)[0]["slot_bytes"]
+    none = slot(_batch((0, W.H_LRU, 8)))
+    for h in (W.H_DTR, W.H_MSPS, W.H_ESTAR):
+        for search in (0, 3):
+            for waves in (0, 1, 2, 8):
+                assert slot(_batch((0, h, 8, search)), flags=D.opt_walk_waves(waves)) == none
+    lanes = {w: slot(_batch((0, W.H_DTR, 8)), flags=D.opt_walk_waves(w) | D.OPT_WALK_QUEUE_SMALL) for w in (1, 2)}
+    assert none < lanes[1] < lanes[2]
+    # a batch in the static working memory is resident as a whole
+    specs = _batch((0, W.H_DTR, 256), (0, W.H_EQ, 256), (0, W.H_LRU, 256))
+    assert sum(r["slots"] for r in plan([rn], specs, flags=D.OPT_STATIC_SCRATCH)) == 768
