@@ -349,24 +349,15 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
         if (g % dtr::N_CLASSES == dtr::GROUP_SWEEP)
             p.chunks[g] = std::max(p.chunks[g], (d.F + dtr::WAVE - 1) / dtr::WAVE);
     }
-    // walk heuristics: wavefronts per workgroup, from each group's largest
-    // trace.  Lane walks: more for large traces, whose pools are long.  Sweeps:
-    // two, one for each side, while a scan has at most 64 candidates (a chain
-    // of 66 tensors 0.42 ms with 2, 0.43 with 4), four from 256 tensors on
-    // (ResNet, 604: without releases 24.1 ms with 2, 18.6 with 4 and with 8;
-    // transformer, 1108: 21.3, 17.4 and 23.5, whose eight reach masks leave
-    // room for one workgroup a compute unit)
-    int32_t ww_max = 1, ww_min = dtr::MAX_WALK_WAVES, lane_waves = 0;
+    // lane walks: wavefronts per workgroup from each group's largest trace,
+    // more for large ones, whose pools are long
+    const int32_t ww_opt = opt ? (opt->flags >> DTR_OPT_WALK_WAVES_SHIFT) & 15 : 0;
+    int32_t lane_waves = 0;
     for (int g = 0; g < dtr::N_GROUPS; g++) {
         p.waves[g] = 1;
-        if (!dtr::group_walks(g) || p.count[g] == 0) continue;
-        int32_t ww = opt ? (opt->flags >> DTR_OPT_WALK_WAVES_SHIFT) & 15 : 0;
-        if (ww == 0 && g % dtr::N_CLASSES == dtr::GROUP_SWEEP) ww = group_n[g] >= 256 ? 4 : 2;
-        else if (ww == 0) ww = group_n[g] >= 8192 ? dtr::MAX_WALK_WAVES : group_n[g] >= 1024 ? 4 : 1;
-        p.waves[g] = ww;
-        ww_max = std::max(ww_max, ww);
-        ww_min = std::min(ww_min, ww);
-        if (g % dtr::N_CLASSES == dtr::GROUP_WALK) lane_waves = std::max(lane_waves, ww);
+        if (g % dtr::N_CLASSES != dtr::GROUP_WALK || p.count[g] == 0) continue;
+        p.waves[g] = ww_opt ? ww_opt : group_n[g] >= 8192 ? dtr::MAX_WALK_WAVES : group_n[g] >= 1024 ? 4 : 1;
+        lane_waves = std::max(lane_waves, p.waves[g]);
     }
     // slot layout
     dtr::SlotLayout &L = p.L;
@@ -387,7 +378,6 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     // for the sweeps (their sets are in LDS): a ResNet slot (604 tensors) takes
     // 169 KB, with four wavefronts' bitmaps and queues 603, so that the static
     // working memory keeps 1586 simulations resident instead of 445
-    L.walk_waves = ww_max;
     const size_t lanes = (size_t)lane_waves * dtr::WAVE;
     L.vis_words = (int64_t)((n + 127) / 128 * 4);
     L.vis_bytes = (int64_t)((n + 15) / 16 * 16);
@@ -407,6 +397,35 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     int32_t cus = 0;
     int rc = device_cus(&cus);
     if (rc) return rc;
+    // Sweeps: wavefronts per workgroup.  With few simulations, two (one for
+    // each side) while a scan has at most 64 candidates (a chain of 66 tensors
+    // 0.42 ms with 2, 0.43 with 4), four from 256 tensors on (ResNet, 604:
+    // without releases 24.1 ms with 2, 18.6 with 4 and with 8; transformer,
+    // 1108: 21.3, 17.4 and 23.5, whose eight reach masks leave room for one
+    // workgroup a compute unit).  With many, as many as leave at most half as
+    // many again waiting as are resident: launches of 256, 768, 1024, 1536,
+    // 2048 and 8192 budgets under h_DTR took, with 4 / 2 / 1 wavefronts,
+    //   ResNet       4.1 / 5.1 / 5.5,  5.9 / 5.3 / -,  7.0 / 5.4 / 5.8,  9.7 / 7.3 / 5.9,  12.8 / 8.3 / 8.2,  51 / 32 / 25 ms
+    //   transformer  15 / 20 / 29,  16 / 21 / -,  20 / 21 / 30,  29 / 28 / 31,  39 / 38 / 39,  153 / 140 / 148 ms
+    int64_t most = opt && opt->slots > 0 ? opt->slots : n_sims;         // simulations in flight
+    if (p.static_only)
+        most = std::min<int64_t>(most, (int64_t)((DTR_STATIC_SCRATCH_BYTES - STATIC_HEADER) / (size_t)L.bytes));
+    int32_t ww_min = dtr::MAX_WALK_WAVES;
+    L.walk_waves = 1;
+    for (int g = 0; g < dtr::N_GROUPS; g++) {
+        if (!dtr::group_walks(g) || p.count[g] == 0) continue;
+        if (g % dtr::N_CLASSES == dtr::GROUP_SWEEP) {
+            int32_t ww = group_n[g] >= 256 ? 4 : 2;
+            for (; ww > 1; ww /= 2) {
+                const int64_t wg = dtr::static_lds_bytes(g) + dtr::dynamic_lds_bytes(g, p.chunks[g], ww, 0);
+                const int64_t resident = cus * std::min<int64_t>(dtr::LDS_BYTES / wg, dtr::WALK_CU_WAVES / ww);
+                if (2 * std::min<int64_t>(p.count[g], most * p.count[g] / n_sims) <= 3 * resident) break;
+            }
+            p.waves[g] = ww_opt ? ww_opt : ww;
+        }
+        L.walk_waves = std::max<int64_t>(L.walk_waves, p.waves[g]);
+        ww_min = std::min(ww_min, p.waves[g]);
+    }
     // 16 slots per compute unit (at least as many as any kernel keeps
     // resident: 8 under h_DTR^eq, one per wavefront); a batch of walk
     // heuristics alone needs no more slots than its larger workgroups occupy

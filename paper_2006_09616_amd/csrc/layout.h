@@ -167,6 +167,8 @@ struct SlotLayout {
 // workgroups of the walk heuristics hold up to this many wavefronts: the
 // first runs the simulation, the others join its eviction scans
 constexpr int MAX_WALK_WAVES = 8;
+// their registers allow two wavefronts a SIMD
+constexpr int WALK_CU_WAVES = 8;
 // a lane's member queue holds at most this many entries (walks that need
 // more are taken by a whole wavefront, a level at a time)
 constexpr int WALK_QUEUE_CAP = 256;

@@ -42,8 +42,8 @@ def plan(tmp_path_factory):
     lib.dtr_sim_destroy.argtypes = [vp]
     lib.plan_launches.argtypes = [vp, i32]
 
-    def launches(programs, specs, logs=False, flags=0):
-        opts = {"flags": flags} if flags else None
+    def launches(programs, specs, logs=False, flags=0, slots=0):
+        opts = {"flags": flags, "slots": slots} if flags or slots else None
         p = (D._PackedLogs if logs else D._Packed)(programs, specs, opts)
         size, h = sz(0), vp()
         kind = "dtr_log" if logs else "dtr_sim"
@@ -139,3 +139,22 @@ def test_slots_hold_lane_walk_arrays_only_for_lane_walks(plan):
     # a batch in the static working memory is resident as a whole
     specs = _batch((0, W.H_DTR, 256), (0, W.H_EQ, 256), (0, W.H_LRU, 256))
     assert sum(r["slots"] for r in plan([rn], specs, flags=D.OPT_STATIC_SCRATCH)) == 768
+
+
+@pytest.mark.parametrize("search", [0, 3])
+def test_sweeping_wavefronts_by_simulations_in_flight(plan, search):
+    """Few simulations sweep with many wavefronts each, many with few: as many
+    as leave at most half as many again waiting as are resident (a compute
+    unit holds two workgroups of four wavefronts, four of two, eight of one,
+    or fewer where their LDS says so); slots and the static working memory
+    count as what is in flight."""
+    rn, small = W.resnet_trace(seed=1, blocks=50), W.chain_trace(32)
+    waves = lambda n, tr=rn, **kw: plan([tr], _batch((0, W.H_DTR, n, search)), **kw)[0]["waves"]
+    assert [waves(n) for n in (1, 256, 768, 769, 1536, 1537, 8192)] == [4, 4, 4, 2, 2, 1, 1]
+    assert [waves(n, small) for n in (1, 1536, 1537)] == [2, 2, 1]
+    assert waves(8192, flags=D.opt_walk_waves(4)) == 4
+    assert waves(8192, slots=256) == 4 and waves(8192, slots=1024) == 2
+    # 170 KB a simulation: 1586 fit the static working memory, shared with the other group
+    both = _batch((0, W.H_DTR, 4096, search), (0, W.H_LRU, 4096, search))
+    assert plan([rn], both, flags=D.OPT_STATIC_SCRATCH)[0]["waves"] == 2
+    assert plan([rn], both)[0]["waves"] == 1
