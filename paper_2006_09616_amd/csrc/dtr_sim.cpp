@@ -405,22 +405,25 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     // workgroup a compute unit).  With many, as many as leave at most half as
     // many again waiting as are resident: launches of 256, 768, 1024, 1536,
     // 2048 and 8192 budgets under h_DTR took, with 4 / 2 / 1 wavefronts,
-    //   ResNet       4.1 / 5.1 / 5.5,  5.9 / 5.3 / -,  7.0 / 5.4 / 5.8,  9.7 / 7.3 / 5.9,  12.8 / 8.3 / 8.2,  51 / 32 / 25 ms
-    //   transformer  15 / 20 / 29,  16 / 21 / -,  20 / 21 / 30,  29 / 28 / 31,  39 / 38 / 39,  153 / 140 / 148 ms
+    //   ResNet       4.1 / 5.1 / 5.5,  5.9 / 5.3 / -,  7.0 / 5.5 / 5.8,  9.7 / 7.3 / 5.9,  12.8 / 8.4 / 6.6,  51 / 32 / 23 ms
+    //   transformer  15 / 20 / 29,  16 / 21 / -,  20 / 21 / 30,  29 / 22 / 31,  39 / 28 / 32,  153 / 108 / 109 ms
     int64_t most = opt && opt->slots > 0 ? opt->slots : n_sims;         // simulations in flight
     if (p.static_only)
         most = std::min<int64_t>(most, (int64_t)((DTR_STATIC_SCRATCH_BYTES - STATIC_HEADER) / (size_t)L.bytes));
+    auto in_flight = [&](int g) { return std::min<int64_t>(p.count[g], most * p.count[g] / n_sims); };
+    // simulations of a group that the device holds at once
+    auto resident = [&](int g, int32_t waves, int32_t small_n) {
+        const int64_t wg = dtr::static_lds_bytes(g) + dtr::dynamic_lds_bytes(g, p.chunks[g], waves, small_n);
+        const int32_t wg_waves = dtr::group_walks(g) ? waves : dtr::group_sims(g);
+        return cus * std::min<int64_t>(dtr::LDS_BYTES / wg, dtr::group_cu_waves(g) / wg_waves) * dtr::group_sims(g);
+    };
     int32_t ww_min = dtr::MAX_WALK_WAVES;
     L.walk_waves = 1;
     for (int g = 0; g < dtr::N_GROUPS; g++) {
         if (!dtr::group_walks(g) || p.count[g] == 0) continue;
         if (g % dtr::N_CLASSES == dtr::GROUP_SWEEP) {
             int32_t ww = group_n[g] >= 256 ? 4 : 2;
-            for (; ww > 1; ww /= 2) {
-                const int64_t wg = dtr::static_lds_bytes(g) + dtr::dynamic_lds_bytes(g, p.chunks[g], ww, 0);
-                const int64_t resident = cus * std::min<int64_t>(dtr::LDS_BYTES / wg, dtr::WALK_CU_WAVES / ww);
-                if (2 * std::min<int64_t>(p.count[g], most * p.count[g] / n_sims) <= 3 * resident) break;
-            }
+            while (ww > 1 && 2 * in_flight(g) > 3 * resident(g, ww, 0)) ww /= 2;
             p.waves[g] = ww_opt ? ww_opt : ww;
         }
         L.walk_waves = std::max<int64_t>(L.walk_waves, p.waves[g]);
@@ -481,18 +484,18 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
         if (ra != rb) return ra < rb;
         return sims[a].budget < sims[b].budget;
     });
-    // groups whose traces are all small keep their state words in LDS; under
-    // h_DTR^eq only if the group is resident at once that way: above 96
-    // tensors a compute unit holds one workgroup of four simulations instead
-    // of two, which a larger batch would pay for with its throughput
+    // groups whose traces are all small keep their state words in LDS, unless
+    // that leaves simulations waiting that would be resident without it: 8192
+    // simulations of 2040 tensors under h_LRU (five a compute unit in place of
+    // twelve) 5.48 s with it, 3.22 without, 1024 of them 1.15 and 1.24; 4096
+    // transformer budgets under h_DTR^eq, ignore-small (five in place of
+    // eight), 28.2 and 18.2 ms
     for (int g = 0; g < dtr::N_GROUPS; g++) {
         if (group_n[g] > dtr::SMALL_TENSORS || g % dtr::N_CLASSES == dtr::GROUP_WALK) continue;
         const int32_t sn = std::max(2, (group_n[g] + 1) / 2 * 2);
-        // eight reach masks of a long trace leave no room for the state words
-        const int64_t wg = dtr::static_lds_bytes(g) + dtr::dynamic_lds_bytes(g, p.chunks[g], p.waves[g], sn);
-        if (wg > dtr::LDS_BYTES) continue;
-        if (g == dtr::GROUP_EQ && p.count[g] > cus * dtr::EQ_WAVES * (dtr::LDS_BYTES / wg)) continue;
-        p.small_n[g] = sn;
+        const int64_t with = resident(g, p.waves[g], sn), without = resident(g, p.waves[g], 0);
+        // (none: eight reach masks of a long trace leave no room for the state words)
+        if (with > 0 && (with >= without || in_flight(g) <= with)) p.small_n[g] = sn;
     }
 
     size_t w = align_up(64);   // header: work counter

@@ -167,8 +167,6 @@ struct SlotLayout {
 // workgroups of the walk heuristics hold up to this many wavefronts: the
 // first runs the simulation, the others join its eviction scans
 constexpr int MAX_WALK_WAVES = 8;
-// their registers allow two wavefronts a SIMD
-constexpr int WALK_CU_WAVES = 8;
 // a lane's member queue holds at most this many entries (walks that need
 // more are taken by a whole wavefront, a level at a time)
 constexpr int WALK_QUEUE_CAP = 256;
@@ -222,7 +220,7 @@ constexpr int64_t sweep_lds_bytes(int64_t chunks, int64_t waves)
 // simulation, with which a compute unit still holds five simple-heuristic ones
 // (27 KB each) and a workgroup of four h_DTR^eq ones (141 KB).  On the ResNet
 // trace an operation went from 18,700 to 15,300 cycles under h_DTR^eq and from
-// 7,700 to 7,300 under h_LRU.
+// 7,700 to 7,300 under h_LRU.  (Not for batches that would wait for it.)
 constexpr int SMALL_TENSORS = 2048;
 constexpr int SMALL_STACK = 16;
 constexpr int64_t small_lds_bytes(int64_t n) { return n > 0 ? (8 * n + 15) / 16 * 16 + SMALL_STACK * (int64_t)sizeof(StackFrame) : 0; }
@@ -232,6 +230,9 @@ constexpr int64_t LDS_BYTES = 160 << 10;
 constexpr int64_t WALK_CTL_BYTES = 2656;       // the walk heuristics' control block, in whole UfNodes
 // simulations per workgroup of a group's kernel
 constexpr int group_sims(int group) { return group == GROUP_EQ ? EQ_WAVES : 1; }
+// wavefronts that a compute unit's registers hold of a group's kernel (two or
+// three a SIMD)
+constexpr int group_cu_waves(int group) { return group == GROUP_SIMPLE ? 12 : 8; }
 // a workgroup's static LDS: the pool head of each of its simulations, and
 // their union-find nodes or the walks' control block
 constexpr int64_t static_lds_bytes(int group)

@@ -158,3 +158,29 @@ def test_sweeping_wavefronts_by_simulations_in_flight(plan, search):
     both = _batch((0, W.H_DTR, 4096, search), (0, W.H_LRU, 4096, search))
     assert plan([rn], both, flags=D.OPT_STATIC_SCRATCH)[0]["waves"] == 2
     assert plan([rn], both)[0]["waves"] == 1
+
+
+def _resident(row, small):
+    """Simulations that 256 compute units hold of a launch's kernel, by LDS
+    and by the wavefronts its registers allow."""
+    per_wg = 4 if row["group"] == 0 else 1
+    waves = row["waves"] if row["sweep_chunks"] else per_wg
+    regs = 12 if row["group"] == 3 else 8
+    return 256 * min(LDS // (row["lds_static"] + (row["lds_dynamic"] if small else row["small_at"])), regs // waves) * per_wg
+
+
+@pytest.mark.parametrize("h,search", [(W.H_LRU, 0), (W.H_LRU, 3), (W.H_EQ, 0), (W.H_EQ, 3), (W.H_DTR, 0), (W.H_DTR, 3)])
+@pytest.mark.parametrize("tensors", [30, 96, 130, 604, 1200, 2000, 2048])
+def test_lds_state_leaves_no_simulation_waiting(plan, h, search, tensors):
+    """State words and stack tops are in LDS while the batch is resident that
+    way, and beyond it only where they cost no residency."""
+    tr = W.chain_trace(tensors // 2)
+    for n in (1, 64, 1000, 1024, 1025, 1280, 1281, 2048, 3000, 4096, 9000):
+        (row,) = plan([tr], _batch((0, h, n, search)))
+        if row["small_n"] == 0:
+            (few,) = plan([tr], _batch((0, h, 1, search)))
+            assert few["small_n"] == tr.n_tensors
+            if few["waves"] == row["waves"]:
+                assert n > _resident(few, True) and _resident(few, True) < _resident(few, False)
+        else:
+            assert n <= _resident(row, True) or _resident(row, True) == _resident(row, False), (n, row)
