@@ -47,15 +47,15 @@ struct LogProgDev {
     const int32_t *req;           // [n_req] tensors still referenced at the end, ascending
     const LogOp *op;              // [F]
     const LogRef *inr, *outr;     // the operators' inputs and outputs
-    int32_t sweep, pad;           // every edge goes from a smaller storage id to a larger: walks are swept
+    int32_t sweep, pad;           // walks are swept: every edge goes from a smaller storage id to a larger, and the rows are in LDS
     const int32_t *born_off, *born; // per operator: (parent, storage) edges its first run creates
 };
 
 // Per-slot working memory of the log replay, sized for the largest log of
 // the batch.  Byte offsets from the slot base, 256-byte aligned.
-//   state/pinned/pending   u8  [S_max]  storage state, never-evictable flag,
-//                                       banishing deferred
-//   locks, node            i32 [S_max]  holds by operators in progress; the
+//   state, pending         u8  [S_max]  storage state; banishing deferred
+//   locks, node            i32 [S_max]  holds by operators in progress, with a
+//                                       bit for never-evictable storages; the
 //                                       union-find node of an evicted storage
 //   sgen, last             i64 [S_max]  residency generation; last access
 //   gen                    i64 [T_max]  generation at which each tensor's
@@ -73,7 +73,7 @@ struct LogProgDev {
 //   stack                  LogFrame [F_max + 2] operator calls in progress
 struct LogSlotLayout {
     int64_t bytes;
-    int64_t state, pinned, pending;
+    int64_t state, pending;
     int64_t locks, node;
     int64_t sgen, last;
     int64_t gen;
@@ -101,12 +101,13 @@ struct LogKernelArgs {
     LogSlotLayout L;
     int32_t n_sims, n_slots;
     // walk state in LDS when lds_bytes > 0: byte offsets of the storage
-    // states, the 64 visited bitsets and the storage graph (16-bit ids)
+    // states, the 64 visited bitsets and the storage graph (16-bit ids and
+    // offsets)
     int32_t lds_bytes, lds_state, lds_wm, lds_po, lds_co, lds_pa, lds_ca;
     // and for the walk scan: storage costs c0, the candidate list, 64
     // pending-storage stacks of LOG_LDS_STACK entries, the candidate counter
     int32_t lds_c0, lds_cand, lds_stk, lds_ctr;
-    int32_t lds_pinned, lds_locks;   // never-evictable flags and lock counts
+    int32_t lds_locks;         // lock counts
     int32_t lds_sz, lds_last;  // storage sizes and last-access times
     int32_t lds_rsum, lds_rcnt;  // per listed candidate: walked cost, count
     int32_t lds_pcnt, lds_ccnt;  // edges created so far per storage
@@ -121,7 +122,9 @@ struct LogKernelArgs {
     int32_t waves, lds_ctl;
 };
 
-constexpr int SWEEP_STORAGES = 4096;      // 64 chunks: the pending chunks are one 64-bit mask
+// 64 chunks: the pending chunks are one 64-bit mask (LDS ends the sweeps
+// earlier: a residual network's log at some 1,850 storages)
+constexpr int SWEEP_STORAGES = 4096;
 constexpr int LOG_LDS_STACK = 32;
 constexpr int MAX_LOG_WAVES = 4;
 

@@ -45,6 +45,9 @@ enum { POLICY_EAGER = 0, POLICY_IGNORE = 1, POLICY_BANISH = 2 };
 enum { SEARCH_IGNORE_SMALL = 1, SEARCH_SAMPLE = 2 };
 // cost measure of a score N / (m^use_m * s^use_s)
 enum { CM_ESTAR = 0, CM_EQCLASS = 1, CM_LOCAL = 2, CM_NONE = 3, CM_ANCESTORS = 4, CM_RAND = 5 };
+// in a lock count (below 2^28: operators and tensors together): a storage that
+// is never evictable (a constant, a banished storage's dependent)
+constexpr int32_t PINNED = 1 << 30;
 constexpr uint64_t GOLDEN = 0x9E3779B97F4A7C15ull;
 constexpr uint64_t SAMPLE_STREAM = 0xD6E8FEB86659FD93ull;
 
@@ -94,7 +97,7 @@ struct Ptr<true, T> {
 };
 template <bool L, class T>
 using Mem = typename Ptr<L, T>::type;
-// neighbour ids: 16 bits in LDS
+// neighbour ids and edge offsets: 16 bits in LDS
 template <bool L>
 using Adj = typename std::conditional<L, uint16_t, int32_t>::type;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -159,7 +162,7 @@ struct Sim {
     ProgG P;
     Mem<L, uint8_t> state;       // storage states
     Mem<L, uint32_t> wm;         // this lane's visited bitset (walks)
-    Mem<L, const int32_t> po, co;          // storage graph: parents, children
+    Mem<L, const Adj<L>> po, co;           // storage graph: parents, children
     Mem<L, const Adj<L>> pa, ca;
     // the graph that exists so far: edges per list (a prefix, lists being in
     // creation order) and each storage's cost over its tensors created so far
@@ -180,8 +183,7 @@ struct Sim {
     int32_t n_storages;        // bound of the storage arrays in LDS
     int32_t wmw;               // words per visited bitset
     // slot memory
-    Mem<L, uint8_t> pinned;    // never evictable (constants, banished storages' dependents)
-    Mem<L, int32_t> locks;
+    Mem<L, int32_t> locks;     // holds of operators in progress; | PINNED: never evictable
     GAS uint8_t *pending;
     GAS int32_t *node;
     GAS int64_t *sgen, *gen;
@@ -220,9 +222,9 @@ template <bool L>
 __device__ __forceinline__ bool evictable(const Sim<L> &s, int32_t st)
 {
     // every read issued before the first test
-    const uint8_t state = s.state[st], pin = s.pinned[st];
+    const uint8_t state = s.state[st];
     const int32_t locks = s.locks[st];
-    return (state == ST_RESIDENT) & (locks == 0) & (pin == 0);
+    return (state == ST_RESIDENT) & (locks == 0);
 }
 
 // ----------------------------------------------------------- union-find --
@@ -649,10 +651,10 @@ __device__ void scan_walk_lds(Sim<L> &s, uint64_t min_size, bool sampling, uint6
         bool ok = false;
         if (x < S) {
             // every read issued before the first test
-            const uint8_t st = s.state[x], pin = s.pinned[x];
+            const uint8_t st = s.state[x];
             const int32_t lk = s.locks[x];
             const uint64_t sz = (uint64_t)s.sz[x];
-            ok = (st == ST_RESIDENT) & (lk == 0) & (pin == 0) & (sz >= min_size);
+            ok = (st == ST_RESIDENT) & (lk == 0) & (sz >= min_size);
         }
         if (ok && sampling) {
             const uint64_t key = ((uint64_t)s.eviction_no << 32) + (uint64_t)(uint32_t)x;
@@ -799,7 +801,7 @@ template <bool L>
 __device__ void try_banish(Sim<L> &s, int32_t st)
 {
     const int32_t b = s.P.dt_off[st], e = s.P.dt_off[st + 1];
-    bool blocked = s.locks[st] > 0;
+    bool blocked = (s.locks[st] & ~PINNED) != 0;
     for (int32_t q = b; q < e && !blocked; q += WAVE) {
         bool bad = false;
         if (q + s.lane < e) {
@@ -815,7 +817,7 @@ __device__ void try_banish(Sim<L> &s, int32_t st)
     s.eager++;
     for (int32_t q = b + s.lane; q < e; q += WAVE) {
         const int32_t d = s.P.t_storage[s.P.dt[q]];
-        if (s.state[d] == ST_RESIDENT) s.pinned[d] = 1;
+        if (s.state[d] == ST_RESIDENT) s.locks[d] |= PINNED;
     }
     wave_sync();
 }
@@ -1032,8 +1034,8 @@ __device__ void run_sim(const LogKernelArgs &a, int32_t sim, uint8_t *base, int3
     if constexpr (L) {
         s.state = (Mem<L, uint8_t>)(lds + a.lds_state);
         s.wm = (Mem<L, uint32_t>)(lds + a.lds_wm) + lane * W;
-        s.po = (Mem<L, const int32_t>)(lds + a.lds_po);
-        s.co = (Mem<L, const int32_t>)(lds + a.lds_co);
+        s.po = (Mem<L, const Adj<L>>)(lds + a.lds_po);
+        s.co = (Mem<L, const Adj<L>>)(lds + a.lds_co);
         s.pa = (Mem<L, const Adj<L>>)(lds + a.lds_pa);
         s.ca = (Mem<L, const Adj<L>>)(lds + a.lds_ca);
         s.c0d = (Mem<L, int64_t>)(lds + a.lds_c0);
@@ -1048,18 +1050,16 @@ __device__ void run_sim(const LogKernelArgs &a, int32_t sim, uint8_t *base, int3
         s.rows = (LAS uint64_t *)(lds + a.lds_rows);
         s.reach = (LAS uint64_t *)(lds + a.lds_wm);
         s.ctl = (LAS int32_t *)(lds + a.lds_ctl);
-        s.pinned = (Mem<L, uint8_t>)(lds + a.lds_pinned);
         s.locks = (Mem<L, int32_t>)(lds + a.lds_locks);
         s.last = (Mem<L, int64_t>)(lds + a.lds_last);
         s.sz = (Mem<L, const int64_t>)(lds + a.lds_sz);
     } else {
         s.state = (Mem<L, uint8_t>)(base + Y.state);
         s.wm = (Mem<L, uint32_t>)(base + Y.wmark) + lane * W;
-        s.po = (Mem<L, const int32_t>)s.P.par_off;
-        s.co = (Mem<L, const int32_t>)s.P.ch_off;
+        s.po = (Mem<L, const Adj<L>>)s.P.par_off;
+        s.co = (Mem<L, const Adj<L>>)s.P.ch_off;
         s.pa = (Mem<L, const Adj<L>>)s.P.par;
         s.ca = (Mem<L, const Adj<L>>)s.P.ch;
-        s.pinned = (Mem<L, uint8_t>)(gb + Y.pinned);
         s.locks = (Mem<L, int32_t>)(gb + Y.locks);
         s.last = (Mem<L, int64_t>)(gb + Y.last);
         s.sz = s.P.s_size;
@@ -1103,9 +1103,8 @@ __device__ void run_sim(const LogKernelArgs &a, int32_t sim, uint8_t *base, int3
     s.n_storages = S;
     for (int32_t i = lane; i < S; i += WAVE) {
         s.state[i] = ST_UNCOMPUTED;
-        s.pinned[i] = s.P.s_const[i];
         s.pending[i] = 0;
-        s.locks[i] = 0;
+        s.locks[i] = s.P.s_const[i] ? PINNED : 0;
         s.node[i] = -1;
         s.sgen[i] = 0;
         s.last[i] = 0;
@@ -1125,11 +1124,11 @@ __device__ void run_sim(const LogKernelArgs &a, int32_t sim, uint8_t *base, int3
     }
     if constexpr (L) {
         // the storage graph of this log, 16-bit neighbour ids
-        Mem<L, int32_t> po = (Mem<L, int32_t>)s.po, co = (Mem<L, int32_t>)s.co;
+        Mem<L, Adj<L>> po = (Mem<L, Adj<L>>)s.po, co = (Mem<L, Adj<L>>)s.co;
         Mem<L, Adj<L>> pa = (Mem<L, Adj<L>>)s.pa, ca = (Mem<L, Adj<L>>)s.ca;
         for (int32_t i = lane; i <= S; i += WAVE) {
-            po[i] = s.P.par_off[i];
-            co[i] = s.P.ch_off[i];
+            po[i] = (Adj<L>)s.P.par_off[i];
+            co[i] = (Adj<L>)s.P.ch_off[i];
         }
         const int32_t E = s.P.par_off[S];
         for (int32_t e = lane; e < E; e += WAVE) {
@@ -1201,8 +1200,8 @@ __device__ void help_walks(const LogKernelArgs &a, uint8_t *base, int32_t lane, 
         s.lane = lane;
         s.state = (Mem<L, uint8_t>)(lds + a.lds_state);
         s.wm = (Mem<L, uint32_t>)(lds + a.lds_wm) + id * W;
-        s.po = (Mem<L, const int32_t>)(lds + a.lds_po);
-        s.co = (Mem<L, const int32_t>)(lds + a.lds_co);
+        s.po = (Mem<L, const Adj<L>>)(lds + a.lds_po);
+        s.co = (Mem<L, const Adj<L>>)(lds + a.lds_co);
         s.pa = (Mem<L, const Adj<L>>)(lds + a.lds_pa);
         s.ca = (Mem<L, const Adj<L>>)(lds + a.lds_ca);
         s.c0d = (Mem<L, int64_t>)(lds + a.lds_c0);

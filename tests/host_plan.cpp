@@ -14,6 +14,7 @@
 
 struct PlanLaunch {
     int64_t group;           // -1: operator logs
+    // (logs: sweep_chunks says whether any log is swept)
     int64_t sims, slots, slot_bytes, waves, sweep_chunks, small_n, lds_static, lds_dynamic;
     int64_t small_at;        // where the state words and stacks start in the dynamic LDS
 };
@@ -59,7 +60,9 @@ hipError_t dtr_launch_group(const dtr::KernelArgs *a, int32_t group, hipStream_t
 }
 hipError_t dtr_launch_log(const dtr::LogKernelArgs *a, hipStream_t)
 {
-    launches.push_back({-1, a->n_sims, a->n_slots, a->L.bytes, a->waves, 0, 0, 0, a->lds_bytes, 0});
+    int64_t sweeps = 0;
+    for (int32_t i = 0; i < a->n_sims; i++) sweeps |= a->progs[a->specs[i].trace].sweep;
+    launches.push_back({-1, a->n_sims, a->n_slots, a->L.bytes, a->waves, sweeps, 0, 0, a->lds_bytes, 0});
     return hipSuccess;
 }
 

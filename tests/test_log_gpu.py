@@ -319,3 +319,27 @@ def test_resnet_log_search_approximations(gpu, oracle_lib):
     print(f"resnet log search: {len(specs)} sims", flush=True)
     compare(gpu.run_log(wl.traces, specs), oracle_lib.run_log(wl.traces, specs, threads=16), specs,
             "resnet log search")
+
+
+@pytest.mark.parametrize("blocks,waves,lds", [(60, 2, True), (70, 1, True), (72, 2, True), (80, 1, True), (90, 1, False)])
+def test_large_logs_swept_and_walked(gpu, oracle_lib, blocks, waves, lds):
+    """Residual networks' logs around the limits of LDS: swept by two waves and
+    by one, then walked lane by lane where the sweeps' rows no longer fit (two
+    waves, one, and in device memory), alone and beside a small log."""
+    logs = [W.resnet_log(seed=blocks, blocks=blocks), W.resnet_log(seed=1, blocks=2), W.random_log(9, n_steps=60)]
+    peaks = unlimited_peaks(oracle_lib, logs)
+    rows = [(i, h, int(peaks[i] * f), i, pol) for i in range(3) for h in (W.H_DTR, W.H_MSPS, W.H_ESTAR, W.H_EQ, W.H_LRU)
+            for f in (0.8, 0.95) for pol in (W.POLICY_EAGER, W.POLICY_BANISH) if not (h == W.H_EQ and pol == W.POLICY_BANISH)]
+    specs = W.make_specs(rows)
+    print(f"log of {blocks} blocks: {len(specs)} replays", flush=True)
+    ref = oracle_lib.run_log(logs, specs)
+    assert int(ref["n_nbr_visits"].max()) > 0
+    one = specs[specs["trace"] == 0]
+    sim = gpu.Simulator(None, one, logs=logs[:1])
+    info = sim.launch_info()
+    sim.run()
+    got = sim.results()
+    sim.close()
+    assert (info["waves_per_group"], info["lds_bytes"] > 0) == (waves, lds), info
+    compare(got, ref[specs["trace"] == 0], one, f"log of {blocks} blocks, {info}")
+    compare(gpu.run_log(logs, specs), ref, specs, f"logs of {blocks} and 2 blocks")

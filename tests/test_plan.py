@@ -184,3 +184,27 @@ def test_lds_state_leaves_no_simulation_waiting(plan, h, search, tensors):
                 assert n > _resident(few, True) and _resident(few, True) < _resident(few, False)
         else:
             assert n <= _resident(row, True) or _resident(row, True) == _resident(row, False), (n, row)
+
+
+@pytest.mark.parametrize("blocks,walks,simple,mixed", [
+    (4, (4, 1), 1, (4, 1)), (50, (4, 1), 1, (2, 1)), (58, (2, 1), 1, (2, 1)), (66, (1, 1), 1, (1, 1)),
+    (70, (1, 1), 1, (2, 0)), (72, (2, 0), 1, (2, 0)), (80, (1, 0), 1, (1, 0)), (84, (1, 0), 1, (1, 0)),
+    (86, None, 1, None), (90, None, 0, None)])
+def test_logs_stay_in_lds(plan, blocks, walks, simple, mixed):
+    """A residual network's log keeps its state in LDS up to 84 blocks, swept
+    up to 70, with the wavefronts that fit: (waves, swept) of a batch with
+    walk heuristics and of one with a cyclic log beside it, and whether a
+    batch without walks is in LDS."""
+    lg, cyclic = W.resnet_log(seed=1, blocks=blocks), W.random_log(5, n_steps=100, n_const=2)
+    shape = lambda r: (r["waves"], r["sweep_chunks"]) if r["lds_dynamic"] else None
+    for hs in ((W.H_DTR,), (W.H_MSPS, W.H_LRU), (W.H_DTR, W.H_EQ, W.H_LOCAL, W.H_LRU, W.H_SIZE, W.H_RAND)):
+        (row,) = plan([lg], _batch(*[(0, h, 2) for h in hs]), logs=True)
+        assert shape(row) == walks, row
+        assert row["lds_dynamic"] <= LDS
+    (row,) = plan([lg], _batch((0, W.H_EQ, 2), (0, W.H_LRU, 2)), logs=True)
+    assert (row["lds_dynamic"] > 0) == simple and row["waves"] == 1
+    (row,) = plan([lg, cyclic], _batch((0, W.H_DTR, 2), (1, W.H_DTR, 2)), logs=True)
+    assert shape(row) == mixed, row
+    # a large log without walks holds no rows for a small swept one
+    (row,) = plan([lg, W.resnet_log(seed=2, blocks=2)], _batch((0, W.H_LRU, 2), (1, W.H_DTR, 2)), logs=True)
+    assert row["sweep_chunks"] == 1 or walks is None
