@@ -43,7 +43,6 @@ namespace {
 
 constexpr int64_t MAX_ITEMS = int64_t(1) << 26;    // storages, tensors, operators, list entries
 constexpr int64_t MAX_C0_SUM = int64_t(1) << 50;    // keeps every score numerator below 2^51
-constexpr size_t LDS_LIMIT = 160 * 1024;            // dynamic LDS of the log kernel (and the device's)
 
 struct Lowered {
     int32_t S = 0, T = 0, F = 0;
@@ -501,7 +500,7 @@ int log_plan_make(const dtr_log *logs, int32_t n_logs, const dtr_sim_spec *sims,
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
             return give_up(fail(DTR_EHIP, "hipDeviceGetAttribute(maxSharedMemoryPerBlock) failed"));
-        const size_t limit = std::min<size_t>(LDS_LIMIT, (size_t)lds_max);
+        const size_t limit = std::min<size_t>(dtr::LDS_BYTES, (size_t)lds_max);
         auto layout = [&](int32_t nw, bool rows) {
             const size_t lanes = (size_t)dtr::WAVE * (size_t)nw;
             size_t q = 0;

@@ -1279,11 +1279,12 @@ extern "C" hipError_t dtr_launch_log(const dtr::LogKernelArgs *args, hipStream_t
     hipLaunchKernelGGL(logk::log_reset_kernel, dim3(1), dim3(WAVE), 0, stream, args->queue);
     if (args->n_sims > 0) {
         if (args->lds_bytes > 0) {
-            if (args->lds_bytes > 64 * 1024) {
-                hipError_t e = hipFuncSetAttribute((const void *)logk::log_kernel<true>,
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, args->lds_bytes);
-                if (e != hipSuccess) return e;
-            }
+            // the allowance is the process's: always all of a compute unit's
+            // LDS (the kernel has no static LDS), so that launches of several
+            // threads agree
+            const hipError_t e = hipFuncSetAttribute((const void *)logk::log_kernel<true>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
+            if (e != hipSuccess) return e;
             hipLaunchKernelGGL(logk::log_kernel<true>, dim3(args->n_slots), dim3(WAVE * args->waves), args->lds_bytes,
                                stream, *args);
         }
