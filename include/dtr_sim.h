@@ -320,12 +320,13 @@ int dtr_log_create(const dtr_log *logs, int32_t n_logs,
  *                  except under exact h_DTR^eq: one wavefront each);
  * waves_per_group  wavefronts per workgroup: 1, except for operator logs
  *                  whose walk state is in LDS (up to 4) and for traces with
- *                  walk heuristics (up to 8): the first simulates, the
- *                  others join its e* / e_R walk scans; else 4 for traces
- *                  with exact h_DTR^eq simulations (a simulation per
- *                  wavefront);
- * lds_bytes        operator logs: dynamic LDS per workgroup (0: walk state in
- *                  device memory); traces: 0.
+ *                  walk heuristics (up to 8, the largest of their kernels):
+ *                  the first simulates, the others join its e* / e_R walk
+ *                  scans; else 4 for traces with exact h_DTR^eq simulations
+ *                  (a simulation per wavefront);
+ * lds_bytes        dynamic LDS per workgroup, for traces the largest of their
+ *                  kernels (0: their static LDS only, or a log's walk state in
+ *                  device memory).
  * Returns DTR_EINVAL for a NULL argument.  No device work. */
 typedef struct {
     int32_t n_slots;

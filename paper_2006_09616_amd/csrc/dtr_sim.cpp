@@ -871,6 +871,9 @@ int dtr_sim_launch_info(const dtr_sim *h, dtr_launch_info *out)
             out->n_slots = (int32_t)std::max<int64_t>(1, std::min<int64_t>(
                 out->n_slots, (int64_t)((DTR_STATIC_SCRATCH_BYTES - STATIC_HEADER) / (size_t)h->plan.L.bytes)));
         out->lds_bytes = 0;
+        for (int g = 0; g < dtr::N_GROUPS; g++)
+            if (p.count[g] > 0)
+                out->lds_bytes = std::max<int32_t>(out->lds_bytes, (int32_t)dtr::dynamic_lds_bytes(g, p.chunks[g], p.waves[g], p.small_n[g]));
     }
     return DTR_OK;
 }

@@ -40,6 +40,7 @@ def plan(tmp_path_factory):
     for f in (lib.dtr_sim_run, lib.dtr_sim_run_static):
         f.argtypes = [vp, vp]
     lib.dtr_sim_destroy.argtypes = [vp]
+    lib.dtr_sim_launch_info.argtypes = [vp, vp]
     lib.plan_launches.argtypes = [vp, i32]
 
     def launches(programs, specs, logs=False, flags=0, slots=0):
@@ -55,11 +56,14 @@ def plan(tmp_path_factory):
         check((lib.dtr_sim_run_static if flags & D.OPT_STATIC_SCRATCH else lib.dtr_sim_run)(h, None))
         out = (C.c_int64 * (len(FIELDS) * 16))()
         n = lib.plan_launches(out, 16)
+        info = D._LaunchInfo()
+        check(lib.dtr_sim_launch_info(h, C.byref(info)))
         lib.dtr_sim_destroy(h)
         rows = [dict(zip(FIELDS, out[len(FIELDS) * i:])) for i in range(n)]
         assert n > 0 and sum(r["sims"] for r in rows) == len(specs)
         for r in rows:
             assert r["lds_static"] + r["lds_dynamic"] <= LDS, r
+        assert info.lds_bytes == max(r["lds_dynamic"] for r in rows)
         return rows
 
     return launches
