@@ -47,7 +47,7 @@ constexpr int64_t MAX_C0_SUM = int64_t(1) << 50;    // keeps every score numerat
 struct Lowered {
     int32_t S = 0, T = 0, F = 0;
     // storages
-    std::vector<int64_t> s_size, s_c0;
+    std::vector<int64_t> s_size;
     std::vector<uint8_t> s_const;
     std::vector<int32_t> par_off, par, ch_off, ch, dt_off, dt;
     std::vector<int32_t> born_off, born;   // per operator: edges its first run creates (parent, storage)
@@ -347,13 +347,11 @@ private:
         // ordered by the operator creating the edge, so the edges that exist
         // at any time are a prefix; born_* lists each operator's new edges.
         // The costs of the storages at the end bound every score.
-        L.s_c0.assign(S, 0);
         int64_t c0_sum = 0;
         for (int32_t t = 0; t < T; t++) {
             const int32_t st = L.t_storage[t];
             if (L.s_const[st]) continue;
-            L.s_c0[st] += L.op_cost[L.t_op[t]];     // a term per tensor of the storage
-            c0_sum += L.op_cost[L.t_op[t]];
+            c0_sum += L.op_cost[L.t_op[t]];         // a term per tensor of the storage
             if (c0_sum >= MAX_C0_SUM) return bad(-1, "storage costs sum to 2^50 or more");
         }
         {
@@ -391,8 +389,6 @@ private:
                 r.ls_e = L.ls_off[o + 1];
                 r.out_b = L.out_off[o];
                 r.out_e = L.out_off[o + 1];
-                r.rel_b = L.rel_off[o];
-                r.rel_e = L.rel_off[o + 1];
                 r.born_b = L.born_off[o];
                 r.born_e = L.born_off[o + 1];
             }
@@ -427,12 +423,10 @@ size_t bytes_of(const std::vector<T> &v) { return align_up(v.size() * sizeof(T))
 
 size_t log_bytes(const Lowered &d)
 {
-    return bytes_of(d.s_size) + bytes_of(d.s_c0) + bytes_of(d.s_const) + bytes_of(d.par_off) + bytes_of(d.par) +
-           bytes_of(d.ch_off) + bytes_of(d.ch) + bytes_of(d.dt_off) + bytes_of(d.dt) + bytes_of(d.t_storage) +
-           bytes_of(d.t_op) + bytes_of(d.t_alias) + bytes_of(d.op_cost) + bytes_of(d.op_need) +
-           bytes_of(d.in_off) + bytes_of(d.in) + bytes_of(d.ls_off) + bytes_of(d.ls) + bytes_of(d.out_off) +
-           bytes_of(d.out) + bytes_of(d.rel_off) + bytes_of(d.rel) + bytes_of(d.req) + bytes_of(d.born_off) +
-           bytes_of(d.born) + bytes_of(d.op) + bytes_of(d.inr) + bytes_of(d.outr) + 29 * ALIGN;
+    return bytes_of(d.s_size) + bytes_of(d.s_const) + bytes_of(d.par_off) + bytes_of(d.par) + bytes_of(d.ch_off) +
+           bytes_of(d.ch) + bytes_of(d.dt_off) + bytes_of(d.dt) + bytes_of(d.t_storage) + bytes_of(d.t_op) +
+           bytes_of(d.op) + bytes_of(d.inr) + bytes_of(d.outr) + bytes_of(d.ls) + bytes_of(d.born) +
+           bytes_of(d.rel_off) + bytes_of(d.rel) + bytes_of(d.req) + 18 * ALIGN;
 }
 
 }  // namespace
@@ -651,7 +645,6 @@ int log_plan_upload(LogPlan *p, uint8_t *ws, hipStream_t st)
         D.sweep = d.sweep && p->sweeps;
         D.pad = 0;
         D.s_size = put(d.s_size);
-        D.s_c0 = put(d.s_c0);
         D.s_const = put(d.s_const);
         D.par_off = put(d.par_off);
         D.par = put(d.par);
@@ -661,19 +654,10 @@ int log_plan_upload(LogPlan *p, uint8_t *ws, hipStream_t st)
         D.dt = put(d.dt);
         D.t_storage = put(d.t_storage);
         D.t_op = put(d.t_op);
-        D.t_alias = put(d.t_alias);
-        D.op_cost = put(d.op_cost);
-        D.op_need = put(d.op_need);
-        D.in_off = put(d.in_off);
-        D.in = put(d.in);
-        D.ls_off = put(d.ls_off);
         D.ls = put(d.ls);
-        D.out_off = put(d.out_off);
-        D.out = put(d.out);
         D.rel_off = put(d.rel_off);
         D.rel = put(d.rel);
         D.req = put(d.req);
-        D.born_off = put(d.born_off);
         D.born = put(d.born);
     }
     std::memcpy(H + p->desc_off, descs.data(), sizeof(dtr::LogProgDev) * n_logs);

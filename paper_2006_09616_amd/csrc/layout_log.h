@@ -16,7 +16,7 @@ namespace dtr {
 // for an output, whether it is a view.
 struct __attribute__((aligned(16))) LogOp {
     int64_t cost, need;
-    int32_t in_b, in_e, ls_b, ls_e, out_b, out_e, rel_b, rel_e, born_b, born_e, pad0, pad1;
+    int32_t in_b, in_e, ls_b, ls_e, out_b, out_e, born_b, born_e, pad[4];
 };
 static_assert(sizeof(LogOp) == 64, "operator record layout");
 struct __attribute__((aligned(16))) LogRef {
@@ -28,7 +28,6 @@ struct LogProgDev {
     int32_t S, T, F, n_req;
     // storages
     const int64_t *s_size;        // [S]
-    const int64_t *s_c0;          // [S] summed cost of the operators computing its tensors (end of log)
     const uint8_t *s_const;       // [S] constant (pinned from creation)
     const int32_t *par_off, *par; // storage graph: parents (distinct input storages of those operators)
     const int32_t *ch_off, *ch;   //   and children; each list in the order its edges are created
@@ -36,19 +35,14 @@ struct LogProgDev {
     // tensors
     const int32_t *t_storage;     // [T]
     const int32_t *t_op;          // [T]
-    const uint8_t *t_alias;       // [T] a view of another tensor's storage
     // operators, in log order
-    const int64_t *op_cost;       // [F]
-    const int64_t *op_need;       // [F] summed size of its non-view outputs
-    const int32_t *in_off, *in;   // input tensors, listed order
-    const int32_t *ls_off, *ls;   // distinct input storages (locking)
-    const int32_t *out_off, *out; // output tensors
+    const LogOp *op;              // [F]
+    const LogRef *inr, *outr;     // input tensors in listed order; output tensors
+    const int32_t *ls;            // distinct input storages (locking)
+    const int32_t *born;          // (parent, storage) edges the operators' first runs create
     const int32_t *rel_off, *rel; // storages released after each operator, in log order
     const int32_t *req;           // [n_req] tensors still referenced at the end, ascending
-    const LogOp *op;              // [F]
-    const LogRef *inr, *outr;     // the operators' inputs and outputs
     int32_t sweep, pad;           // walks are swept: every edge goes from a smaller storage id to a larger, and the rows are in LDS
-    const int32_t *born_off, *born; // per operator: (parent, storage) edges its first run creates
 };
 
 // Per-slot working memory of the log replay, sized for the largest log of

@@ -108,14 +108,11 @@ struct ProgG {
     int32_t sweep;
     const GAS LogOp *op;
     const GAS LogRef *inr, *outr;
-    const GAS int64_t *s_size, *s_c0;
+    const GAS int64_t *s_size;
     const GAS uint8_t *s_const;
     const GAS int32_t *par_off, *par, *ch_off, *ch, *dt_off, *dt;
     const GAS int32_t *t_storage, *t_op;
-    const GAS uint8_t *t_alias;
-    const GAS int64_t *op_cost, *op_need;
-    const GAS int32_t *in_off, *in, *ls_off, *ls, *out_off, *out, *rel_off, *rel, *req;
-    const GAS int32_t *born_off, *born;
+    const GAS int32_t *ls, *born, *rel_off, *rel, *req;
 };
 
 __device__ __forceinline__ ProgG prog_global(const LogProgDev &d)
@@ -130,7 +127,6 @@ __device__ __forceinline__ ProgG prog_global(const LogProgDev &d)
     g.inr = (const GAS LogRef *)d.inr;
     g.outr = (const GAS LogRef *)d.outr;
     g.s_size = (const GAS int64_t *)d.s_size;
-    g.s_c0 = (const GAS int64_t *)d.s_c0;
     g.s_const = (const GAS uint8_t *)d.s_const;
     g.par_off = (const GAS int32_t *)d.par_off;
     g.par = (const GAS int32_t *)d.par;
@@ -140,19 +136,10 @@ __device__ __forceinline__ ProgG prog_global(const LogProgDev &d)
     g.dt = (const GAS int32_t *)d.dt;
     g.t_storage = (const GAS int32_t *)d.t_storage;
     g.t_op = (const GAS int32_t *)d.t_op;
-    g.t_alias = (const GAS uint8_t *)d.t_alias;
-    g.op_cost = (const GAS int64_t *)d.op_cost;
-    g.op_need = (const GAS int64_t *)d.op_need;
-    g.in_off = (const GAS int32_t *)d.in_off;
-    g.in = (const GAS int32_t *)d.in;
-    g.ls_off = (const GAS int32_t *)d.ls_off;
     g.ls = (const GAS int32_t *)d.ls;
-    g.out_off = (const GAS int32_t *)d.out_off;
-    g.out = (const GAS int32_t *)d.out;
     g.rel_off = (const GAS int32_t *)d.rel_off;
     g.rel = (const GAS int32_t *)d.rel;
     g.req = (const GAS int32_t *)d.req;
-    g.born_off = (const GAS int32_t *)d.born_off;
     g.born = (const GAS int32_t *)d.born;
     return g;
 }
@@ -840,7 +827,7 @@ __device__ __forceinline__ int32_t op_load(const Sim<L> &s, int32_t o)
 {
     return ((const GAS int32_t *)(s.P.op + o))[s.lane & 15];
 }
-enum { OP_COST = 0, OP_NEED = 2, OP_IN = 4, OP_LS = 6, OP_OUT = 8, OP_REL = 10, OP_BORN = 12 };
+enum { OP_COST = 0, OP_NEED = 2, OP_IN = 4, OP_LS = 6, OP_OUT = 8, OP_BORN = 10 };
 __device__ __forceinline__ int32_t op_word(int32_t rv, int k) { return __builtin_amdgcn_readlane(rv, k); }
 __device__ __forceinline__ int64_t op_word64(int32_t rv, int k)
 {

@@ -3,6 +3,7 @@ against a recorded device (tests/host_plan.cpp), so that limits of workgroups
 and LDS are checked for batches of every shape without a GPU."""
 import ctypes as C
 import os
+import re
 import shutil
 import subprocess
 
@@ -212,3 +213,17 @@ def test_logs_stay_in_lds(plan, blocks, walks, simple, mixed):
     # a large log without walks holds no rows for a small swept one
     (row,) = plan([lg, W.resnet_log(seed=2, blocks=2)], _batch((0, W.H_LRU, 2), (1, W.H_DTR, 2)), logs=True)
     assert row["sweep_chunks"] == 1 or walks is None
+
+
+@pytest.mark.parametrize("header,struct,source", [("layout.h", "TraceDev", "replay.hip"),
+                                                  ("layout_log.h", "LogProgDev", "replay_log.hip")])
+def test_every_uploaded_table_is_read(header, struct, source):
+    """A program's device tables are those its kernel reads."""
+    body = open(os.path.join(CSRC, header)).read()
+    body = body[body.index(f"struct {struct} {{"):]
+    body = re.sub(r"//.*", "", body[:body.index("\n};")])
+    code = re.sub(r"//.*|\w+\.\w+ = \([^;]*\)d\.\w+;", "", open(os.path.join(CSRC, source)).read())
+    tables = [t for line in body.splitlines() if "*" in line for t in re.findall(r"\*\s*(\w+)", line)]
+    assert len(tables) > 10
+    unread = [t for t in tables if not re.search(rf"\b(t|P)\.{t}\b", code)]
+    assert not unread, unread
