@@ -4,7 +4,11 @@
 // Control is wave-uniform: every lane computes the same clock, memory,
 // counters and stack frame, and a state update is stored by every lane with
 // the same value, so each lane later reads its own write.  Lanes work apart
-// where the work is wide:
+// where the work is wide (what one lane then stores and others read is
+// ordered: a wavefront's accesses execute in order, and lds_order or
+// wave_sync keeps the compiler to it):
+//   * an operator's input storages are locked, stamped and unlocked by a lane
+//     each;
 //   * the eviction search scores one storage per lane per round and reduces
 //     the exact (score, id) minimum across the wave (scores N/D compared by
 //     128-bit cross-multiplication, ties to the smaller storage id);
@@ -844,10 +848,11 @@ __device__ __forceinline__ LogRef ref_load(const GAS LogRef *list, bool want, in
 
 // the locks of an operator's distinct input storages, one lane each
 template <bool L>
-__device__ __forceinline__ void lock_storages(Sim<L> &s, int32_t rv, int32_t d)
+__device__ __forceinline__ void lock_storages(Sim<L> &s, int32_t rv)
 {
     const int32_t e = op_word(rv, OP_LS + 1);
-    for (int32_t k = op_word(rv, OP_LS) + s.lane; k < e; k += WAVE) s.locks[s.P.ls[k]] += d;
+    for (int32_t k = op_word(rv, OP_LS) + s.lane; k < e; k += WAVE) s.locks[s.P.ls[k]] += 1;
+    lds_order();
 }
 
 // run operator o (record rv) once its inputs are defined: allocate its new
@@ -934,6 +939,7 @@ __device__ void execute(Sim<L> &s, int32_t rv, bool remat)
     if (s.clock >= CLOCK_LIMIT) { s.status = STATUS_CLOCK; return; }
     if (in_st >= 0) s.locks[in_st] -= 1;
     for (int32_t k = lb + WAVE + s.lane; k < le; k += WAVE) s.locks[s.P.ls[k]] -= 1;
+    lds_order();
     if (remat && s.policy == POLICY_BANISH)
         for (int32_t e = op_word(rv, OP_IN), ie = op_word(rv, OP_IN + 1); e < ie; e++) {
             const int32_t in = s.P.inr[e].st;
@@ -949,7 +955,7 @@ __device__ void call(Sim<L> &s, int32_t o, int32_t remat)
 {
     int32_t depth = 0;
     int32_t rv = op_load(s, o), next = op_word(rv, OP_IN);
-    lock_storages(s, rv, 1);
+    lock_storages(s, rv);
     for (;;) {
         const int32_t end = op_word(rv, OP_IN + 1);
         int32_t found = -1, found_op = 0;
@@ -980,7 +986,7 @@ __device__ void call(Sim<L> &s, int32_t o, int32_t remat)
             remat = 1;
             rv = op_load(s, o);
             next = op_word(rv, OP_IN);
-            lock_storages(s, rv, 1);
+            lock_storages(s, rv);
             continue;
         }
         execute(s, rv, remat != 0);

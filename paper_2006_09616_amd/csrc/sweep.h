@@ -14,8 +14,9 @@ __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_bal
 // a wave-uniform lane mask as this lane's predicate
 __device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
-// Keep the compiler from moving LDS accesses across (one wavefront's LDS
-// accesses execute in order, so nothing has to be waited for).
+// Keep the compiler from moving memory accesses across (one wavefront's
+// accesses to LDS, and to a device-memory address, execute in order, so
+// nothing has to be waited for).
 __device__ __forceinline__ void lds_order()
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
