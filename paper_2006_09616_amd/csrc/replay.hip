@@ -82,7 +82,7 @@ static_assert(LB == NB_HEAD, "a cache build may take its first chunk from the re
 // top of the rematerialization stack in LDS (| HC_SMALL).  Walks are swept
 // (HC_WALK | HC_SWEEP) or go lane by lane (HC_WALK), in kernels and groups of
 // their own: one kernel with both took 245 registers and 408 bytes of scratch
-// a lane, where the lane walks alone take 197 and none.
+// a lane, the lane walks alone take 198 and 160 (the helpers' call).
 enum { HC_EQ = 0, HC_WALK = 1, HC_SIMPLE = 2, HC_APPROX = 4, HC_SMALL = 8, HC_SWEEP = 16 };
 __host__ __device__ constexpr int cls(int hc) { return hc & 3; }
 __host__ __device__ constexpr bool approx(int hc) { return (hc & HC_APPROX) != 0; }
@@ -1714,9 +1714,11 @@ __device__ void walk_scan(Sim<HC> &s, const Filter &F, Best &best, int64_t &scor
 
 // A helper wavefront of a walk heuristic's workgroup: joins the simulating
 // wavefront's walk scans (the three workgroup barriers of each) until it is
-// released at the end of the simulation.
+// released at the end of the simulation.  (Left to the compiler, which calls it
+// for the lane walks: inlined, their registers are shared out with the
+// simulation's, and the walks of a 6000-operation DAG took 185 ms, not 170.)
 template <int HC>
-__device__ __forceinline__ void help_walks(const KernelArgs &a, const Slot<HC> &S, int32_t lane, int32_t wave, LAS WalkCtl *C,
+__device__ void help_walks(const KernelArgs &a, const Slot<HC> &S, int32_t lane, int32_t wave, LAS WalkCtl *C,
                            LAS uint8_t *sweep_lds)
 {
     for (;;) {
