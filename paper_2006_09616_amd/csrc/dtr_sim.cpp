@@ -530,20 +530,28 @@ struct dtr_sim {
     hipStream_t last_stream = nullptr;
     bool ran = false;
     int32_t n_sims = 0;
-    // a batch with simulations in several groups runs each group's kernel on
-    // a stream of its own (default priority), forked from and joined back to
-    // the caller's stream by events, so that the groups overlap
-    hipStream_t aux[dtr::N_GROUPS] = {};
+    // a batch with simulations in several groups runs the first group's kernel
+    // on the caller's stream and the others on streams of the handle (default
+    // priority), forked from and joined back to the caller's by events, so
+    // that the groups overlap.  Streams run at once only on different hardware
+    // queues, of which the runtime has four and takes the least used for a new
+    // stream: every handle creates as many as there are, which leaves their
+    // use even, and runs on the first three, which are not the caller's.  (A
+    // stream per group: of seven live handles of a three-group ResNet sweep
+    // the third, fourth and seventh took 8.2 to 8.9 ms, the others 4.7; so, all
+    // take 4.7.)
+    static constexpr int HW_QUEUES = 4;
+    hipStream_t aux[HW_QUEUES] = {};
     hipEvent_t fork = nullptr, join[dtr::N_GROUPS] = {};
     uint32_t *last_queue = nullptr;       // counter block of the last trace run
     hipStream_t progress_stream = nullptr;  // dtr_sim_progress's reads
     ~dtr_sim()
     {
         dtrhost::log_plan_free(log);
-        for (int g = 0; g < dtr::N_GROUPS; g++) {
-            if (aux[g]) (void)hipStreamDestroy(aux[g]);
-            if (join[g]) (void)hipEventDestroy(join[g]);
-        }
+        for (hipStream_t a : aux)
+            if (a) (void)hipStreamDestroy(a);
+        for (hipEvent_t j : join)
+            if (j) (void)hipEventDestroy(j);
         if (fork) (void)hipEventDestroy(fork);
         if (progress_stream) (void)hipStreamDestroy(progress_stream);
     }
@@ -631,9 +639,8 @@ int dtr_sim_create(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec
     if (groups > 1) {
         bool okk = hipEventCreateWithFlags(&h->fork, hipEventDisableTiming) == hipSuccess;
         for (int c = 0; okk && c < dtr::N_GROUPS; c++)
-            if (p.count[c] > 0)
-                okk = hipStreamCreateWithFlags(&h->aux[c], hipStreamNonBlocking) == hipSuccess &&
-                      hipEventCreateWithFlags(&h->join[c], hipEventDisableTiming) == hipSuccess;
+            if (p.count[c] > 0) okk = hipEventCreateWithFlags(&h->join[c], hipEventDisableTiming) == hipSuccess;
+        for (hipStream_t &a : h->aux) okk = okk && hipStreamCreateWithFlags(&a, hipStreamNonBlocking) == hipSuccess;
         if (!okk) {
             rc = fail(DTR_EHIP, "stream or event creation failed");
             delete h;
@@ -657,7 +664,8 @@ namespace {
 // Enqueue the replay kernels of a trace batch: slots from `slots` (at most
 // `max_slots` resident simulations), work counters at `queue`.  When several
 // groups have simulations, the slots are shared out in proportion to their
-// simulations and each group's kernel runs on its own stream.
+// simulations and up to four groups' kernels run at once, each on its own
+// stream.
 int launch_traces(dtr_sim *h, void *stream, uint8_t *slots, uint32_t *queue, int64_t max_slots)
 {
     const Plan &p = h->plan;
@@ -714,7 +722,7 @@ int launch_traces(dtr_sim *h, void *stream, uint8_t *slots, uint32_t *queue, int
     if (e == hipSuccess && fan) e = hipEventRecord(h->fork, st);
     for (int k = 0; e == hipSuccess && k < ng; k++) {
         const int c = groups[k];
-        hipStream_t gs = fan && k > 0 ? h->aux[c] : st;
+        hipStream_t gs = fan && k > 0 ? h->aux[(k - 1) % (dtr_sim::HW_QUEUES - 1)] : st;
         if (gs != st) e = hipStreamWaitEvent(gs, h->fork, 0);
         if (e == hipSuccess) e = dtr_launch_group(&a[c], c, gs);
         if (e == hipSuccess && gs != st) e = hipEventRecord(h->join[c], gs);

@@ -16,9 +16,11 @@ struct PlanLaunch {
     int64_t group;           // -1: operator logs
     // (logs: sweep_chunks says whether any log is swept)
     int64_t sims, slots, slot_bytes, waves, sweep_chunks, small_n, lds_static, lds_dynamic;
+    int64_t stream;          // 0: the caller's
     int64_t small_at;        // where the state words and stacks start in the dynamic LDS
 };
 static std::vector<PlanLaunch> launches;
+static int64_t streams;     // created so far
 static std::vector<uint8_t> scratch(DTR_STATIC_SCRATCH_BYTES + 256);
 
 extern "C" {
@@ -34,7 +36,7 @@ hipError_t hipMemcpyAsync(void *to, const void *from, size_t n, hipMemcpyKind, h
     std::memcpy(to, from, n);
     return hipSuccess;
 }
-hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)(uintptr_t)64; return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)(uintptr_t)++streams; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
@@ -50,19 +52,19 @@ hipError_t dtr_static_scratch(void **p, size_t *bytes)
     return hipSuccess;
 }
 hipError_t dtr_launch_reset(uint32_t *, hipStream_t) { return hipSuccess; }
-hipError_t dtr_launch_group(const dtr::KernelArgs *a, int32_t group, hipStream_t)
+hipError_t dtr_launch_group(const dtr::KernelArgs *a, int32_t group, hipStream_t st)
 {
     launches.push_back({group, a->n_sims, a->n_slots, a->L.bytes, a->L.walk_waves, a->sweep_chunks,
                         a->small_n, dtr::static_lds_bytes(group),
                         dtr::dynamic_lds_bytes(group, a->sweep_chunks, a->L.walk_waves, a->small_n),
-                        dtr::dynamic_lds_bytes(group, a->sweep_chunks, a->L.walk_waves, 0)});
+                        (int64_t)(uintptr_t)st, dtr::dynamic_lds_bytes(group, a->sweep_chunks, a->L.walk_waves, 0)});
     return hipSuccess;
 }
 hipError_t dtr_launch_log(const dtr::LogKernelArgs *a, hipStream_t)
 {
     int64_t sweeps = 0;
     for (int32_t i = 0; i < a->n_sims; i++) sweeps |= a->progs[a->specs[i].trace].sweep;
-    launches.push_back({-1, a->n_sims, a->n_slots, a->L.bytes, a->waves, sweeps, 0, 0, a->lds_bytes, 0});
+    launches.push_back({-1, a->n_sims, a->n_slots, a->L.bytes, a->waves, sweeps, 0, 0, a->lds_bytes, 0, 0});
     return hipSuccess;
 }
 

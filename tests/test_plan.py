@@ -18,7 +18,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(ROOT, "paper_2006_09616_amd", "csrc")
 LDS = 160 * 1024
 FIELDS = ["group", "sims", "slots", "slot_bytes", "waves", "sweep_chunks", "small_n", "lds_static", "lds_dynamic",
-          "small_at"]
+          "stream", "small_at"]
 
 
 @pytest.fixture(scope="module")
@@ -227,3 +227,21 @@ def test_every_uploaded_table_is_read(header, struct, source):
     assert len(tables) > 10
     unread = [t for t in tables if not re.search(rf"\b(t|P)\.{t}\b", code)]
     assert not unread, unread
+
+
+def test_groups_run_at_once_on_streams_of_different_queues(plan):
+    """Up to four groups each on a stream of its own, the first on the
+    caller's; every handle with several groups creates four streams, so that
+    handles leave the hardware queues evenly used."""
+    short, long_ = W.chain_trace(100), W.chain_trace(1100)
+    parts = [(0, W.H_DTR, 2), (1, W.H_DTR, 2), (0, W.H_EQ, 2), (0, W.H_LRU, 2), (0, W.H_DTR, 2, 3), (0, W.H_LRU, 2, 3),
+             (0, W.H_EQ, 2, 3), (1, W.H_DTR, 2, 3)]
+    last = None
+    for n in range(1, 9):
+        rows = plan([short, long_], _batch(*parts[:n]))
+        streams = [r["stream"] for r in rows]
+        assert len(rows) == n and streams[0] == 0
+        assert len(set(streams)) == min(n, 4) and 0 not in streams[1:]
+        if n > 1:
+            assert last is None or min(streams[1:]) == last + 4
+            last = min(streams[1:])
