@@ -95,7 +95,7 @@ struct Derived {
     int32_t n = 0, F = 0;
     std::vector<int64_t> size, c0, cost;
     std::vector<uint8_t> flags;
-    std::vector<int32_t> producer, out, in_off, in, ch_off, ch, adj_off, adj, rel_off, rel, req;
+    std::vector<int32_t> producer, out, in_off, in, ch_off, ch, adj_off, adj, rel_off, rel, req, consts;
     std::vector<dtr::TRecX> rec;
     std::vector<dtr::SweepRec> sw;   // walk heuristics' sweep tables (make_sweep)
     std::vector<uint16_t> sx;
@@ -237,7 +237,10 @@ int validate_and_derive(const dtr_trace &tr, int32_t index, Derived &d)
     }
     for (int32_t t = 0; t < n; t++) {
         if (d.flags[t] & DTR_FLAG_REQUIRED) d.req.push_back(t);
-        if (d.flags[t] & DTR_FLAG_CONSTANT) d.const_mem += d.size[t];
+        if (d.flags[t] & DTR_FLAG_CONSTANT) {
+            d.consts.push_back(t);
+            d.const_mem += d.size[t];
+        }
     }
     return DTR_OK;
 }
@@ -295,9 +298,10 @@ size_t bytes_of(const std::vector<T> &v) { return align_up(v.size() * sizeof(T))
 
 size_t trace_bytes(const Derived &d)
 {
-    return bytes_of(d.flags) + bytes_of(d.out) + bytes_of(d.in) + bytes_of(d.ch_off) + bytes_of(d.ch) +
-           bytes_of(d.adj) + bytes_of(d.rel_off) + bytes_of(d.rel) + bytes_of(d.req) + bytes_of(d.rec) +
-           bytes_of(d.sw) + bytes_of(d.sx) + 8 * ALIGN;
+    return bytes_of(d.size) + bytes_of(d.c0) + bytes_of(d.flags) + bytes_of(d.producer) + bytes_of(d.out) +
+           bytes_of(d.cost) + bytes_of(d.in_off) + bytes_of(d.in) + bytes_of(d.ch_off) + bytes_of(d.ch) +
+           bytes_of(d.adj_off) + bytes_of(d.adj) + bytes_of(d.rel_off) + bytes_of(d.rel) + bytes_of(d.req) +
+           bytes_of(d.consts) + bytes_of(d.rec) + bytes_of(d.sw) + bytes_of(d.sx) + 8 * ALIGN;
 }
 
 int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sims, int32_t n_sims,
@@ -611,17 +615,24 @@ int dtr_sim_create(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec
         D.n = d.n;
         D.F = d.F;
         D.n_req = (int32_t)d.req.size();
-        D.pad = 0;
+        D.n_const = (int32_t)d.consts.size();
         D.const_mem = d.const_mem;
+        D.size = put(d.size);
+        D.c0 = put(d.c0);
         D.flags = put(d.flags);
+        D.producer = put(d.producer);
         D.out = put(d.out);
+        D.cost = put(d.cost);
+        D.in_off = put(d.in_off);
         D.in = put(d.in);
         D.ch_off = put(d.ch_off);
         D.ch = put(d.ch);
+        D.adj_off = put(d.adj_off);
         D.adj = put(d.adj);
         D.rel_off = put(d.rel_off);
         D.rel = put(d.rel);
         D.req = put(d.req);
+        D.consts = put(d.consts);
         D.rec = put(d.rec);
         D.sw = d.sw.empty() ? nullptr : put(d.sw);
         D.sx = d.sw.empty() ? nullptr : put(d.sx);

@@ -73,17 +73,24 @@ constexpr int64_t SWEEP_MAX_POOL = int64_t(1) << (32 - SWEEP_POS_SHIFT);
 struct TraceDev {
     int32_t n;               // tensors
     int32_t F;               // ops
-    int32_t n_req, pad;
+    int32_t n_req, n_const;
     int64_t const_mem;       // memory held by constants
+    const int64_t *size;     // [n]
+    const int64_t *c0;       // [n]
     const uint8_t *flags;    // [n]
+    const int32_t *producer; // [n]  -1 for constants
     const int32_t *out;      // [F]
+    const int64_t *cost;     // [F]
+    const int32_t *in_off;   // [F+1]
     const int32_t *in;       // [E]
     const int32_t *ch_off;   // [n+1]
     const int32_t *ch;       // [E]
+    const int32_t *adj_off;  // [n+1]
     const int32_t *adj;      // [2E]
     const int32_t *rel_off;  // [F+1]
     const int32_t *rel;      // [<= n]
     const int32_t *req;      // [n_req]
+    const int32_t *consts;   // [n_const]
     const TRecX *rec;        // [n]
     const SweepRec *sw;      // [F], null when the trace's walks go lane by lane
     const uint16_t *sx;

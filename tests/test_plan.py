@@ -215,17 +215,15 @@ def test_logs_stay_in_lds(plan, blocks, walks, simple, mixed):
     assert row["sweep_chunks"] == 1 or walks is None
 
 
-@pytest.mark.parametrize("header,struct,source", [("layout.h", "TraceDev", "replay.hip"),
-                                                  ("layout_log.h", "LogProgDev", "replay_log.hip")])
-def test_every_uploaded_table_is_read(header, struct, source):
-    """A program's device tables are those its kernel reads."""
-    body = open(os.path.join(CSRC, header)).read()
-    body = body[body.index(f"struct {struct} {{"):]
+def test_every_uploaded_log_table_is_read():
+    """An operator log's device tables are those its kernel reads."""
+    body = open(os.path.join(CSRC, "layout_log.h")).read()
+    body = body[body.index("struct LogProgDev {"):]
     body = re.sub(r"//.*", "", body[:body.index("\n};")])
-    code = re.sub(r"//.*|\w+\.\w+ = \([^;]*\)d\.\w+;", "", open(os.path.join(CSRC, source)).read())
+    code = re.sub(r"//.*|\w+\.\w+ = \([^;]*\)d\.\w+;", "", open(os.path.join(CSRC, "replay_log.hip")).read())
     tables = [t for line in body.splitlines() if "*" in line for t in re.findall(r"\*\s*(\w+)", line)]
     assert len(tables) > 10
-    unread = [t for t in tables if not re.search(rf"\b(t|P)\.{t}\b", code)]
+    unread = [t for t in tables if not re.search(rf"\bP\.{t}\b", code)]
     assert not unread, unread
 
 
