@@ -410,7 +410,7 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     int64_t most = opt && opt->slots > 0 ? opt->slots : n_sims;         // simulations in flight
     if (p.static_only)
         most = std::min<int64_t>(most, (int64_t)((DTR_STATIC_SCRATCH_BYTES - STATIC_HEADER) / (size_t)L.bytes));
-    auto in_flight = [&](int g) { return std::min<int64_t>(p.count[g], most * p.count[g] / n_sims); };
+    auto in_flight = [&](int g) { return std::min<int64_t>(p.count[g], most * p.count[g] / std::max(1, n_sims)); };
     // simulations of a group that the device holds at once
     auto resident = [&](int g, int32_t waves, int32_t small_n) {
         const int64_t wg = dtr::static_lds_bytes(g) + dtr::dynamic_lds_bytes(g, p.chunks[g], waves, small_n);
@@ -444,11 +444,10 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     slots = std::min<int64_t>(slots, std::max<int32_t>(1, n_sims));
     p.n_slots = (int32_t)std::max<int64_t>(1, slots);
 
-    // grouped by heuristic class (one kernel specialisation each), then the
-    // Likely heaviest first: each trace's tightest simulation (budget relative
-    // to the trace's no-eviction peak, in steps of 1/1024 of the peak, so
-    // that budgets set at one fraction of their traces' peaks tie) before the
-    // rest, those by tightness, then the longest trace, then the exact ratio;
+    // grouped by kernel specialisation, then likely heaviest first: each
+    // trace's tightest simulation (budget relative to the trace's no-eviction
+    // peak, in steps of 1/1024 of the peak, so that budgets set at one
+    // fraction of their traces' peaks tie) before the rest, those by tightness, then the longest trace, then the exact ratio;
     // then the rest trace by trace (longest first), each trace's tightest
     // first, so that the simulations of one trace run side by side and share
     // its tables in the caches.
@@ -491,7 +490,7 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
     // transformer budgets under h_DTR^eq, ignore-small (five in place of
     // eight), 28.2 and 18.2 ms
     for (int g = 0; g < dtr::N_GROUPS; g++) {
-        if (group_n[g] > dtr::SMALL_TENSORS || g % dtr::N_CLASSES == dtr::GROUP_WALK) continue;
+        if (p.count[g] == 0 || group_n[g] > dtr::SMALL_TENSORS || g % dtr::N_CLASSES == dtr::GROUP_WALK) continue;
         const int32_t sn = std::max(2, (group_n[g] + 1) / 2 * 2);
         const int64_t with = resident(g, p.waves[g], sn), without = resident(g, p.waves[g], 0);
         // (none: eight reach masks of a long trace leave no room for the state words)
