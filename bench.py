@@ -65,7 +65,7 @@ def scan_bytes(specs, res) -> int:
 # copy of known size; valid only for the kernel sources it was measured on.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "replay_kernel_eq_treelstm4096_traffic.md")
 # (the host library too: its dispatch order decides which simulations share the caches)
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2006_09616_amd", "csrc", f) for f in ("replay.hip", "layout.h", "dtr_sim.cpp")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2006_09616_amd", "csrc", f) for f in ("replay.hip", "layout.h", "score.h", "sweep.h", "dtr_sim.cpp")]
 
 
 def kernel_source_digest() -> str:

@@ -67,3 +67,18 @@ def test_cpu_baseline_reports_both_rates_and_parity(oracle_lib):
 def test_ordinals():
     assert [bench.ordinal(n) for n in (1, 2, 3, 4, 11, 12, 13, 21, 61, 111, 1769)] == \
         ["1st", "2nd", "3rd", "4th", "11th", "12th", "13th", "21st", "61st", "111th", "1769th"]
+
+
+def test_traffic_digest_covers_the_kernel_sources():
+    """Every file of the package that the trace kernels include is hashed."""
+    import os
+    import re
+    names = {os.path.basename(f) for f in bench.KERNEL_SOURCES}
+    csrc = os.path.dirname(bench.KERNEL_SOURCES[0])
+    todo, seen = ["replay.hip"], set()
+    while todo:
+        f = todo.pop()
+        if f not in seen and os.path.exists(os.path.join(csrc, f)):
+            seen.add(f)
+            todo += re.findall(r'#include "([\w.]+)"', open(os.path.join(csrc, f)).read())
+    assert seen | {"dtr_sim.cpp"} <= names, seen - names
