@@ -1714,11 +1714,9 @@ __device__ void walk_scan(Sim<HC> &s, const Filter &F, Best &best, int64_t &scor
 
 // A helper wavefront of a walk heuristic's workgroup: joins the simulating
 // wavefront's walk scans (the three workgroup barriers of each) until it is
-// released at the end of the simulation.  (Left to the compiler, which calls it
-// for the lane walks: inlined, their registers are shared out with the
-// simulation's, and the walks of a 6000-operation DAG took 185 ms, not 170.)
+// released at the end of the simulation.
 template <int HC>
-__device__ void help_walks(const KernelArgs &a, const Slot<HC> &S, int32_t lane, int32_t wave, LAS WalkCtl *C,
+__device__ __forceinline__ void help_scans(const KernelArgs &a, const Slot<HC> &S, int32_t lane, int32_t wave, LAS WalkCtl *C,
                            LAS uint8_t *sweep_lds)
 {
     for (;;) {
@@ -1761,6 +1759,15 @@ __device__ void help_walks(const KernelArgs &a, const Slot<HC> &S, int32_t lane,
         if (lane == 0) *(WaveBest *)&C->res[wave] = r;
         __syncthreads();
     }
+}
+
+// The lane walks' helpers: left to the compiler, which makes it a call.
+// Inlined, their registers are shared out with the simulation's, and the walks
+// of a 6000-operation DAG took 185 ms, not 170.
+template <int HC>
+__device__ void help_walks(const KernelArgs &a, const Slot<HC> &S, int32_t lane, int32_t wave, LAS WalkCtl *C)
+{
+    help_scans<HC>(a, S, lane, wave, C, nullptr);
 }
 
 // Score the pool rounds of a scan (each WAVE * U entries) into this
@@ -2612,7 +2619,8 @@ __global__ void __launch_bounds__(cls(HC) == HC_WALK ? MAX_WALK_WAVES * WAVE : l
         if (k >= (uint32_t)a.n_sims) break;
         if constexpr (cls(HC) == HC_WALK) {
             if (wave == 0) run_sim<HC>(a, a.order[k], S, lane, ctl, nw, (LAS uint8_t *)lds_dyn);
-            else help_walks<HC>(a, S, lane, wave, ctl, (LAS uint8_t *)lds_dyn);
+            else if constexpr (swept(HC)) help_scans<HC>(a, S, lane, wave, ctl, (LAS uint8_t *)lds_dyn);
+            else help_walks<HC>(a, S, lane, wave, ctl);
         } else {
             run_sim<HC>(a, a.order[k], S, lane, ctl, 1, nullptr);
         }
