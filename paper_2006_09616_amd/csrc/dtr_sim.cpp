@@ -15,6 +15,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -524,6 +525,83 @@ int make_plan(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec *sim
 
 }  // namespace
 
+namespace {
+
+// The streams of a handle with several groups (default priority).  Streams run
+// at once only on different hardware queues, of which the runtime has four and
+// takes the least used for a new stream: a set has as many streams as there
+// are queues, which leaves their use even, and a launch takes the first three.
+// (A stream per group: of seven live handles of a three-group ResNet sweep the
+// third, fourth and seventh took 8.2 to 8.9 ms, the others 4.7; with sets all
+// take 4.7.)
+struct StreamSet {
+    static constexpr int N = 4;
+    hipStream_t s[N] = {};
+};
+
+// Sets that no handle holds, a few of them, for the next handle on their device
+// (four streams take some 0.25 ms to create, as much as a small batch).  A set
+// is one handle's until the handle is destroyed; work still on its streams is
+// before the next handle's.  Never destroyed at the process's end, where the
+// runtime may be gone already.
+struct StreamPool {
+    static constexpr size_t MAX_FREE = 8;
+    std::mutex mu;
+    std::vector<std::pair<int32_t, StreamSet>> free;
+};
+StreamPool &stream_pool()
+{
+    static StreamPool *p = new StreamPool;
+    return *p;
+}
+
+void streams_destroy(const StreamSet &set)
+{
+    for (hipStream_t s : set.s)
+        if (s) (void)hipStreamDestroy(s);
+}
+
+bool streams_take(int32_t device, StreamSet &set)
+{
+    StreamPool &p = stream_pool();
+    {
+        std::lock_guard<std::mutex> lock(p.mu);
+        for (size_t i = 0; i < p.free.size(); i++)
+            if (p.free[i].first == device) {
+                set = p.free[i].second;
+                p.free.erase(p.free.begin() + i);
+                return true;
+            }
+    }
+    for (hipStream_t &s : set.s)
+        if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) {
+            s = nullptr;
+            streams_destroy(set);
+            return false;
+        }
+    return true;
+}
+
+void streams_give(int32_t device, const StreamSet &set)
+{
+    bool usable = true;                     // not part of a capture that goes on
+    for (hipStream_t s : set.s) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        usable = usable && hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone;
+    }
+    if (usable) {
+        StreamPool &p = stream_pool();
+        std::lock_guard<std::mutex> lock(p.mu);
+        if (p.free.size() < StreamPool::MAX_FREE) {
+            p.free.push_back({device, set});
+            return;
+        }
+    }
+    streams_destroy(set);
+}
+
+}  // namespace
+
 struct dtr_sim {
     Plan plan;
     dtrhost::LogPlan *log = nullptr;    // set for operator logs
@@ -533,26 +611,18 @@ struct dtr_sim {
     hipStream_t last_stream = nullptr;
     bool ran = false;
     int32_t n_sims = 0;
-    // a batch with simulations in several groups runs the first group's kernel
-    // on the caller's stream and the others on streams of the handle (default
-    // priority), forked from and joined back to the caller's by events, so
-    // that the groups overlap.  Streams run at once only on different hardware
-    // queues, of which the runtime has four and takes the least used for a new
-    // stream: every handle creates as many as there are, which leaves their
-    // use even, and runs on the first three, which are not the caller's.  (A
-    // stream per group: of seven live handles of a three-group ResNet sweep
-    // the third, fourth and seventh took 8.2 to 8.9 ms, the others 4.7; so, all
-    // take 4.7.)
-    static constexpr int HW_QUEUES = 4;
-    hipStream_t aux[HW_QUEUES] = {};
+    // a batch with simulations in several groups runs their kernels on streams
+    // of the handle, forked from and joined back to the caller's by events, so
+    // that the groups overlap
+    int32_t device = -1;                    // the streams' device (-1: none)
+    StreamSet aux;
     hipEvent_t fork = nullptr, join[dtr::N_GROUPS] = {};
     uint32_t *last_queue = nullptr;       // counter block of the last trace run
     hipStream_t progress_stream = nullptr;  // dtr_sim_progress's reads
     ~dtr_sim()
     {
         dtrhost::log_plan_free(log);
-        for (hipStream_t a : aux)
-            if (a) (void)hipStreamDestroy(a);
+        if (device >= 0) streams_give(device, aux);
         for (hipEvent_t j : join)
             if (j) (void)hipEventDestroy(j);
         if (fork) (void)hipEventDestroy(fork);
@@ -650,7 +720,9 @@ int dtr_sim_create(const dtr_trace *traces, int32_t n_traces, const dtr_sim_spec
         bool okk = hipEventCreateWithFlags(&h->fork, hipEventDisableTiming) == hipSuccess;
         for (int c = 0; okk && c < dtr::N_GROUPS; c++)
             if (p.count[c] > 0) okk = hipEventCreateWithFlags(&h->join[c], hipEventDisableTiming) == hipSuccess;
-        for (hipStream_t &a : h->aux) okk = okk && hipStreamCreateWithFlags(&a, hipStreamNonBlocking) == hipSuccess;
+        int dev = 0;
+        okk = okk && hipGetDevice(&dev) == hipSuccess && streams_take(dev, h->aux);
+        if (okk) h->device = dev;
         if (!okk) {
             rc = fail(DTR_EHIP, "stream or event creation failed");
             delete h;
@@ -674,8 +746,7 @@ namespace {
 // Enqueue the replay kernels of a trace batch: slots from `slots` (at most
 // `max_slots` resident simulations), work counters at `queue`.  When several
 // groups have simulations, the slots are shared out in proportion to their
-// simulations and up to four groups' kernels run at once, each on its own
-// stream.
+// simulations and the groups' kernels run side by side on streams.
 int launch_traces(dtr_sim *h, void *stream, uint8_t *slots, uint32_t *queue, int64_t max_slots)
 {
     const Plan &p = h->plan;
@@ -730,9 +801,18 @@ int launch_traces(dtr_sim *h, void *stream, uint8_t *slots, uint32_t *queue, int
     }
     hipError_t e = dtr_launch_reset(queue, st);
     if (e == hipSuccess && fan) e = hipEventRecord(h->fork, st);
+    int chain = -1;
     for (int k = 0; e == hipSuccess && k < ng; k++) {
         const int c = groups[k];
-        hipStream_t gs = fan && k > 0 ? h->aux[(k - 1) % (dtr_sim::HW_QUEUES - 1)] : st;
+        // with four groups and more, a class's lane walks and sweeps share a
+        // stream: three run at once, a fourth may meet another's queue (trees
+        // with search approximations 0.53 s, 0.69 with the sweeps apart and the
+        // longest group behind the lane walks)
+        if (ng <= 3 || c % dtr::N_CLASSES != dtr::GROUP_SWEEP || k == 0 || groups[k - 1] != c - 1) chain++;
+        // the first group runs on the caller's stream if that is the default
+        // one, whose queue the sets' first streams leave alone
+        const int32_t at = st ? chain : chain - 1;
+        hipStream_t gs = fan && at >= 0 ? h->aux.s[at % (StreamSet::N - 1)] : st;
         if (gs != st) e = hipStreamWaitEvent(gs, h->fork, 0);
         if (e == hipSuccess) e = dtr_launch_group(&a[c], c, gs);
         if (e == hipSuccess && gs != st) e = hipEventRecord(h->join[c], gs);

@@ -5,6 +5,7 @@
 // reads what a batch would have launched.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <cstring>
 #include <vector>
@@ -20,7 +21,8 @@ struct PlanLaunch {
     int64_t small_at;        // where the state words and stacks start in the dynamic LDS
 };
 static std::vector<PlanLaunch> launches;
-static int64_t streams;     // created so far
+static std::atomic<int64_t> streams, destroyed;     // so far
+static hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
 static std::vector<uint8_t> scratch(DTR_STATIC_SCRATCH_BYTES + 256);
 
 extern "C" {
@@ -36,8 +38,9 @@ hipError_t hipMemcpyAsync(void *to, const void *from, size_t n, hipMemcpyKind, h
     std::memcpy(to, from, n);
     return hipSuccess;
 }
-hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)(uintptr_t)++streams; return hipSuccess; }
-hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)(uintptr_t)(int64_t)++streams; return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { destroyed++; return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st) { *st = capturing; return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = (hipEvent_t)(uintptr_t)64; return hipSuccess; }
@@ -67,6 +70,10 @@ hipError_t dtr_launch_log(const dtr::LogKernelArgs *a, hipStream_t)
     launches.push_back({-1, a->n_sims, a->n_slots, a->L.bytes, a->waves, sweeps, 0, 0, a->lds_bytes, 0, 0});
     return hipSuccess;
 }
+
+// streams created and destroyed so far, and what every stream says of captures
+void plan_streams(int64_t *out) { out[0] = streams; out[1] = destroyed; }
+void plan_capture(int32_t on) { capturing = on ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; }
 
 // the launches since the last call, at most max of them
 int32_t plan_launches(PlanLaunch *out, int32_t max)

@@ -43,8 +43,10 @@ def plan(tmp_path_factory):
     lib.dtr_sim_destroy.argtypes = [vp]
     lib.dtr_sim_launch_info.argtypes = [vp, vp]
     lib.plan_launches.argtypes = [vp, i32]
+    lib.plan_streams.argtypes = [vp]
+    lib.plan_capture.argtypes = [i32]
 
-    def launches(programs, specs, logs=False, flags=0, slots=0):
+    def launches(programs, specs, logs=False, flags=0, slots=0, stream=None):
         opts = {"flags": flags, "slots": slots} if flags or slots else None
         p = (D._PackedLogs if logs else D._Packed)(programs, specs, opts)
         size, h = sz(0), vp()
@@ -54,7 +56,7 @@ def plan(tmp_path_factory):
         ws = np.empty(size.value + 256, np.uint8)               # only the tables at its head are touched
         at = (ws.ctypes.data + 255) // 256 * 256
         check(getattr(lib, kind + "_create")(*p.args(), at, size, None, C.byref(h)))
-        check((lib.dtr_sim_run_static if flags & D.OPT_STATIC_SCRATCH else lib.dtr_sim_run)(h, None))
+        check((lib.dtr_sim_run_static if flags & D.OPT_STATIC_SCRATCH else lib.dtr_sim_run)(h, stream))
         out = (C.c_int64 * (len(FIELDS) * 16))()
         n = lib.plan_launches(out, 16)
         info = D._LaunchInfo()
@@ -67,6 +69,17 @@ def plan(tmp_path_factory):
         assert info.lds_bytes == max(r["lds_dynamic"] for r in rows)
         return rows
 
+    keep = []
+
+    def create(programs, specs):
+        """A handle that has not run, for its caller to destroy."""
+        p, size, h = D._Packed(programs, specs, None), sz(0), vp()
+        assert lib.dtr_sim_workspace_bytes(*p.args(), C.byref(size)) == 0
+        keep.append(np.empty(size.value + 256, np.uint8))
+        assert lib.dtr_sim_create(*p.args(), (keep[-1].ctypes.data + 255) // 256 * 256, size, None, C.byref(h)) == 0
+        return h
+
+    launches.lib, launches.create = lib, create
     return launches
 
 
@@ -227,19 +240,61 @@ def test_every_uploaded_log_table_is_read():
     assert not unread, unread
 
 
-def test_groups_run_at_once_on_streams_of_different_queues(plan):
-    """Up to four groups each on a stream of its own, the first on the
-    caller's; every handle with several groups creates four streams, so that
-    handles leave the hardware queues evenly used."""
+def test_groups_run_at_once_on_streams(plan):
+    """Up to three groups each on a stream of its own, the first on the
+    caller's if that is the default one; with more, a class's lane walks and
+    sweeps share one."""
     short, long_ = W.chain_trace(100), W.chain_trace(1100)
     parts = [(0, W.H_DTR, 2), (1, W.H_DTR, 2), (0, W.H_EQ, 2), (0, W.H_LRU, 2), (0, W.H_DTR, 2, 3), (0, W.H_LRU, 2, 3),
              (0, W.H_EQ, 2, 3), (1, W.H_DTR, 2, 3)]
-    last = None
     for n in range(1, 9):
         rows = plan([short, long_], _batch(*parts[:n]))
-        streams = [r["stream"] for r in rows]
-        assert len(rows) == n and streams[0] == 0
-        assert len(set(streams)) == min(n, 4) and 0 not in streams[1:]
-        if n > 1:
-            assert last is None or min(streams[1:]) == last + 4
-            last = min(streams[1:])
+        at = {r["group"]: r["stream"] for r in rows}
+        assert len(rows) == n and rows[0]["stream"] == 0 and (0 not in [at[g] for g in at if g > 2])
+        if n <= 3:
+            assert len(set(at.values())) == n
+        else:
+            assert all(at[g] == at[g - 1] for g in (2, 6) if g in at and g - 1 in at)
+            assert len(set(at.values())) >= 3
+        mine = {r["group"]: r["stream"] for r in plan([short, long_], _batch(*parts[:n]), stream=1 << 20)}
+        assert (1 << 20 in mine.values()) == (n == 1) and len(set(mine.values())) == min(n, 3)
+
+
+def test_stream_sets_are_kept_for_the_next_handle(plan):
+    """A handle with several groups holds four streams of its own; a few sets
+    are kept for later handles, from any thread, and none that is capturing."""
+    import threading
+    lib, tr = plan.lib, W.chain_trace(20)
+    count = lambda: (lambda v: (lib.plan_streams(v), v[0], v[1])[1:])((C.c_int64 * 2)())
+    two = _batch((0, W.H_DTR, 2), (0, W.H_LRU, 2))
+    plan([tr], _batch((0, W.H_DTR, 2)))
+    none = count()
+    handles = [plan.create([tr], two) for _ in range(10)]
+    held = count()
+    assert 4 * 10 - 4 * 8 <= held[0] - none[0] <= 4 * 10
+    for h in handles:
+        lib.dtr_sim_destroy(h)
+    kept = count()
+    assert kept[1] - held[1] == 4 * 2                      # eight sets are kept
+    handles = [plan.create([tr], two) for _ in range(8)]
+    assert count()[0] == kept[0]
+    lib.plan_capture(1)
+    lib.dtr_sim_destroy(handles.pop())
+    lib.plan_capture(0)
+    assert count()[1] == kept[1] + 4
+    for h in handles:
+        lib.dtr_sim_destroy(h)
+
+    def work():
+        for _ in range(50):
+            mine = [plan.create([tr], two) for _ in range(2)]
+            for h in mine:
+                lib.dtr_sim_destroy(h)
+    threads = [threading.Thread(target=work) for _ in range(4)]
+    before = count()
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    after = count()
+    assert after[0] - before[0] <= 4 * 400 and (after[0] - after[1]) % 4 == 0 and after[0] - after[1] <= 4 * 8
