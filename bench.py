@@ -395,9 +395,11 @@ def main():
         # a launch that lasts minutes reports the operations its walk
         # simulations have executed so far (dtr_sim_progress) while it runs
         t = time.perf_counter()
+        line = 30
         while not log and not sim.done():
-            time.sleep(0.05 if time.perf_counter() - t < 30 else 20)
-            if time.perf_counter() - t >= 30:
+            time.sleep(0.05)
+            if time.perf_counter() - t >= line:
+                line += 20
                 print(f"[bench] {label}: {time.perf_counter() - t:.0f} s, {sim.progress()} operations executed",
                       file=sys.stderr, flush=True)
         torch.cuda.synchronize()
